@@ -182,6 +182,7 @@ int last_launch(nqs_ctx* c) {
 size_t esize(int prec) { return prec == 0 ? 8 : 4; }
 
 size_t layout_holo(nqs_ctx* c, char* base);
+size_t part_bytes(const nqs_ctx* c);
 
 // Walk the workspace; with base == nullptr only the size is computed.
 size_t layout(nqs_ctx* c, char* base) {
@@ -250,8 +251,7 @@ size_t layout(nqs_ctx* c, char* base) {
         b.rrp = (double*)take(8 * 2 * 3 * (size_t)qgt_nbr(d));
         b.pap = (double*)take(8 * (size_t)qgt_nbo(d, b.q));   // p.G p partials
         b.Pop = take(qgt_pop_bytes(d, c->prec));               // r, contraction-1 layout
-        const size_t ks = (size_t)(c->ksplit > b.q.ks ? c->ksplit : b.q.ks);
-        b.part = take(es * ks * PV);
+        b.part = take(part_bytes(c));
     }
     if (c->symm) {
         b.psym = (double*)take(8 * (size_t)c->Psym);
@@ -603,15 +603,22 @@ int read_acceptance(nqs_ctx* c) {
     return take_acceptance(c);
 }
 
+// bytes of the slot buffer `part` (slots of the force and the CG products; also
+// the row slices of sums over a batch)
+size_t part_bytes(const nqs_ctx* c) {
+    const size_t ks = (size_t)(c->ksplit > c->b.q.ks ? c->ksplit : c->b.q.ks);
+    return esize(c->prec) * ks * c->d.Ma * c->d.Na;
+}
+
 // dense Jacobian form: build G once for this batch and set up CG in packed space
 void issue_dense_setup(nqs_ctx* c, double tol, int maxiter, double shift) {
     const int P = (int)c->P;
     {
         PROF(NQS_PROF_JACOBIAN);
-        // (the Gram matrix's buffer is free until the Gram is formed: column-sum partials)
-        launch_jacobian_centred(c->stream, c->d, c->prec, c->b.samples, c->b.tsm, c->Ns, c->b.O,
-                                P, c->Pld, c->b.colsum, (double*)c->b.G,
-                                esize(c->prec) * (size_t)c->P * c->Pld, c->prec == 2);
+        launch_colsum(c->stream, c->d, c->prec, c->b.samples, c->b.tsm, c->Ns, c->b.part,
+                      part_bytes(c), c->ncu, c->b.gacc, true, true, c->b.colsum);
+        launch_jacobian_centred(c->stream, c->d, c->prec, c->b.samples, c->b.tsm, c->Ns, c->Ns,
+                                c->b.O, P, c->Pld, c->b.colsum, c->prec == 2);
     }
     {
         PROF(NQS_PROF_GRAM);
@@ -1881,17 +1888,29 @@ int nqs_jacobian(nqs_ctx* c, const int8_t* s, int64_t n, void* O_out, int center
         return last_launch(c);
     }
     const size_t es = esize(c->prec);
-    for (int64_t k0 = 0; k0 < n; k0 += c->Bx) {
+    if (center && n > 65535) return fail(c, NQS_EINVAL, "centring supports at most 65535 rows");
+    const long nc = (long)((n + c->Bx - 1) / c->Bx);  // the batch in parts of at most Bx rows
+    if (center)  // the column sums first (a single part's activations are kept for the rows)
+        for (long q = 0; q < nc; ++q) {
+            const int64_t k0 = q * c->Bx;
+            const long m = (long)((n - k0) < c->Bx ? (n - k0) : c->Bx);
+            const int8_t* sk = s + (size_t)k0 * c->N;
+            launch_theta(c->stream, c->d, c->prec, c->b.tab, sk, (int)m, c->b.tx, nullptr, 0);
+            launch_colsum(c->stream, c->d, c->prec, sk, c->b.tx, m, c->b.part, part_bytes(c),
+                          c->ncu, c->b.gacc, q == 0, q + 1 == nc, c->b.tmpv);
+        }
+    for (long q = 0; q < nc; ++q) {
+        const int64_t k0 = q * c->Bx;
         const long m = (long)((n - k0) < c->Bx ? (n - k0) : c->Bx);
         const int8_t* sk = s + (size_t)k0 * c->N;
-        launch_theta(c->stream, c->d, c->prec, c->b.tab, sk, (int)m, c->b.tx, nullptr, 0);
-        launch_jacobian(c->stream, c->d, c->prec, sk, c->b.tx, m,
-                        (char*)O_out + es * (size_t)k0 * c->P, (int)c->P, (long)c->P);
-    }
-    if (center) {
-        if (n > 65535) return fail(c, NQS_EINVAL, "centring supports at most 65535 rows");
-        launch_center_cols(c->stream, c->prec, O_out, n, (long)c->P, (int)c->P, c->b.tmpv,
-                           nullptr, 0, false);
+        if (!center || nc > 1)
+            launch_theta(c->stream, c->d, c->prec, c->b.tab, sk, (int)m, c->b.tx, nullptr, 0);
+        char* rows = (char*)O_out + es * (size_t)k0 * c->P;
+        if (center)
+            launch_jacobian_centred(c->stream, c->d, c->prec, sk, c->b.tx, m, (long)n, rows,
+                                    (int)c->P, (long)c->P, c->b.tmpv, false);
+        else
+            launch_jacobian(c->stream, c->d, c->prec, sk, c->b.tx, m, rows, (int)c->P, (long)c->P);
     }
     return last_launch(c);
 }

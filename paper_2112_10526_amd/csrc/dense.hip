@@ -8,35 +8,6 @@
 
 namespace nqs {
 
-// O[k][p] for the packed layout [a | b | W]; row stride ld, zero padding to ld.
-template <typename R>
-__global__ __launch_bounds__(256) void k_jacobian(Dims d, const int8_t* __restrict__ s,
-                                                  const R* __restrict__ tact, long n, int P,
-                                                  long ld, R* __restrict__ O) {
-    const long k = blockIdx.x;
-    if (k >= n) return;
-    const int8_t* sk = s + k * d.N;
-    const R* tk = tact + k * d.Mw;
-    R* row = O + k * ld;
-    for (long p = threadIdx.x; p < ld; p += 256) {
-        R v = (R)0;
-        if (p < P) {
-            long idx = p;
-            if (d.vb) {
-                if (idx < d.N) { row[p] = (R)sk[idx]; continue; }
-                idx -= d.N;
-            }
-            if (d.hb) {
-                if (idx < d.M) { row[p] = tk[idx]; continue; }
-                idx -= d.M;
-            }
-            const long j = idx / d.N, i = idx - j * d.N;
-            v = tk[j] * (R)sk[i];
-        }
-        row[p] = v;
-    }
-}
-
 // colsum[p] = sum_k O[k][p] (fixed order down each column)
 // Column sums in two fixed-order passes: `splits` slices of rows give partial
 // sums (one thread per column and slice), then each column adds its slices in
@@ -127,111 +98,114 @@ __device__ __forceinline__ JacCol jac_col(const Dims& d, long p, int P) {
         if (idx < d.M) return JacCol{1, (int)idx, 0};
         idx -= d.M;
     }
-    const int j = (int)(idx / d.N);
-    return JacCol{2, j, (int)(idx - (long)j * d.N)};
+    const int j = (int)idx / d.N;  // (P fits 32 bits)
+    return JacCol{2, j, (int)idx - j * d.N};
 }
-// Column sums over the same row slices, in the same order, as k_colsum_part,
-// read from the spins and activations instead of a materialised Jacobian.  A
-// missing factor (the spin of a hidden-bias column, the activation of a
-// visible-bias column) is read as the constant 1 with stride 0, so the loop has
-// no branch; 1 * x is x exactly, so the sums are unchanged.
-__device__ const int8_t k_one_s = 1;
+// The Jacobian's rows in one write pass: O[k][p] = t s (CENTER: dJ = (O - cs[p] / n)
+// / sqrt(n), with the column sums cs), zero in the padding columns P <= p < ld.
+// A block writes 1,024 columns of `rpb` rows; each thread finds its four columns'
+// spin and activation once (pointers and row strides, a missing factor being the
+// constant 1, or 0 for padding, with stride 0) and walks the rows, four rows'
+// loads ahead of their arithmetic.  VEC: ld a multiple of 4 and O 16-byte aligned:
+// four neighbouring columns per thread, one 16-byte store per FP32 row; else
+// columns 256 apart, so that every store instruction still covers whole lines.
+// In the VEC form four columns of one hidden unit (N a multiple of 4) read one
+// activation and one word of spins.
+// Bound by the write: 4,000 x 33,344 FP32 entries (534 MB) in 127 us, 4.2 TB/s (a
+// copy moves 5.1 TB/s); with the column sums 150 us, against 1,980 us for the three
+// passes (rows, column sums by one thread per column, centring) it replaces.
+__device__ const int8_t k_one_s = 1, k_zero_s = 0;
 template <typename R>
 __device__ const R k_one_t = (R)1;
-template <typename R>
-__global__ __launch_bounds__(256) void k_colsum_st(Dims d, const int8_t* __restrict__ s,
-                                                   const R* __restrict__ tact, long n, int P,
-                                                   int splits, double* __restrict__ part) {
-    const long p = (long)blockIdx.x * 256 + threadIdx.x;
-    if (p >= P) return;
-    const JacCol c = jac_col(d, p, P);
-    const bool has_s = c.kind != 1, has_t = c.kind != 0;
-    const int8_t* sp = has_s ? s + c.i : &k_one_s;
-    const R* tp = has_t ? tact + c.j : &k_one_t<R>;
-    const long ss = has_s ? d.N : 0, ts = has_t ? d.Mw : 0;
-    const long k0 = n * blockIdx.y / splits, k1 = n * (blockIdx.y + 1) / splits;
-    double acc = 0.0;
-    long k = k0;
-    for (; k + 4 <= k1; k += 4) {  // (loads of four rows issued together; sum order unchanged)
-        const double t0 = (double)tp[k * ts], t1 = (double)tp[(k + 1) * ts];
-        const double t2 = (double)tp[(k + 2) * ts], t3 = (double)tp[(k + 3) * ts];
-        const double s0 = (double)sp[k * ss], s1 = (double)sp[(k + 1) * ss];
-        const double s2 = (double)sp[(k + 2) * ss], s3 = (double)sp[(k + 3) * ss];
-        acc += t0 * s0;
-        acc += t1 * s1;
-        acc += t2 * s2;
-        acc += t3 * s3;
-    }
-    for (; k < k1; ++k) acc += (double)tp[k * ts] * (double)sp[k * ss];
-    part[(size_t)blockIdx.y * P + p] = acc;
-}
-
-// Centred, scaled Jacobian written in one pass: dJ[k][p] = (O[k][p] - cs[p] / n)
-// / sqrt(n) (the same expression as k_center_scale over a materialised O), zero
-// in the padding columns P <= p < ld.  Four columns per thread, JC_ROWS rows per
-// block; vec: ld a multiple of 4 and O 16-byte aligned (one 16-byte store per
-// FP32 row, two per FP64 row).  Each column reads its spin and activation through
-// a pointer and a row stride, a missing factor being the constant 1 (or 0 for
-// padding) with stride 0, so a full block of rows issues all its loads before
-// any arithmetic.
-__device__ const int8_t k_zero_s = 0;
-constexpr int JC_ROWS = 8;
-template <typename R, bool SPLIT>
-__global__ __launch_bounds__(256) void k_jacobian_centred(Dims d, const int8_t* __restrict__ s,
-                                                          const R* __restrict__ tact, long n,
-                                                          long rows, int P, long ld,
-                                                          const double* __restrict__ cs, int vec,
-                                                          R* __restrict__ O) {
-    const long p = 4 * ((long)blockIdx.x * 256 + threadIdx.x);
-    if (p >= ld) return;
-    const double inv = 1.0 / (double)n;  // (n: all samples; rows: this launch's)
-    const double rs = 1.0 / sqrt((double)n);
+template <typename R, bool CENTER, bool SPLIT, bool VEC>
+__global__ __launch_bounds__(256) void k_jac_rows(Dims d, const int8_t* __restrict__ s,
+                                                  const R* __restrict__ tact, long rows, int rpb,
+                                                  double inv, double rs, int P, long ld,
+                                                  const double* __restrict__ cs,
+                                                  R* __restrict__ O) {
+    const long c0 = (long)blockIdx.x * 1024;
+    const long p0 = VEC ? c0 + 4 * threadIdx.x : c0 + threadIdx.x;
+    if (p0 >= ld) return;
     const int8_t* sp[4];
     const R* tp[4];
-    long ss[4], ts[4];
+    int ss[4], ts[4];
     double mean[4];
+    JacCol cc[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        const JacCol c = jac_col(d, p + e, P);
+        const long p = VEC ? p0 + e : p0 + 256 * e;
+        const JacCol c = jac_col(d, p, P);
         const bool has_s = c.kind == 0 || c.kind == 2, has_t = c.kind == 1 || c.kind == 2;
         sp[e] = has_s ? s + c.i : (c.kind == 3 ? &k_zero_s : &k_one_s);
         ss[e] = has_s ? d.N : 0;
         tp[e] = has_t ? tact + c.j : &k_one_t<R>;
         ts[e] = has_t ? d.Mw : 0;
-        mean[e] = c.kind != 3 ? cs[p + e] * inv : 0.0;
+        mean[e] = CENTER && c.kind != 3 ? cs[p] * inv : 0.0;
+        cc[e] = c;
     }
-    const long k0 = (long)blockIdx.y * JC_ROWS;
-    auto store = [&](long k, const double* x) {
-        R v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = center_store<R, SPLIT>((x[e] - mean[e]) * rs);
-        R* row = O + k * ld + p;
-        if (vec) {
+    const long k0 = (long)blockIdx.y * rpb, k1 = min(rows, k0 + rpb);
+    auto entry = [&](R t, int sv, int e) -> R {
+        if constexpr (CENTER)
+            return center_store<R, SPLIT>(((double)t * (double)sv - mean[e]) * rs);
+        else
+            return t * (R)sv;
+    };
+    auto put = [&](long k, const R (&v)[4]) {
+        R* row = O + k * ld;
+        if constexpr (VEC) {
             if constexpr (sizeof(R) == 4) {
-                *(float4*)row = make_float4(v[0], v[1], v[2], v[3]);
+                *(float4*)(row + p0) = make_float4(v[0], v[1], v[2], v[3]);
             } else {
-                *(double2*)row = make_double2(v[0], v[1]);
-                *(double2*)(row + 2) = make_double2(v[2], v[3]);
+                *(double2*)(row + p0) = make_double2(v[0], v[1]);
+                *(double2*)(row + p0 + 2) = make_double2(v[2], v[3]);
             }
         } else {
-            for (int e = 0; e < 4 && p + e < ld; ++e) row[e] = v[e];
-        }
-    };
-    if (k0 + JC_ROWS <= rows) {
-        double x[JC_ROWS][4];
-#pragma unroll
-        for (int r = 0; r < JC_ROWS; ++r)
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                x[r][e] = (double)tp[e][(k0 + r) * ts[e]] * (double)sp[e][(k0 + r) * ss[e]];
+                if (p0 + 256 * e < ld) row[p0 + 256 * e] = v[e];
+        }
+    };
+    constexpr int U = 4;  // rows in flight
+    if (VEC && d.N % 4 == 0 && ((uintptr_t)s & 3) == 0 && cc[0].kind == 2 && cc[3].kind == 2 &&
+        cc[0].j == cc[3].j && cc[0].i % 4 == 0) {
+        const R* t = tp[0];
+        const int8_t* w = sp[0];
+        for (long k = k0; k < k1; k += U) {
+            R tv[U];
+            uint32_t wv[U];
 #pragma unroll
-        for (int r = 0; r < JC_ROWS; ++r) store(k0 + r, x[r]);
-    } else {
-        for (long k = k0; k < rows; ++k) {
-            double x[4];
+            for (int u = 0; u < U; ++u) {
+                const long kk = min(k + u, k1 - 1);
+                tv[u] = t[kk * d.Mw];
+                wv[u] = *(const uint32_t*)(w + kk * d.N);
+            }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) x[e] = (double)tp[e][k * ts[e]] * (double)sp[e][k * ss[e]];
-            store(k, x);
+            for (int u = 0; u < U; ++u) {
+                R v[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = entry(tv[u], (int8_t)(wv[u] >> (8 * e)), e);
+                if (k + u < k1) put(k + u, v);
+            }
+        }
+        return;
+    }
+    for (long k = k0; k < k1; k += U) {
+        R tv[U][4];
+        int sv[U][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const long kk = min(k + u, k1 - 1);
+                tv[u][e] = tp[e][kk * ts[e]];
+                sv[u][e] = sp[e][kk * ss[e]];
+            }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            R v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = entry(tv[u][e], sv[u][e], e);
+            if (k + u < k1) put(k + u, v);
         }
     }
 }
@@ -537,15 +511,45 @@ __global__ __launch_bounds__(256) void k_dense_matvec(const R* __restrict__ G, i
 int dense_matvec_blocks(int P) { return (P + 4 * DMV_RW - 1) / (4 * DMV_RW); }
 
 // ---------------------------------------------------------------------------
+// rows per block: long enough to pay for finding the columns (64), shorter where
+// that leaves fewer than about four blocks per compute unit
+template <typename R, bool CENTER, bool SPLIT>
+static void jac_rows(hipStream_t st, const Dims& d, const int8_t* s, const void* tact, long n,
+                     long nmean, void* O, int P, long ld, const double* cs) {
+    const long cb = (ld + 1023) / 1024;
+    int rpb = 64;
+    while (rpb > 4 && cb * ((n + rpb - 1) / rpb) < 1024) rpb /= 2;
+    const double inv = 1.0 / (double)nmean, rs = 1.0 / sqrt((double)nmean);
+    const bool vec = ld % 4 == 0 && ((uintptr_t)O & 15) == 0;
+    const long chunk = 65535L * rpb;  // rows per launch (grid y limit)
+    for (long r0 = 0; r0 < n; r0 += chunk) {
+        const long m = n - r0 < chunk ? n - r0 : chunk;
+        const dim3 g((unsigned)cb, (unsigned)((m + rpb - 1) / rpb));
+        const int8_t* sr = s + r0 * d.N;
+        const R* tr = (const R*)tact + r0 * d.Mw;
+        R* orow = (R*)O + r0 * ld;
+        if (vec)
+            k_jac_rows<R, CENTER, SPLIT, true><<<g, 256, 0, st>>>(d, sr, tr, m, rpb, inv, rs, P, ld,
+                                                                  cs, orow);
+        else
+            k_jac_rows<R, CENTER, SPLIT, false><<<g, 256, 0, st>>>(d, sr, tr, m, rpb, inv, rs, P,
+                                                                   ld, cs, orow);
+    }
+}
 void launch_jacobian(hipStream_t st, const Dims& d, int prec, const int8_t* s, const void* tact,
                      long n, void* O, int P, long ld) {
     if (n <= 0) return;
-    if (prec == 0)
-        k_jacobian<double><<<(unsigned)n, 256, 0, st>>>(d, s, (const double*)tact, n, P, ld,
-                                                        (double*)O);
-    else
-        k_jacobian<float><<<(unsigned)n, 256, 0, st>>>(d, s, (const float*)tact, n, P, ld,
-                                                       (float*)O);
+    if (prec == 0) jac_rows<double, false, false>(st, d, s, tact, n, n, O, P, ld, nullptr);
+    else jac_rows<float, false, false>(st, d, s, tact, n, n, O, P, ld, nullptr);
+}
+// `n` rows of a centred, scaled Jacobian over nmean samples with column sums cs
+void launch_jacobian_centred(hipStream_t st, const Dims& d, int prec, const int8_t* s,
+                             const void* tact, long n, long nmean, void* O, int P, long ld,
+                             const double* cs, bool split) {
+    if (n <= 0) return;
+    if (prec == 0) jac_rows<double, true, false>(st, d, s, tact, n, nmean, O, P, ld, cs);
+    else if (split) jac_rows<float, true, true>(st, d, s, tact, n, nmean, O, P, ld, cs);
+    else jac_rows<float, true, false>(st, d, s, tact, n, nmean, O, P, ld, cs);
 }
 
 void launch_center_cols(hipStream_t st, int prec, void* O, long n, long ld, int P, double* cs,
@@ -568,43 +572,6 @@ void launch_center_cols(hipStream_t st, int prec, void* O, long n, long ld, int 
         k_center_scale<float, true><<<g2, 256, 0, st>>>((float*)O, n, ld, P, cs, vec);
     else
         k_center_scale<float><<<g2, 256, 0, st>>>((float*)O, n, ld, P, cs, vec);
-}
-
-// Centred, scaled Jacobian of n samples in one write pass (column sums from the
-// spins and activations first; scratch holds the slice partials).
-void launch_jacobian_centred(hipStream_t st, const Dims& d, int prec, const int8_t* s,
-                             const void* tact, long n, void* O, int P, long ld, double* cs,
-                             double* scratch, size_t scratch_bytes, bool split) {
-    if (n <= 0) return;
-    const int nb = (P + 255) / 256;
-    size_t sp = scratch ? scratch_bytes / (8 * (size_t)P) : 1;
-    const int splits = (int)(sp < 1 ? 1 : (sp > CS_SPLIT_MAX ? CS_SPLIT_MAX : sp));
-    double* part = splits > 1 ? scratch : cs;
-    const dim3 g1(nb, splits);
-    if (prec == 0)
-        k_colsum_st<double><<<g1, 256, 0, st>>>(d, s, (const double*)tact, n, P, splits, part);
-    else
-        k_colsum_st<float><<<g1, 256, 0, st>>>(d, s, (const float*)tact, n, P, splits, part);
-    if (splits > 1) k_colsum_fin<<<nb, 256, 0, st>>>(part, P, splits, cs);
-    const int vec = (ld % 4 == 0 && ((uintptr_t)O & 15) == 0) ? 1 : 0;
-    const size_t es = prec == 0 ? 8 : 4;
-    const long chunk = 65535L * JC_ROWS;  // rows per launch (grid y limit)
-    for (long r0 = 0; r0 < n; r0 += chunk) {
-        const long m = n - r0 < chunk ? n - r0 : chunk;
-        const dim3 g2((unsigned)((ld + 1023) / 1024), (unsigned)((m + JC_ROWS - 1) / JC_ROWS));
-        const int8_t* sr = s + r0 * d.N;
-        const char* tr = (const char*)tact + es * (size_t)r0 * d.Mw;
-        char* orow = (char*)O + es * (size_t)r0 * ld;
-        if (prec == 0)
-            k_jacobian_centred<double, false><<<g2, 256, 0, st>>>(
-                d, sr, (const double*)tr, n, m, P, ld, cs, vec, (double*)orow);
-        else if (split)
-            k_jacobian_centred<float, true><<<g2, 256, 0, st>>>(
-                d, sr, (const float*)tr, n, m, P, ld, cs, vec, (float*)orow);
-        else
-            k_jacobian_centred<float, false><<<g2, 256, 0, st>>>(
-                d, sr, (const float*)tr, n, m, P, ld, cs, vec, (float*)orow);
-    }
 }
 
 int gram_tiles(int P) {

@@ -122,6 +122,14 @@ void launch_cg_update(hipStream_t st, int total, double* x, double* r, double* p
 void launch_axpy_update(hipStream_t st, int total, double* x, const double* delta, double lr,
                         CgScalars* sc);
 
+// tsum.hip: column sums of the Jacobian, sum_k t~_k (x) s~_k, in packed order
+// (FP64 sums in every precision).  A long batch may come in parts: `acc` ([Ma][Na]
+// doubles) carries the sum from a part to the next, the last one writes out.
+// part: scratch for the row slices, part_bytes of it (at least Ma Na doubles).
+void launch_colsum(hipStream_t st, const Dims& d, int prec, const int8_t* s, const void* tact,
+                   long n, void* part, size_t part_bytes, int ncu, double* acc, bool first,
+                   bool last, double* out);
+
 // qgt.hip: force and on-the-fly QGT products of one SR step, and CG
 struct QgtBatch {
     void* Sp;        // augmented spins, sample-major: int8 [Nsp][Kq] (FP64) or FP4 [Nsp][Kq/2]
@@ -221,9 +229,11 @@ void launch_cg_group_iter(hipStream_t st, const CgGroupTable* t_dev, const CgGro
                           int par, int write_flag);
 
 // dense.hip
+// n rows of dJ = (O - cs / nmean) / sqrt(nmean) (cs: column sums over the whole
+// batch of nmean samples); split as for launch_center_cols
 void launch_jacobian_centred(hipStream_t st, const Dims& d, int prec, const int8_t* s,
-                             const void* tact, long n, void* O, int P, long ld, double* cs,
-                             double* scratch, size_t scratch_bytes, bool split);
+                             const void* tact, long n, long nmean, void* O, int P, long ld,
+                             const double* cs, bool split);
 void launch_jacobian(hipStream_t st, const Dims& d, int prec, const int8_t* s, const void* tact,
                      long n, void* O, int P, long ld);
 // centre and scale the columns of O [n][ld] (first P); scratch (may be null)
