@@ -10,103 +10,272 @@
 // Operand lane layouts (16x16 tiles, 64 lanes): A[row = lane % 16][k = lane / 16]
 // (BF16: k = 8 * (lane / 16) + e), B[k][col = lane % 16]; accumulator slot i
 // of lane l holds D[acc_row(l / 16, i)][l % 16] (see common.h).
-// One workgroup = 4 waves = 64 rows x 64 hidden columns; each wave owns 16 rows.
 #include "kernels.h"
+
+#include <type_traits>
 
 namespace nqs {
 
-template <typename R>
-__device__ __forceinline__ R act(R th, int col, int M) {
-    return col < M ? (R)tanh(th) : (col == M ? (R)1 : (R)0);
+// e^{-y} for y in [0, 44] as its FP64 value `e` and as `m` = e^{-y} - 1, each with
+// its own relative accuracy: a two-term (Cody-Waite) reduction by ln 2 and the
+// Taylor polynomial of e^r - 1 (|r| <= ln 2 / 2, degree 13: the remainder is below
+// 2^-56 of the result).
+struct ExpNeg {
+    double e, m;
+};
+__device__ __forceinline__ ExpNeg exp_neg(double y) {
+    const double k = rint(-y * 1.4426950408889634074);
+    double r = fma(-k, 0.6931471805601177, -y);      // ln 2 to 40 bits (k times it is exact)
+    r = fma(-k, -1.7239444525614835e-13, r);  // the rest of ln 2
+    double p = 1.0 / 6227020800.0;
+    p = fma(p, r, 1.0 / 479001600.0);
+    p = fma(p, r, 1.0 / 39916800.0);
+    p = fma(p, r, 1.0 / 3628800.0);
+    p = fma(p, r, 1.0 / 362880.0);
+    p = fma(p, r, 1.0 / 40320.0);
+    p = fma(p, r, 1.0 / 5040.0);
+    p = fma(p, r, 1.0 / 720.0);
+    p = fma(p, r, 1.0 / 120.0);
+    p = fma(p, r, 1.0 / 24.0);
+    p = fma(p, r, 1.0 / 6.0);
+    p = fma(p, r, 0.5);
+    p = fma(p * r, r, r);  // e^r - 1
+    const double s = ldexp(1.0, (int)k);
+    return ExpNeg{fma(s, p, s), fma(s, p, s - 1.0)};
+}
+__device__ __forceinline__ double recip64(double x) {
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(fma(-x, y, 1.0), y, y);
+    return fma(fma(-x, y, 1.0), y, y);
+}
+// tanh|x| = -m / (2 + m), m = e^{-2|x|} - 1 (1 past |x| = 22)
+__device__ __forceinline__ double tanh64(double x) {
+    const double a = fabs(x);
+    const double m = exp_neg(2.0 * (a > 22.0 ? 22.0 : a)).m, d = 2.0 + m;  // d in [1, 2]
+    const double y = recip64(d);
+    double q = -m * y;
+    q = fma(fma(-d, q, -m), y, q);
+    return copysign(q, x);
+}
+// cosh x - 1 = m^2 / (2 e^{-|x|}), m = e^{-|x|} - 1, for |x| <= 22 (larger: its value at 22)
+__device__ __forceinline__ double coshm1(double a) {
+    const ExpNeg x = exp_neg(a > 22.0 ? 22.0 : a);
+    return x.m * x.m * (0.5 * recip64(x.e));
+}
+__device__ __forceinline__ double act(double th, int col, int M) {
+    const double t = tanh64(th);  // (no branch around it)
+    return col < M ? t : (col == M ? 1.0 : 0.0);
+}
+__device__ __forceinline__ float act(float th, int col, int M) {
+    return col < M ? tanhf(th) : (col == M ? 1.0f : 0.0f);
 }
 
-template <typename R>
-__device__ __forceinline__ R spin_aug(const int8_t* __restrict__ s, int N, int r, int rows, int k) {
-    if (r >= rows || k > N) return (R)0;
-    return k == N ? (R)1 : (R)s[(size_t)r * N + k];
+// FP64 and FP32 paths.  A wave keeps the W~^T fragments of its 16 hidden columns
+// in registers (G groups of 16 sites) and walks the block's rows, RT 16-row tiles
+// at a time, so W is read once per block and wave and each MFMA takes one bit-field
+// extract and one conversion of spins staged in LDS ([row][site] bytes, rows an odd
+// number of 16-byte pieces apart: a fragment read hits distinct banks).  The
+// accumulation over sites is one chain in site order.  EPI 0 (k_theta): a block
+// covers 64 columns, tanh in the epilogue; EPI 1 (ln psi): a block covers all
+// columns, its waves taking tiles w, w + nw, ..., and sums ln cosh over them: the
+// factors cosh x are multiplied over 16 columns before one logarithm.  G is
+// exact (no test inside the products: with one, the compiler moved every
+// accumulator between register files around each MFMA); MULTI: lattices too wide
+// for that walk the sites in chunks of G groups (the last one zero-padded), W
+// reloaded for each step of rows.
+// 16,384 x (100 sites, 200 hidden units) FP64, 0.76 GFLOP (12 us at the FP64 matrix
+// rate): theta 62 -> 34 us against staging W in LDS for every 64 x 64 tile with the
+// library tanh, ln psi 289 -> 41 us against a vector dot product per hidden unit.
+// What is left is vector issue: conversions, tanh and the drain of 512 blocks.
+constexpr int TH_ST = 8;  // staging words per thread and step
+
+// (1 + f) multiplied over the 16 lanes of a DPP row, less 1
+__device__ __forceinline__ double row16_prod1(double f) {
+    auto mul = [](double a, double b) { return fma(a, b, a + b); };
+    f = mul(f, dpp<0xB1>(f));
+    f = mul(f, dpp<0x4E>(f));
+    f = mul(f, dpp<0x124>(f));
+    return mul(f, dpp<0x128>(f));
 }
 
-// Block = 4 waves = 64 rows x 64 hidden columns.  The sites run in tiles of
-// TK_THETA: each tile's spins (augmented, [64][TK]) and the block's 64 columns
-// of W~^T ([TK][64]) are staged in LDS with batched loads, then every wave runs
-// its 16 rows over the tile (any lattice size fits the fixed LDS footprint).
-constexpr int TK_THETA = 128;
-
-template <typename R>
-__global__ __launch_bounds__(256) void k_theta(Dims d, const int8_t* __restrict__ s, int rows,
-                                               const R* __restrict__ Wa, R* __restrict__ dst1,
-                                               R* __restrict__ dst2, long dst2_stride) {
-    constexpr int TK = TK_THETA;
-    __shared__ __align__(16) R Bs[TK * 64];     // [TK][64]
-    __shared__ __align__(16) int8_t Ss[64 * TK];  // [64][TK]
-    const int Na = d.Na;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int lr = lane & 15, lk = lane >> 4;
-    const int rowb = blockIdx.x * 64, row0 = rowb + wave * 16;
-    const int col0 = blockIdx.y * 64;
+template <typename R, int G, int RT, int EPI, bool MULTI>
+__global__ __launch_bounds__(EPI ? 512 : 256) void k_theta(
+    Dims d, const int8_t* __restrict__ s, long rows, int words, int RB, const R* __restrict__ Wa,
+    R* __restrict__ dst1, R* __restrict__ dst2, long dst2_stride, const double* __restrict__ av) {
+    extern __shared__ __align__(16) int8_t th_lds[];
     typedef typename std::conditional<sizeof(R) == 8, v4d, v4f>::type acc_t;
-    acc_t acc[4];
+    constexpr int LD = 16 * (G | 1);  // LDS row stride
+    const int tid = threadIdx.x, lane = tid & 63, nth = blockDim.x, nw = nth >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lr = lane & 15, lk = lane >> 4;
+    const long r0 = (long)blockIdx.x * RB;
+    const int nr = (int)min((long)RB, rows - r0);  // rows of this block
+    const int ng = d.Na / 16;
+    const int nch = MULTI ? (ng + G - 1) / G : 1;  // site chunks
+    double* red = (double*)(th_lds + (size_t)RB * LD);  // EPI 1: [nw][RB]
+    // spins of chunk c, rows of the block, augmented (1 at site N, then 0); eight
+    // words per thread loaded together (items past the end repeat the last one)
+    auto stage = [&](int c) {
+        constexpr int W = 4 * G;
+        const int i0 = 16 * G * c, items = RB * W;
+        auto fill = [&](auto word) {
+#pragma unroll 1
+            for (int e0 = tid; e0 < items; e0 += TH_ST * nth) {
+                uint32_t v[TH_ST];
+                int at[TH_ST];
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct) acc[ct] = acc_t{0, 0, 0, 0};
-    for (int kt = 0; kt < Na; kt += TK) {
-        const int kn = min(TK, Na - kt);  // a multiple of 16 (Na is)
-        __syncthreads();                  // the previous tile is no longer read
-        for (int base = 0; base < kn * 64; base += 256 * 8) {
-            R v[8];
+                for (int u = 0; u < TH_ST; ++u) {
+                    const int e = min(e0 + u * nth, items - 1);
+                    const int row = e / W, i = 4 * (e - row * W);
+                    at[u] = row * LD + i;
+                    v[u] = word(s + (r0 + min(row, nr - 1)) * d.N, i0 + i);
+                }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int e = base + u * 256 + tid;
-                const int k = e >> 6, cl = e & 63;
-                v[u] = (e < kn * 64 && col0 + cl < d.Mw) ? Wa[(size_t)(kt + k) * d.Mw + col0 + cl]
-                                                         : (R)0;
+                for (int u = 0; u < TH_ST; ++u) *(uint32_t*)(th_lds + at[u]) = v[u];
             }
+        };
+        if (words)  // (N is a multiple of 4: a word is all spins or all constants)
+            fill([&](const int8_t* p, int i) {
+                const uint32_t v = *(const uint32_t*)(p + min(i, d.N - 4));
+                return i < d.N ? v : (i == d.N ? 1u : 0u);
+            });
+        else
+            fill([&](const int8_t* p, int i) {
+                uint32_t v = 0;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int e = base + u * 256 + tid;
-                if (e < kn * 64) Bs[e] = v[u];
-            }
-        }
-        for (int base = 0; base < 64 * kn; base += 256 * 8) {
-            int8_t v[8];
+                for (int q = 0; q < 4; ++q) {
+                    const uint32_t x = (uint8_t)p[min(i + q, d.N - 1)];
+                    v |= (i + q < d.N ? x : (i + q == d.N ? 1u : 0u)) << (8 * q);
+                }
+                return v;
+            });
+    };
+    const int tiles = EPI ? (d.M + 15) / 16 : d.Mw / 16;
+    R wf[4 * G];
+    auto load_w = [&](int tile, int c) {  // (tiles past the last one repeat it)
+        const R* w = Wa + 16 * min(tile, tiles - 1) + lr;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int e = base + u * 256 + tid;
-                const int rl = e / kn, k = e - rl * kn;
-                v[u] = (e < 64 * kn) ? (int8_t)spin_aug<R>(s, d.N, rowb + rl, rows, kt + k)
-                                     : (int8_t)0;
-            }
+        for (int g = 0; g < G; ++g)
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int e = base + u * 256 + tid;
-                if (e < 64 * kn) Ss[e] = v[u];
+            for (int e = 0; e < 4; ++e) {
+                const int k = 16 * (c * G + g) + 4 * e + lk;
+                if constexpr (MULTI) {
+                    const R v = w[(size_t)min(k, d.Na - 1) * d.Mw];
+                    wf[4 * g + e] = k < d.Na ? v : (R)0;
+                } else {
+                    wf[4 * g + e] = w[(size_t)k * d.Mw];
+                }
             }
-        }
+    };
+    const int tile0 = (EPI ? 0 : (int)blockIdx.y * nw) + wave;
+    if constexpr (!MULTI) {
+        load_w(tile0, 0);
+        stage(0);
         __syncthreads();
-        const int8_t* Sw = Ss + (wave * 16 + lr) * kn;
-        for (int k0 = 0; k0 < kn; k0 += 4) {
-            const R a = (R)Sw[k0 + lk];
-            const R* Bk = Bs + (k0 + lk) * 64 + lr;
+    }
+    const int trounds = EPI ? (tiles + nw - 1) / nw : 1;
+    const int sh = 8 * lk;
+    for (int q = 0; q < trounds; ++q) {
+        const int tile = tile0 + q * nw;
+        const bool work = tile < tiles && 16 * tile < d.M;  // (past M: constants only)
+        if (!MULTI && q > 0) load_w(tile, 0);
+        const int col = 16 * tile + lr;
+#pragma unroll 1
+        for (int rt = 0; rt < nr; rt += 16 * RT) {
+            acc_t acc[RT];
 #pragma unroll
-            for (int ct = 0; ct < 4; ++ct) {
-                const R b = Bk[ct * 16];
-                if constexpr (sizeof(R) == 8)
-                    acc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc[ct], 0, 0, 0);
-                else
-                    acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc[ct], 0, 0, 0);
+            for (int u = 0; u < RT; ++u) acc[u] = acc_t{0, 0, 0, 0};
+            const int8_t* row_lds = th_lds + (rt + lr) * LD;
+            auto products = [&]() {
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    uint4 sp[RT];
+#pragma unroll
+                    for (int u = 0; u < RT; ++u)
+                        sp[u] = *(const uint4*)(row_lds + 16 * u * LD + 16 * g);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int u = 0; u < RT; ++u) {
+                            const uint32_t w = e == 0 ? sp[u].x : e == 1 ? sp[u].y : e == 2 ? sp[u].z : sp[u].w;
+                            const R a = (R)(int)__builtin_amdgcn_sbfe((int)w, sh, 8);
+                            if constexpr (sizeof(R) == 8)
+                                acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, wf[4 * g + e], acc[u], 0, 0, 0);
+                            else
+                                acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, wf[4 * g + e], acc[u], 0, 0, 0);
+                        }
+                }
+            };
+            if constexpr (MULTI) {
+                for (int c = 0; c < nch; ++c) {
+                    __syncthreads();  // (the same trip counts in every wave)
+                    stage(c);
+                    load_w(tile, c);
+                    __syncthreads();
+                    products();
+                }
+            } else if (work) {
+                products();
+            }
+            if constexpr (EPI == 0) {
+                if (tile >= tiles) continue;
+                const long b1 = (r0 + rt) * d.Mw, b2 = (r0 + rt) * dst2_stride;
+#pragma unroll
+                for (int u = 0; u < RT; ++u)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int row = 16 * u + acc_row<R>(lk, i);
+                        const R t = work ? act(acc[u][i], col, d.M) : (R)(col == d.M ? 1 : 0);
+                        if (rt + 16 * RT <= nr || rt + row < nr) {
+                            (dst1 + b1)[(unsigned)(row * d.Mw + col)] = t;
+                            if (dst2) (dst2 + b2)[row * dst2_stride + col] = t;
+                        }
+                    }
+            } else if (work) {
+                // each row's sum over the tile's 16 columns (lanes of a DPP row):
+                // ln prod cosh with the product kept as its difference from 1, so
+                // that small activations keep their relative accuracy; past |x| = 22,
+                // ln cosh x = ln cosh 22 + |x| - 22
+#pragma unroll
+                for (int u = 0; u < RT; ++u) {
+                    double f[4], big[4];
+                    bool any = false;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const double x = col < d.M ? fabs((double)acc[u][i]) : 0.0;
+                        f[i] = row16_prod1(coshm1(x));
+                        big[i] = x > 22.0 ? x - 22.0 : 0.0;
+                        any = any || !(x <= 22.0);
+                    }
+                    if (__any(any)) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) big[i] = row16_sum(big[i]);
+                    }
+                    // lane lr takes row slot lr % 4: one logarithm for the four rows
+                    const int i = lr & 3;
+                    const double p = i == 0 ? f[0] : i == 1 ? f[1] : i == 2 ? f[2] : f[3];
+                    const double a = i == 0 ? big[0] : i == 1 ? big[1] : i == 2 ? big[2] : big[3];
+                    const int row = rt + 16 * u + acc_row<R>(lk, i);
+                    if (lr < 4 && row < RB) {
+                        double* o = red + wave * RB + row;
+                        *o = (q > 0 ? *o : 0.0) + (a + log1p(p));
+                    }
+                    __builtin_amdgcn_sched_barrier(0);  // one tile's values live at a time
+                }
             }
         }
     }
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-        const int col = col0 + ct * 16 + lr;
-        if (col >= d.Mw) continue;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int row = row0 + acc_row<R>(lk, i);
-            if (row >= rows) continue;
-            const R t = act<R>(acc[ct][i], col, d.M);
-            dst1[(size_t)row * d.Mw + col] = t;
-            if (dst2) dst2[(size_t)row * dst2_stride + col] = t;
+    if constexpr (EPI == 1) {  // the waves' sums in order, and the visible part
+        __syncthreads();
+        // (16 lanes per row; every lane stays in the loop for the row sums)
+        for (int rb = 4 * wave; rb < nr; rb += 4 * nw) {
+            const int row = min(rb + lk, nr - 1);
+            double v = 0.0;
+            if (av)
+                for (int i = lr; i < d.N; i += 16) v += av[i] * (double)s[(r0 + row) * d.N + i];
+            for (int w = lr; w < nw; w += 16) v += red[w * RB + row];
+            v = row16_sum(v);
+            if (lr == 0 && rb + lk < nr) dst1[r0 + row] = (R)v;
         }
     }
 }
@@ -220,60 +389,79 @@ __global__ __launch_bounds__(256) void k_theta_bf16(Dims d, const int8_t* __rest
         for (int i = 0; i < 4; ++i) {
             const int row = row0 + acc_row<float>(lk, i);
             if (row >= rows) continue;
-            const float t = act<float>(acc[ct][i], col, d.M);
+            const float t = act(acc[ct][i], col, d.M);
             dst1[(size_t)row * d.Mw + col] = t;
             if (dst2) dst2[(size_t)row * dst2_stride + col] = t;
         }
     }
 }
 
-// ln psi(s) = sum_i a_i s_i + sum_j ln cosh theta_j; one wave per configuration.
-template <typename R>
-__global__ __launch_bounds__(256) void k_log_psi(Dims d, const double* __restrict__ Pm,
-                                                 const R* __restrict__ Wa,
-                                                 const int8_t* __restrict__ s, long n,
-                                                 R* __restrict__ out) {
-    const long r = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (r >= n) return;
-    const int8_t* sr = s + r * d.N;
-    R acc = 0;
-    for (int j = lane; j < d.M; j += 64) {
-        R th = Wa[(size_t)d.N * d.Mw + j];
-        for (int i = 0; i < d.N; ++i) th += (R)sr[i] * Wa[(size_t)i * d.Mw + j];
-        const R ath = th < 0 ? -th : th;
-        // ln cosh x = |x| + ln(1 + e^{-2|x|}) - ln 2, finite for any x
-        acc += ath + (R)log1p(exp(-2 * ath)) - (R)0.69314718055994530942;
+// Rows per block: the fewest of 16, 32, 64, 128 that leave `target` blocks or more
+// (16 rows where even those are fewer).
+static int theta_rows(long rows, long nby, long target) {
+    int RB = 128;
+    while (RB > 16 && ((rows + RB - 1) / RB) * nby < target) RB /= 2;
+    return RB;
+}
+
+template <typename R, int G, int EPI, bool MULTI>
+static void theta_g(hipStream_t st, const Dims& d, const int8_t* s, long rows, const R* Wa, R* dst1,
+                    R* dst2, long dst2_stride, const double* av) {
+    const int tiles = EPI ? (d.M + 15) / 16 : d.Mw / 16;
+    // waves of an EPI 1 block: all tiles in rounds of at most eight, as equal as they come
+    const int rounds = (tiles + 7) / 8;
+    const int nw = EPI ? (tiles + rounds - 1) / rounds : 4;
+    const int nby = EPI ? 1 : (tiles + nw - 1) / nw;
+    const int RB = MULTI ? 32 : theta_rows(rows, nby, 512);
+    const size_t lds = (size_t)RB * 16 * (G | 1) + (EPI ? 8 * (size_t)nw * RB : 0);
+    const int words = d.N % 4 == 0 && ((uintptr_t)s & 3) == 0;
+    const dim3 grid((unsigned)((rows + RB - 1) / RB), (unsigned)nby);
+    if (RB > 16)
+        k_theta<R, G, 2, EPI, MULTI><<<grid, 64 * nw, lds, st>>>(d, s, rows, words, RB, Wa, dst1,
+                                                                 dst2, dst2_stride, av);
+    else
+        k_theta<R, G, 1, EPI, MULTI><<<grid, 64 * nw, lds, st>>>(d, s, rows, words, RB, Wa, dst1,
+                                                                 dst2, dst2_stride, av);
+}
+template <typename R, int EPI>
+static void theta_r(hipStream_t st, const Dims& d, const int8_t* s, long rows, const void* Wa,
+                    void* dst1, void* dst2, long dst2_stride, const double* av) {
+#define THETA_G(G, MULTI)                                                                     \
+    theta_g<R, G, EPI, MULTI>(st, d, s, rows, (const R*)Wa, (R*)dst1, (R*)dst2, dst2_stride, av)
+    switch (d.Na / 16) {
+        case 1: return THETA_G(1, false);
+        case 2: return THETA_G(2, false);
+        case 3: return THETA_G(3, false);
+        case 4: return THETA_G(4, false);
+        case 5: return THETA_G(5, false);
+        case 6: return THETA_G(6, false);
+        case 7: return THETA_G(7, false);
+        case 8: return THETA_G(8, false);
+        default: return THETA_G(8, true);
     }
-    if (d.vb)
-        for (int i = lane; i < d.N; i += 64) acc += (R)(Pm[(size_t)d.M * d.Na + i] * sr[i]);
-    acc = wave_sum(acc);
-    if (lane == 0) out[r] = acc;
+#undef THETA_G
 }
 
 void launch_theta(hipStream_t st, const Dims& d, int prec, const Tables& t, const int8_t* s,
                   int rows, void* dst1, void* dst2, long dst2_stride) {
     if (rows <= 0) return;
-    dim3 grid((rows + 63) / 64, (d.Mw + 63) / 64);
-    if (prec == 0)
-        k_theta<double><<<grid, 256, 0, st>>>(d, s, rows, (const double*)t.Wa, (double*)dst1,
-                                              (double*)dst2, dst2_stride);
-    else if (prec == 1)
-        k_theta<float><<<grid, 256, 0, st>>>(d, s, rows, (const float*)t.Wa, (float*)dst1,
-                                             (float*)dst2, dst2_stride);
-    else
+    if (prec == 0) {
+        theta_r<double, 0>(st, d, s, rows, t.Wa, dst1, dst2, dst2_stride, nullptr);
+    } else if (prec == 1) {
+        theta_r<float, 0>(st, d, s, rows, t.Wa, dst1, dst2, dst2_stride, nullptr);
+    } else {
+        dim3 grid((rows + 63) / 64, (d.Mw + 63) / 64);
         k_theta_bf16<<<grid, 256, 0, st>>>(d, s, rows, t.Whi, t.Wlo, (float*)dst1, (float*)dst2,
                                            dst2_stride);
+    }
 }
 
 void launch_log_psi(hipStream_t st, const Dims& d, int prec, const double* Pm, const Tables& t,
                     const int8_t* s, long n, void* out) {
     if (n <= 0) return;
-    const int nb = (int)((n + 3) / 4);
-    if (prec == 0)
-        k_log_psi<double><<<nb, 256, 0, st>>>(d, Pm, (const double*)t.Wa, s, n, (double*)out);
-    else
-        k_log_psi<float><<<nb, 256, 0, st>>>(d, Pm, (const float*)t.Wa, s, n, (float*)out);
+    const double* av = d.vb ? Pm + (size_t)d.M * d.Na : nullptr;
+    if (prec == 0) theta_r<double, 1>(st, d, s, n, t.Wa, out, nullptr, 0, av);
+    else theta_r<float, 1>(st, d, s, n, t.Wa, out, nullptr, 0, av);
 }
 
 }  // namespace nqs
