@@ -101,7 +101,7 @@ struct nqs_ctx {
     bool bound = false;
     Buffers b{};
     long Ns = 0, Bx = 0;
-    int ksplit = 1, chunk = 256, ndpart = 1, Pld = 0, ntiles = 0;
+    int ksplit = 1, ndpart = 1, Pld = 0, ntiles = 0;
     size_t lds_limit = 65536;
     int ncu = 256;  // compute units of the device
     long cg_iter = 0;
@@ -359,8 +359,7 @@ void derive(nqs_ctx* c) {
     if (c->has_sampler) {
         c->Ns = (long)c->C * c->S;
         c->Bx = c->Ns > 1024 ? c->Ns : 1024;
-        c->chunk = outer_chunk(d, c->prec, c->lds_limit);
-        c->ksplit = outer_ksplit(c->Bx, c->chunk);
+        c->ksplit = (int)((c->Bx + 255) / 256);
         c->Pld = round_up(c->Pd, 128);
         c->ntiles = gram_tiles(c->Pd);
         if (c->cplx) {  // Re G and Im G are P x P
@@ -1239,14 +1238,6 @@ int s_issue_solve(nqs_ctx* c, double diag_shift, double tol, int maxiter) {
     return run_cg(c, NQS_QGT_JACOBIAN_DENSE, diag_shift, mi);
 }
 
-__global__ void k_f32_to_f64(const float* a, double* b, long n) {
-    const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < n) b[e] = (double)a[e];
-}
-__global__ void k_f64_to_f32(const double* a, float* b, long n) {
-    const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < n) b[e] = (float)a[e];
-}
 __global__ void k_check_finite(const double* a, long n, int* flag) {
     const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (e < n && !isfinite(a[e])) *flag = 1;
@@ -1827,31 +1818,14 @@ int nqs_log_psi_vjp(nqs_ctx* c, const int8_t* s, int64_t n, const void* g, void*
     if (n < 0 || (n > 0 && (!s || !g)) || !grad_out) return fail(c, NQS_EINVAL, "bad batch");
     if (c->cplx || c->symm)
         return fail(c, NQS_EINVAL, "complex and symmetric models are not supported here");
-    const int PV = c->d.Ma * c->d.Na;
-    launch_zero(c->stream, c->b.gacc, 8 * (size_t)PV);
+    const size_t es = esize(c->prec);
+    if (n == 0) launch_zero(c->stream, grad_out, es * c->P);
     for (int64_t k0 = 0; k0 < n; k0 += c->Bx) {
         const long m = (long)((n - k0) < c->Bx ? (n - k0) : c->Bx);
         const int8_t* sk = s + (size_t)k0 * c->N;
         launch_theta(c->stream, c->d, c->prec, c->b.tab, sk, (int)m, c->b.tx, nullptr, 0);
-        if (c->prec == 0)
-            HIPCHK(c, hipMemcpyAsync(c->b.vvec, (const double*)g + k0, 8 * (size_t)m,
-                                     hipMemcpyDeviceToDevice, c->stream));
-        else
-            k_f32_to_f64<<<(unsigned)((m + 255) / 256), 256, 0, c->stream>>>((const float*)g + k0,
-                                                                             c->b.vvec, m);
-        launch_outer(c->stream, c->d, c->prec, sk, c->b.tx, m, c->b.vvec, 1, c->b.part, c->chunk,
-                     c->b.sc);
-        launch_reduce_outer(c->stream, c->d, c->prec, c->b.part, outer_ksplit(m, c->chunk),
-                            nullptr, 0.0, c->b.Ap, c->b.dpart, c->b.sc, 1);
-        launch_axpy_update(c->stream, PV, c->b.gacc, c->b.Ap, -1.0, c->b.sc);
-    }
-    if (c->prec == 0) {
-        launch_pack(c->stream, c->d, c->b.gacc, (double*)grad_out, (int)c->P);
-    } else {
-        launch_pack(c->stream, c->d, c->b.gacc, c->b.tmpv, (int)c->P);
-        k_f64_to_f32<<<(unsigned)((c->P + 255) / 256), 256, 0, c->stream>>>(c->b.tmpv,
-                                                                           (float*)grad_out,
-                                                                           (long)c->P);
+        launch_vjp(c->stream, c->d, c->prec, sk, c->b.tx, m, (const char*)g + es * k0, c->b.part,
+                   part_bytes(c), c->ncu, c->b.gacc, k0 == 0, k0 + m == n, grad_out);
     }
     return last_launch(c);
 }

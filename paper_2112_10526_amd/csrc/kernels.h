@@ -102,15 +102,6 @@ void launch_eloc(hipStream_t st, const Dims& d, int prec, const Tables& t, const
 void launch_stats(hipStream_t st, const double* E, long n, double* out3);
 void launch_center(hipStream_t st, const double* E, const double* stats, double scale, long n,
                    double* v);
-int outer_chunk(const Dims& d, int prec, size_t lds_limit);
-int outer_ksplit(long n, int chunk);
-// part: [outer_ksplit(n, chunk)][Ma][Na]
-void launch_outer(hipStream_t st, const Dims& d, int prec, const int8_t* s, const void* tact,
-                  long n, const double* v, int v_mode, void* part, int chunk,
-                  const CgScalars* sc);
-void launch_reduce_outer(hipStream_t st, const Dims& d, int prec, const void* part, int ksplit,
-                         const double* p, double shift, double* out, double* dpart,
-                         CgScalars* sc, int mode);
 void launch_cg_init(hipStream_t st, int total, const double* f, double* x, double* r, double* p,
                     double* dpart, CgScalars* sc, double tol, int maxiter, double shift);
 // dense-form CG iteration after the product: dpart holds the product's npap
@@ -129,6 +120,13 @@ void launch_axpy_update(hipStream_t st, int total, double* x, const double* delt
 void launch_colsum(hipStream_t st, const Dims& d, int prec, const int8_t* s, const void* tact,
                    long n, void* part, size_t part_bytes, int ncu, double* acc, bool first,
                    bool last, double* out);
+
+// sum_k g_k O(s_k) in packed order (g and out: double for FP64, float otherwise;
+// FP32 sums of at most 256 rows, added in FP64), in parts as above; the slot
+// buffer holds a slot per 256 rows
+void launch_vjp(hipStream_t st, const Dims& d, int prec, const int8_t* s, const void* tact, long n,
+                const void* g, void* part, size_t part_bytes, int ncu, double* acc, bool first,
+                bool last, void* out);
 
 // qgt.hip: force and on-the-fly QGT products of one SR step, and CG
 struct QgtBatch {

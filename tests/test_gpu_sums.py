@@ -50,3 +50,45 @@ def test_jacobian_rows_and_centring(N, M, n, vb, hb, precision, shift):
     np.testing.assert_allclose(st.jacobian(view).cpu().numpy(), ref, rtol=0, atol=tol)
     out = st.jacobian(view, center=True).cpu().numpy()
     np.testing.assert_allclose(out, (ref - ref.mean(0)) / np.sqrt(n), rtol=0, atol=tol)
+
+
+@pytest.mark.parametrize("N,M,n,vb,hb", CASES + [(300, 20, 70, True, True)])
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "bf16"])
+def test_log_psi_and_its_vjp(N, M, n, vb, hb, precision):
+    """ln psi (all columns of a row in one block, several site chunks at 300 sites) and
+    sum_k g_k O(s_k).  FP64: 1e-12 of the sum of the terms' sizes.  FP32: theta is a
+    sum of N + 1 terms below max |theta| (<= 2 here), each rounded by 2^-24, weighted
+    by |tanh theta| <= 1 in ln psi; the product's sums run over at most 256 rows (the
+    BF16 form splits W with 2^-16 of it)."""
+    import torch
+    print(f"[case] {N} {M} {n} {vb} {hb} {precision}", flush=True)
+    st, rbm = _state(N, M, precision, vb, hb)
+    s = synth.random_configs(n, N, 8)
+    sd = torch.from_numpy(s).cuda()
+    g = np.random.default_rng(4).normal(size=n)
+    gd = torch.from_numpy(g).cuda().to(st.rdtype)
+    eps = 2.0 ** -24
+    th_err = 0.0 if precision == "fp64" else 2 * (N + 1) * eps
+    if precision == "bf16":
+        th_err += (N + 1) * 0.3 * 2.0 ** -16
+    y = st.log_psi(sd).double().cpu().numpy()
+    np.testing.assert_allclose(y, core.log_psi(rbm, s), rtol=0, atol=1e-12 * (N + M) + M * th_err)
+    v = st.log_psi_vjp(sd, gd).double().cpu().numpy()
+    ref = core.jacobian(rbm, s).T @ g
+    tol = 1e-13 * n if precision == "fp64" else (256 * eps + th_err + 4 * eps) * np.abs(g).sum()
+    np.testing.assert_allclose(v, ref, rtol=0, atol=tol)
+    assert not st.log_psi_vjp(sd[:0], gd[:0]).any()
+
+
+def test_log_psi_past_the_cap():
+    """Activations beyond |theta| = 22, where ln cosh is |theta| - ln 2 to FP64."""
+    import torch
+    N, M = 12, 5
+    st, _ = _state(N, M, "fp64")
+    p = synth.rbm_params(N, M, 6, 0.05)
+    p[N:N + M] = [30.0, -25.0, 22.0, 5.0, 300.0]
+    st.set_params(p)
+    s = synth.random_configs(40, N, 9)
+    ref = core.log_psi(core.Rbm(N, M, p), s)
+    y = st.log_psi(torch.from_numpy(s).cuda()).cpu().numpy()
+    np.testing.assert_allclose(y, ref, rtol=1e-14, atol=1e-12)
