@@ -1,255 +1,357 @@
 // Dense direct solve of (A + shift I) x = f for a symmetric positive-definite A
 // (paper: solving the SR / TDVP linear system with a dense QGT; the jVMC
-// comparison's dense-solver rows): blocked Cholesky A + shift I = L L^T in
-// place (the lower triangle of A becomes L; the upper triangle is never read),
-// then L y = f and L^T x = y.  Panels of CH_NB = 32 columns:
-//   k_chol_panel  factors the shifted diagonal block in LDS and inverts the
-//                 factor (one wave, the block's entries spread over the lanes),
-//                 multiplies the panel's rows below by the inverse's transpose
-//                 (64-row tiles through LDS), keeps the inverse for the backward solve
-//                 and carries the forward solve;
-//   k_chol_update subtracts the panel's outer product from the trailing lower
-//                 triangle on the FP64 matrix cores (64 x 64 tiles);
-// L y = f rides on the panels (each panel forms its y_k and takes its part out
-// of the right-hand side of the rows below); L^T x = y runs in one workgroup,
-// 32 rows per step, each step a product with the stored inverse of its
-// diagonal block.  A pivot
-// that is not positive (A + shift I not positive definite) sets *bad.
+// comparison's dense-solver rows): blocked Cholesky A + shift I = L L^T from the
+// lower triangle of A, then L y = f and L^T x = y.  Panels of CH_NB = 32 columns,
+// one launch each (k_chol_step): every block factors the panel's 32 x 32 diagonal
+// block for itself, solves its own panel rows against it, and subtracts their outer
+// product from its 64 x 64 tile of the trailing triangle.  As the blocks still read
+// the panel while others finish, the solved rows go to the mirrored place in the
+// upper triangle; k_chol_mirror puts them into the lower one.  L y = f rides on the panels: the right-hand side is one more
+// row of each.  L^T x = y walks the diagonal blocks from the last: x_k from the
+// stored inverse, then its part out of the columns before it, whose entries of L
+// are loaded ahead (they do not depend on x): one workgroup for systems of up to
+// 2,048, one launch per block above.
+// The steps are a chain of dependent latencies (32 pivots at about 0.15 us each,
+// one panel after the other), so launches and passes were what could go.  n = 880:
+// 28 steps of 13.9 us (5 us of them the elimination, 3 us the loads behind the
+// previous launch) and 73 us backward, 0.48 ms; a panel and an update launch per
+// step (28 + 11 us) with a left-looking backward solve took 1.31 ms.  n = 8,448 (the
+// 64-site complex model): 43 -> 33 ms.
+// A pivot that is not positive (A + shift I not positive definite) sets *bad.
 #include "kernels.h"
 
 namespace nqs {
 
 constexpr int CH_NB = 32;
-constexpr int CH_ROWS = 64;  // rows below the diagonal block per panel workgroup
+constexpr int CH_XD = 33;   // LDS row of a 32-column matrix
 
-__global__ __launch_bounds__(256) void k_chol_panel(double* __restrict__ A, int n, long ld, int k0,
-                                                    double shift, int32_t* __restrict__ bad,
-                                                    double* __restrict__ Yout,
-                                                    double* __restrict__ rhs,
-                                                    double* __restrict__ yout) {
-    __shared__ double D[CH_NB][CH_NB + 1];  // the block, then its factor L_kk
-    __shared__ double Y[CH_NB][CH_NB + 1];  // L_kk^-1
-    __shared__ double yk[CH_NB];            // this block's part of y = L^-1 f
-    __shared__ double fk[CH_NB];            // the panel rows' right-hand side
-    __shared__ double Lc[CH_NB][CH_NB + 1]; // the factor's columns, Lc[j][i] = L_ij
-    const int w = n - k0 < CH_NB ? n - k0 : CH_NB;
-    const int tid = threadIdx.x;
-    // the diagonal block's lower part, shifted; identity past w; Y = I
-    for (int e = tid; e < CH_NB * CH_NB; e += 256) {
-        const int i = e / CH_NB, c = e - i * CH_NB;
-        double v = 0.0;
-        if (c <= i) {
-            if (i < w) v = A[(long)(k0 + i) * ld + k0 + c] + (i == c ? shift : 0.0);
-            else if (i == c) v = 1.0;
-        }
-        D[i][c] = v;
-        Y[i][c] = i == c ? 1.0 : 0.0;
-    }
-    if (tid < CH_NB) fk[tid] = tid < w ? rhs[k0 + tid] : 0.0;
-    __syncthreads();
-    if (tid < 64) {
-        // One wave, the block in registers: lane l holds column c = l % 32 at the
-        // rows i = 2 m + l / 32 (m < 16).  Factor step j (unrolled): the pivot
-        // comes from its owner by readlane, the two lanes holding column j scale
-        // it and publish it (Lc, LDS), then every lane reads its rows' and its
-        // column's entries of column j and updates its trailing entries.
-        const int l = tid, c = l & 31, par = l >> 5;
-        double dr[16], y[16];
+// Elimination of the 32 x 32 block next to the identity, one wave, all in registers:
+// lane c < 32 holds column c of the (symmetric) block, lane 32 + c column c of the
+// identity, register i row i.  Step j takes A_ij / d_j times row j out of every row
+// i > j; column j's entries reach all lanes as scalars (readlane), so a step's chain
+// is a pivot, its reciprocal (hardware estimate, two Newton steps) and one product.
+// Scaling row j by 1 / sqrt(d_j) then gives L^T on the left and L^-1 on the right.
+// Returns false if a pivot is not positive.
+__device__ __forceinline__ bool chol_block32(double (&a)[CH_NB]) {
+    const int c = threadIdx.x & 31;
+    bool ok = true;
+    double dd = 1.0;  // lane c: pivot c
 #pragma unroll
-        for (int m = 0; m < 16; ++m) {
-            dr[m] = D[2 * m + par][c];
-            y[m] = (2 * m + par == c) ? 1.0 : 0.0;
-        }
-        bool ok = true;
+    for (int j = 0; j < CH_NB; ++j) {
+        double d = readlane(a[j], j);
+        const bool pos = d > 0.0 && isfinite(d);
+        ok = ok && pos;
+        d = pos ? d : 1.0;
+        double r = __builtin_amdgcn_rcp(d);
+        r = fma(fma(-d, r, 1.0), r, r);
+        r = fma(fma(-d, r, 1.0), r, r);
+        const double t = -a[j] * r;
+        if (c == j) dd = d;
+        // (scalars in groups: one at a time, each product waits for its own readlane)
 #pragma unroll
-        for (int j = 0; j < CH_NB; ++j) {
-            const double djj = readlane(dr[j >> 1], j + 32 * (j & 1));
-            ok = ok && djj > 0.0 && isfinite(djj);
-            const double d = sqrt(djj > 0.0 ? djj : 1.0), rd = 1.0 / d;
-            if (c == j) {
+        for (int i0 = j + 1; i0 < CH_NB; i0 += 8) {
+            double v[8];
 #pragma unroll
-                for (int m = 0; m < 16; ++m) {
-                    const int i = 2 * m + par;
-                    dr[m] = i == j ? d : (i > j ? dr[m] * rd : dr[m]);
-                    Lc[j][i] = dr[m];
-                }
-            }
-            __builtin_amdgcn_wave_barrier();
-            double lr_[16];
+            for (int u = 0; u < 8; ++u)
+                if (i0 + u < CH_NB) v[u] = readlane(a[i0 + u], j);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int m = 0; m < 16; ++m) lr_[m] = Lc[j][2 * m + par];
-            const double lcj = Lc[j][c];
-#pragma unroll
-            for (int m = 0; m < 16; ++m) {
-                const int i = 2 * m + par;
-                if (c > j && i >= c) dr[m] -= lr_[m] * lcj;
-            }
-            __builtin_amdgcn_wave_barrier();
-        }
-        if (!ok && blockIdx.x == 0 && l == 0) *bad = 1;
-        // Y = L_kk^-1 by row operations on the identity (same layout): step j
-        // scales row j by 1 / L_jj, then row i -= L_ij row j for i > j; Y[j][c]
-        // comes from the lane holding row j's parity (this lane or l ^ 32)
-#pragma unroll
-        for (int j = 0; j < CH_NB; ++j) {
-            const double rjj = 1.0 / Lc[j][j];
-            if (par == (j & 1)) y[j >> 1] *= rjj;
-            const double mine = y[j >> 1];
-            const double other = __shfl_xor(mine, 32);
-            const double yjc = par == (j & 1) ? mine : other;
-            double lr_[16];
-#pragma unroll
-            for (int m = 0; m < 16; ++m) lr_[m] = Lc[j][2 * m + par];
-#pragma unroll
-            for (int m = 0; m < 16; ++m) {
-                const int i = 2 * m + par;
-                if (i > j) y[m] -= lr_[m] * yjc;
-            }
-        }
-#pragma unroll
-        for (int m = 0; m < 16; ++m) {
-            D[2 * m + par][c] = dr[m];
-            Y[2 * m + par][c] = y[m];
+            for (int u = 0; u < 8; ++u)
+                if (i0 + u < CH_NB) a[i0 + u] = fma(v[u], t, a[i0 + u]);
         }
     }
-    // y_k = L_kk^-1 f_k (f_k as left by the earlier panels; every block forms it,
-    // no block writes the rhs rows of this panel)
-    if (tid < CH_NB) {
-        double y = 0.0;
+    // 1 / sqrt of every lane's pivot: hardware estimate, two coupled Newton steps
+    double h = __builtin_amdgcn_rsq(dd), g = dd * h;
+    h *= 0.5;
 #pragma unroll
-        for (int m = 0; m < CH_NB; ++m) y += Y[tid][m] * fk[m];  // (Y lower; fk zero past w)
-        yk[tid] = tid < w ? y : 0.0;
+    for (int q = 0; q < 2; ++q) {
+        const double e = fma(-h, g, 0.5);
+        g = fma(g, e, g);
+        h = fma(h, e, h);
     }
-    __syncthreads();
-    if (blockIdx.x == 0) {  // the factor into A; the inverse and y_k to the side
-        for (int e = tid; e < CH_NB * CH_NB; e += 256) {
-            const int i = e / CH_NB, c = e - i * CH_NB;
-            if (i < w && c <= i) A[(long)(k0 + i) * ld + k0 + c] = D[i][c];
-            Yout[(size_t)(k0 / CH_NB) * CH_NB * CH_NB + e] = Y[i][c];
-        }
-        if (tid < w) yout[k0 + tid] = yk[tid];
-        return;
-    }
-    // rows below the block, 64 per block: x = a L_kk^-T, x_c = sum_m a_m
-    // (L_kk^-1)[c][m], and each row's right-hand side loses x . y_k.  The tile
-    // moves through LDS so that its loads and stores are coalesced; thread t
-    // computes row t / 4, columns 8 (t % 4) .. + 7.
-    __shared__ double T[CH_ROWS][CH_NB + 1];
-    const long r0 = (long)k0 + w + (long)(blockIdx.x - 1) * CH_ROWS;
-    const int tr = tid >> 2, tc = (tid & 3) * 8;
-    const long r = r0 + tr;
+    const double rs = 2.0 * h;
 #pragma unroll
-    for (int q = 0; q < 8; ++q)
-        T[tr][tc + q] = (r < n && tc + q < w) ? A[r * ld + k0 + tc + q] : 0.0;
-    __syncthreads();
-    double xo[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) xo[q] = 0.0;
-#pragma unroll
-    for (int m = 0; m < CH_NB; ++m) {
-        const double t = T[tr][m];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) xo[q] += t * Y[tc + q][m];
-    }
-    double fr = 0.0;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) fr += xo[q] * yk[tc + q];
-    fr += __shfl_xor(fr, 1);
-    fr += __shfl_xor(fr, 2);
-    if (r < n) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-            if (tc + q < w) A[r * ld + k0 + tc + q] = xo[q];
-        if ((tid & 3) == 0) rhs[r] -= fr;
-    }
+    for (int j = 0; j < CH_NB; ++j) a[j] *= readlane(rs, j);
+    return ok;
 }
 
-// trailing update T -= X X^T on the lower triangle, T = A[k1:, k1:], X = A[k1:, k0:k1];
-// block = a 64 x 64 tile (ti >= tj), wave = a 32 x 32 quarter of 2 x 2 MFMA tiles
-__global__ __launch_bounds__(256) void k_chol_update(double* __restrict__ A, int n, long ld, int k0,
-                                                     int k1) {
-    const long b = blockIdx.x;
-    long ti = (long)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
+// Panel k0 (w columns): block b is tile (ti, tj), ti >= tj, of the trailing
+// triangle's T x T tiles.  Wave 0 factors; then the waves solve the panel rows of
+// tile rows ti and tj (X = A L^-T on the matrix cores, 16 rows at a time, the
+// operands loaded before the factorisation) and each updates a quarter of the tile.
+template <int T>
+__global__ __launch_bounds__(256) void k_chol_step(double* __restrict__ A, int n, long ld, int k0,
+                                                   double shift, int32_t* __restrict__ bad,
+                                                   double* __restrict__ Yinv,
+                                                   double* __restrict__ rhs,
+                                                   double* __restrict__ yout) {
+    constexpr int NG = T / 32;  // row groups per wave, 16 x 16 tiles per quarter side
+    __shared__ double Y[CH_NB][CH_XD];  // L_kk^-1
+    __shared__ double yk[CH_NB];
+    __shared__ double Xs[2 * T][CH_XD];  // solved rows of tile row ti, then tj
+    const int w = n - k0 < CH_NB ? n - k0 : CH_NB, k1 = k0 + w;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lr = lane & 15, lk = lane >> 4;
+    const int b = blockIdx.x;
+    int ti = (int)((sqrtf(8.0f * (float)b + 1.0f) - 1.0f) * 0.5f);
     while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
     while (ti * (ti + 1) / 2 > b) --ti;
-    const long tj = b - ti * (ti + 1) / 2;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int lr = lane & 15, lk = lane >> 4;
-    const long ri = k1 + ti * 64 + (wave >> 1) * 32, cj = k1 + tj * 64 + (wave & 1) * 32;
-    const int w = k1 - k0;
-    v4d acc[2][2];
+    const int tj = b - ti * (ti + 1) / 2;
+    const int ri = k1 + ti * T, cj = k1 + tj * T;
+    const bool rest = k1 < n;  // (the last panel has no trailing rows: one block)
+    double x[CH_NB];
+    if (wave == 0) {
+        const int c = lane & 31;
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int c = 0; c < 2; ++c) acc[a][c] = v4d{0, 0, 0, 0};
-    for (int kk = 0; kk < w; kk += 4) {
-        const int k = kk + lk;
-        double fa[2], fb[2];
-#pragma unroll
-        for (int a = 0; a < 2; ++a) {
-            const long rr = ri + a * 16 + lr, cc = cj + a * 16 + lr;
-            fa[a] = (rr < n && k < w) ? A[rr * ld + k0 + k] : 0.0;
-            fb[a] = (cc < n && k < w) ? A[cc * ld + k0 + k] : 0.0;
+        for (int i = 0; i < CH_NB; ++i) {
+            double v = i == c ? 1.0 : 0.0;  // (identity past w, and on the right)
+            const int hi = i > c ? i : c, lo = i > c ? c : i;
+            if (lane < 32 && hi < w)
+                v = A[(long)(k0 + hi) * ld + k0 + lo] + (i == c ? shift : 0.0);
+            x[i] = v;
         }
+    }
+    // panel rows in MFMA order (row lr of 16, columns 4 q + lk), the tile in
+    // accumulator order, the right-hand side: all loaded before the barrier
+    double pa[NG][CH_NB / 4];
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
+    for (int g = 0; g < NG; ++g) {
+        const int gr = 16 * (wave + 4 * g);  // row of Xs
+        const int r = (gr < T ? ri + gr : cj + gr - T) + lr;
+#pragma unroll
+        for (int q = 0; q < CH_NB / 4; ++q)
+            pa[g][q] = r < n ? A[(long)r * ld + k0 + 4 * q + lk] : 0.0;
+    }
+    const int r0 = ri + (wave >> 1) * (T / 2), c0 = cj + (wave & 1) * (T / 2);
+    double ct[NG][NG][4];
+#pragma unroll
+    for (int a = 0; a < NG; ++a)
+#pragma unroll
+        for (int c = 0; c < NG; ++c)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int row = r0 + a * 16 + acc_row<double>(lk, q), col = c0 + c * 16 + lr;
+                ct[a][c][q] = row < n && col <= row ? A[(long)row * ld + col] : 0.0;
+            }
+    const double fk = tid < w ? rhs[k0 + tid] : 0.0;
+    const double fr = tid < T && ri + tid < n ? rhs[ri + tid] : 0.0;
+    __builtin_amdgcn_sched_barrier(0);
+    if (wave == 0) {
+        const bool ok = chol_block32(x);
+        if (!ok && b == 0 && lane == 0) *bad = 1;
+        if (lane >= 32) {
+#pragma unroll
+            for (int i = 0; i < CH_NB; ++i) Y[i][lane - 32] = x[i];
+        }
+        if (lane < CH_NB) yk[lane] = fk;  // f_k for now
+    }
+    __syncthreads();
+    if (rest) {
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const int gr = 16 * (wave + 4 * g);
+            if (gr >= T && ti == tj) continue;
+            v4d xa[2];
+#pragma unroll
+            for (int c = 0; c < 2; ++c) xa[c] = v4d{0, 0, 0, 0};
+#pragma unroll
+            for (int q = 0; q < CH_NB / 4; ++q)
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+                    xa[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(pa[g][q], Y[16 * c + lr][4 * q + lk],
+                                                                 xa[c], 0, 0, 0);
 #pragma unroll
             for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    Xs[gr + acc_row<double>(lk, q)][16 * c + lr] = xa[c][q];
+        }
+    }
+    double y = 0.0;  // y_k = L_kk^-1 f_k, by the last wave's lanes
+    const int yl = tid - 192;
+    if (yl >= 0 && yl < CH_NB) {
+        double a[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int m = 0; m < CH_NB; ++m) a[m & 3] = fma(Y[yl][m], yk[m], a[m & 3]);  // (Y lower)
+        y = (a[0] + a[1]) + (a[2] + a[3]);
+    }
+    __syncthreads();
+    if (b == 0) {
+        for (int e = tid; e < CH_NB * CH_NB; e += 256)
+            Yinv[(size_t)(k0 / CH_NB) * CH_NB * CH_NB + e] = Y[e / CH_NB][e % CH_NB];
+        if (yl >= 0 && yl < w) yout[k0 + yl] = y;
+    }
+    if (!rest) return;
+    const double(*Xi)[CH_XD] = Xs;
+    const double(*Xj)[CH_XD] = Xs + (ti == tj ? 0 : T);
+    v4d acc[NG][NG];
+#pragma unroll
+    for (int a = 0; a < NG; ++a)
+#pragma unroll
+        for (int c = 0; c < NG; ++c) acc[a][c] = v4d{0, 0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < CH_NB; k += 4) {
+        double fa[NG], fb[NG];
+#pragma unroll
+        for (int a = 0; a < NG; ++a) {
+            fa[a] = Xi[(wave >> 1) * (T / 2) + a * 16 + lr][k + lk];
+            fb[a] = Xj[(wave & 1) * (T / 2) + a * 16 + lr][k + lk];
+        }
+#pragma unroll
+        for (int a = 0; a < NG; ++a)
+#pragma unroll
+            for (int c = 0; c < NG; ++c)
                 acc[a][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[a], fb[c], acc[a][c], 0, 0, 0);
     }
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < NG; ++a)
 #pragma unroll
-        for (int c = 0; c < 2; ++c)
+        for (int c = 0; c < NG; ++c)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const long row = ri + a * 16 + acc_row<double>(lk, q), col = cj + c * 16 + lr;
-                if (row < n && col <= row) A[row * ld + col] -= acc[a][c][q];
+                const int row = r0 + a * 16 + acc_row<double>(lk, q), col = c0 + c * 16 + lr;
+                if (row < n && col <= row) A[(long)row * ld + col] = ct[a][c][q] - acc[a][c][q];
             }
+    if (ti != tj) return;  // (uniform over the block)
+    // this tile row's solved panel rows to the upper triangle, and their part out of
+    // the right-hand side
+    if (yl >= 0 && yl < CH_NB) yk[yl] = y;
+    __syncthreads();
+    for (int e = tid; e < T * CH_NB; e += 256) {
+        const int r = e % T, c = e / T;
+        if (ri + r < n) A[(long)(k0 + c) * ld + ri + r] = Xs[r][c];
+    }
+    if (tid < T && ri + tid < n) {
+        double a[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int c = 0; c < CH_NB; ++c) a[c & 3] = fma(Xs[tid][c], yk[c], a[c & 3]);
+        rhs[ri + tid] = fr - ((a[0] + a[1]) + (a[2] + a[3]));
+    }
 }
 
-// L^T x = y, one workgroup of 1024 threads, a 32-row block per step from the
-// last: x_k = Yinv_k^T (y_k - sum_{j>k} L_jk^T x_j), Yinv_k (the inverse of the
-// diagonal block, [blocks][32][32]) staged in LDS
+// 32 x 32 tiles (bi, bj), bi > bj, of L from the mirrored place in the upper
+// triangle (the diagonal blocks are used through their inverses only).
+__global__ __launch_bounds__(256) void k_chol_mirror(double* __restrict__ A, int n, long ld) {
+    __shared__ double T[CH_NB][CH_NB + 1];
+    const int tid = threadIdx.x;
+    const long b = blockIdx.x;
+    long bi = (long)((sqrt(8.0 * (double)b + 1.0) + 1.0) * 0.5);
+    while (bi * (bi + 1) / 2 <= b) ++bi;
+    while (bi * (bi - 1) / 2 > b) --bi;
+    const long bj = b - bi * (bi - 1) / 2;
+    const int tx = tid & 31, ty = tid >> 5;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const long r = bi * CH_NB + tx;
+        if (r < n) T[ty + 8 * m][tx] = A[(bj * CH_NB + ty + 8 * m) * ld + r];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const long r = bi * CH_NB + ty + 8 * m;
+        if (r < n) A[r * ld + bj * CH_NB + tx] = T[tx][ty + 8 * m];
+    }
+}
+
+// x_k = Yinv_k^T s_k by the first 32 lanes (s in LDS), into xk
+__device__ __forceinline__ void chol_back_block(const double (*Yk)[CH_NB + 1], const double* s,
+                                                double* xk) {
+    const int c = threadIdx.x;
+    if (c >= CH_NB) return;
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int m = 0; m < CH_NB; ++m) a[m & 3] = fma(Yk[m][c], s[m], a[m & 3]);  // (Yinv lower)
+    xk[c] = (a[0] + a[1]) + (a[2] + a[3]);
+}
+
+// A barrier for data passed through LDS only: loads from memory stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// L^T x = y in one workgroup, Q columns per thread (n <= 1024 Q), the columns'
+// running right-hand side in registers: per diagonal block its 32 values meet in
+// LDS, x_k, then every earlier column loses its part.  The block's rows of L are
+// loaded ahead of that chain and stay in flight across its barriers.
+template <int Q>
 __global__ __launch_bounds__(1024) void k_chol_back(const double* __restrict__ L, int n, long ld,
                                                     const double* __restrict__ Yinv,
                                                     const double* __restrict__ y,
                                                     double* __restrict__ x) {
-    __shared__ double red[16][CH_NB];
-    __shared__ double sv[CH_NB];
-    __shared__ double Yk[CH_NB * CH_NB];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    __shared__ double Yk[2][CH_NB][CH_NB + 1];
+    __shared__ double sk[CH_NB], xk[CH_NB];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nblk = (n + CH_NB - 1) / CH_NB;
+    double s[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) s[q] = tid + 1024 * q < n ? y[tid + 1024 * q] : 0.0;
+    double yn = Yinv[(size_t)(nblk - 1) * CH_NB * CH_NB + tid];
     for (int kb = nblk - 1; kb >= 0; --kb) {
         const int k0 = kb * CH_NB;
-        const int w = n - k0 < CH_NB ? n - k0 : CH_NB;
-        Yk[threadIdx.x] = Yinv[(size_t)kb * CH_NB * CH_NB + threadIdx.x];
-        // partial sums over j >= k0 + w of L[j][k0 + i] x[j], rows j split over the waves
-        double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-        if (lane < w) {
-            long j = k0 + w + wave;
-            for (; j + 48 < n; j += 64) {  // four independent rows in flight
-                a0 += L[j * ld + k0 + lane] * x[j];
-                a1 += L[(j + 16) * ld + k0 + lane] * x[j + 16];
-                a2 += L[(j + 32) * ld + k0 + lane] * x[j + 32];
-                a3 += L[(j + 48) * ld + k0 + lane] * x[j + 48];
+        Yk[kb & 1][tid >> 5][tid & 31] = yn;  // (waits for it before the loads below)
+        double l[Q][CH_NB];
+        const double* Lk = L + (long)k0 * ld;
+        const int last = n - 1 - k0;  // (rows past n repeat the last one; their x is 0)
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const unsigned i = (unsigned)min(tid + 1024 * q, n - 1);
+            if (64 * wave + 1024 * q < k0) {  // (the wave has earlier columns)
+#pragma unroll
+                for (int m = 0; m < CH_NB; ++m) l[q][m] = (Lk + (long)min(m, last) * ld)[i];
             }
-            for (; j < n; j += 16) a0 += L[j * ld + k0 + lane] * x[j];
         }
-        if (lane < CH_NB) red[wave][lane] = (a0 + a1) + (a2 + a3);
-        __syncthreads();
-        if (wave == 0 && lane < CH_NB) {
-            double t = 0.0;
-            for (int v = 0; v < 16; ++v) t += red[v][lane];
-            sv[lane] = lane < w ? y[k0 + lane] - t : 0.0;
+        yn = Yinv[(size_t)max(kb - 1, 0) * CH_NB * CH_NB + tid];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int i = tid + 1024 * q - k0;
+            if (i >= 0 && i < CH_NB) sk[i] = s[q];  // (zero past n)
         }
-        __syncthreads();
-        if (wave == 0 && lane < w) {  // x_i = sum_m Yinv[m][i] s_m, m >= i
-            double xi = 0.0;
-            for (int m = lane; m < w; ++m) xi += Yk[m * CH_NB + lane] * sv[m];
-            x[k0 + lane] = xi;
-        }
-        __syncthreads();
+        lds_barrier();
+        chol_back_block(Yk[kb & 1], sk, xk);
+        if (tid < CH_NB && k0 + tid < n) x[k0 + tid] = xk[tid];
+        lds_barrier();
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (tid + 1024 * q < k0) {
+                double a[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int m = 0; m < CH_NB; ++m) a[m & 3] = fma(l[q][m], xk[m], a[m & 3]);
+                s[q] -= (a[0] + a[1]) + (a[2] + a[3]);
+            }
+    }
+}
+
+// The same, one diagonal block per launch: every block forms x_k for itself, the
+// first one stores it, and each takes its part out of its own 256 columns of y.
+__global__ __launch_bounds__(256) void k_chol_back_step(const double* __restrict__ L, int n,
+                                                        long ld, int k0,
+                                                        const double* __restrict__ Yinv,
+                                                        double* __restrict__ y,
+                                                        double* __restrict__ x) {
+    __shared__ double Yk[CH_NB][CH_NB + 1];
+    __shared__ double sk[CH_NB], xk[CH_NB];
+    const int tid = threadIdx.x;
+    const int i = blockIdx.x * 256 + tid;
+    double l[CH_NB];
+    if (i < k0) {
+#pragma unroll
+        for (int m = 0; m < CH_NB; ++m) l[m] = L[(long)min(k0 + m, n - 1) * ld + i];
+    }
+    for (int e = tid; e < CH_NB * CH_NB; e += 256)
+        Yk[e / CH_NB][e % CH_NB] = Yinv[(size_t)(k0 / CH_NB) * CH_NB * CH_NB + e];
+    if (tid < CH_NB) sk[tid] = k0 + tid < n ? y[k0 + tid] : 0.0;
+    __syncthreads();
+    chol_back_block(Yk, sk, xk);
+    if (blockIdx.x == 0 && tid < CH_NB && k0 + tid < n) x[k0 + tid] = xk[tid];
+    __syncthreads();
+    if (i < k0) {
+        double a[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int m = 0; m < CH_NB; ++m) a[m & 3] = fma(l[m], xk[m], a[m & 3]);
+        y[i] -= (a[0] + a[1]) + (a[2] + a[3]);
     }
 }
 
@@ -277,17 +379,29 @@ void launch_chol_solve(hipStream_t st, double* A, int n, long ld, double shift, 
     launch_zero(st, bad, sizeof(int32_t));
     // x holds the right-hand side as the panels eliminate it (L y = f), y gets y
     k_copy_vec<<<(n + 255) / 256, 256, 0, st>>>(f, x, n);
+    // (tiles of 32: shorter steps, but every block factors the panel's block again:
+    // up to 2,048 only)
+    const int T = n <= 2048 ? 32 : 64;
     for (int k0 = 0; k0 < n; k0 += CH_NB) {
-        const int w = n - k0 < CH_NB ? n - k0 : CH_NB;
-        const int below = n - k0 - w;
-        k_chol_panel<<<1 + (below + CH_ROWS - 1) / CH_ROWS, 256, 0, st>>>(A, n, ld, k0, shift,
-                                                                          bad, Yinv, x, y);
-        if (below > 0) {
-            const long mt = (below + 63) / 64;
-            k_chol_update<<<(unsigned)(mt * (mt + 1) / 2), 256, 0, st>>>(A, n, ld, k0, k0 + w);
-        }
+        const int below = n - k0 - CH_NB;
+        const int mt = below > 0 ? (below + T - 1) / T : 1, nb = mt * (mt + 1) / 2;
+        if (T == 32)
+            k_chol_step<32><<<nb, 256, 0, st>>>(A, n, ld, k0, shift, bad, Yinv, x, y);
+        else
+            k_chol_step<64><<<nb, 256, 0, st>>>(A, n, ld, k0, shift, bad, Yinv, x, y);
     }
-    k_chol_back<<<1, 1024, 0, st>>>(A, n, ld, Yinv, y, x);
+    const int nblk = (n + CH_NB - 1) / CH_NB;
+    if (nblk > 1)
+        k_chol_mirror<<<(unsigned)((long)nblk * (nblk - 1) / 2), 256, 0, st>>>(A, n, ld);
+    if (n <= 1024) {
+        k_chol_back<1><<<1, 1024, 0, st>>>(A, n, ld, Yinv, y, x);
+    } else if (n <= 2048) {
+        k_chol_back<2><<<1, 1024, 0, st>>>(A, n, ld, Yinv, y, x);
+    } else {
+        for (int k0 = (nblk - 1) * CH_NB; k0 >= 0; k0 -= CH_NB)
+            k_chol_back_step<<<k0 > 0 ? (k0 + 255) / 256 : 1, 256, 0, st>>>(A, n, ld, k0, Yinv, y,
+                                                                            x);
+    }
     k_chol_status<<<1, 64, 0, st>>>(bad, sc);
 }
 
