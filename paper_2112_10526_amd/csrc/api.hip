@@ -1219,8 +1219,8 @@ int s_issue_solve(nqs_ctx* c, double diag_shift, double tol, int maxiter) {
         PROF(NQS_PROF_JACOBIAN);
         launch_symm_jacobian(c->stream, c->prec, c->N, c->G, c->alpha, c->vb, c->hb, c->d.Mw,
                              c->b.perms, c->b.samples, c->b.tsm, c->Ns, c->Pld, (double*)c->b.O);
-        launch_center_cols(c->stream, 0, c->b.O, c->Ns, c->Pld, c->Psym, c->b.colsum,
-                           (double*)c->b.G, 8 * (size_t)c->Pd * c->Pld, false);
+        launch_center_cols(c->stream, (double*)c->b.O, c->Ns, c->Pld, c->Psym, c->b.colsum,
+                           (double*)c->b.part, part_bytes(c));
     }
     {
         PROF(NQS_PROF_GRAM);
@@ -1856,8 +1856,8 @@ int nqs_jacobian(nqs_ctx* c, const int8_t* s, int64_t n, void* O_out, int center
         }
         if (center) {
             if (n > 65535) return fail(c, NQS_EINVAL, "centring supports at most 65535 rows");
-            launch_center_cols(c->stream, 0, O_out, n, c->Psym, c->Psym, c->b.tmpv, nullptr, 0,
-                               false);
+            launch_center_cols(c->stream, (double*)O_out, n, c->Psym, c->Psym, c->b.tmpv,
+                               (double*)c->b.part, part_bytes(c));
         }
         return last_launch(c);
     }

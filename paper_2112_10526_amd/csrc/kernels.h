@@ -228,18 +228,17 @@ void launch_cg_group_iter(hipStream_t st, const CgGroupTable* t_dev, const CgGro
 
 // dense.hip
 // n rows of dJ = (O - cs / nmean) / sqrt(nmean) (cs: column sums over the whole
-// batch of nmean samples); split as for launch_center_cols
+// batch of nmean samples); split (FP32 entries only): each
+// entry is stored as the BF16 pair (hi << 16) | lo that the BF16 Gram reads
 void launch_jacobian_centred(hipStream_t st, const Dims& d, int prec, const int8_t* s,
                              const void* tact, long n, long nmean, void* O, int P, long ld,
                              const double* cs, bool split);
 void launch_jacobian(hipStream_t st, const Dims& d, int prec, const int8_t* s, const void* tact,
                      long n, void* O, int P, long ld);
-// centre and scale the columns of O [n][ld] (first P); scratch (may be null)
-// holds column-sum partials, up to 64 row slices of P doubles; split (FP32
-// entries only): store each entry as the BF16 pair (hi << 16) | lo that the
-// BF16 Gram reads
-void launch_center_cols(hipStream_t st, int prec, void* O, long n, long ld, int P, double* cs,
-                        double* scratch, size_t scratch_bytes, bool split);
+// centre and scale the columns of the FP64 O [n][ld] (first P); scratch holds
+// column-sum partials, at least P doubles
+void launch_center_cols(hipStream_t st, double* O, long n, long ld, int P, double* cs,
+                        double* scratch, size_t scratch_bytes);
 int gram_tiles(int P);
 void fill_gram_tiles(int P, int* host_tiles);
 void launch_gram(hipStream_t st, int prec, const void* A, long n, long ld, int P, void* G,

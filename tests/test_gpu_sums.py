@@ -92,3 +92,36 @@ def test_log_psi_past_the_cap():
     ref = core.log_psi(core.Rbm(N, M, p), s)
     y = st.log_psi(torch.from_numpy(s).cuda()).cpu().numpy()
     np.testing.assert_allclose(y, ref, rtol=1e-14, atol=1e-12)
+
+
+@pytest.mark.parametrize("lattice,L,alpha,n", [("chain", 3, 1, 5), ("chain", 10, 3, 33),
+                                               ("chain", 130, 1, 66), ("square", 9, 3, 67),
+                                               ("chain", 300, 6, 9)])
+@pytest.mark.parametrize("precision", ["fp64", "bf16"])
+def test_symmetric_jacobian_rows_and_centring(lattice, L, alpha, n, precision):
+    """Rows not a multiple of the four a block takes, odd feature counts, several
+    128-site passes, and 1,800 hidden units (more than 64 KiB of LDS).  Entries are
+    sums of G activations (<= 1 each): FP64 to 1e-12 G; BF16 form 6e-6 G (its theta:
+    the split of W to 2^-16 and FP32 sums over at most 301 sites of 0.05 weights)."""
+    import torch
+    from paper_2112_10526_amd.nqs import VMCState
+    print(f"[case] {lattice} {L} {alpha} {n} {precision}", flush=True)
+    perms = synth.chain_translations(L) if lattice == "chain" else synth.square_translations(L)
+    bonds = synth.chain_bonds(L) if lattice == "chain" else synth.square_bonds(L)
+    N, G = perms.shape[1], perms.shape[0]
+    p = synth.symm_params(N, alpha, 3, 0.05)
+    st = VMCState(model="tfim", n_sites=N, bonds=bonds, J=1.0, h=1.0, n_hidden=0,
+                  precision=precision, n_chains=8, samples_per_chain=1, sweep_size=N, seed=3,
+                  params=p, symmetries=perms, alpha=alpha)
+    s = synth.random_configs(n, N, 4)
+    # the definition, feature by feature: b_i + sum_k W_i[k] s[perm_g[k]]
+    b, W = p[1:1 + alpha], p[1 + alpha:].reshape(alpha, N)
+    sg = s[:, perms].astype(np.float64)                       # [n][G][N]
+    t = np.tanh(np.einsum("rgk,ik->rig", sg, W) + b[None, :, None])
+    ref = np.concatenate([s.sum(1, keepdims=True), t.sum(2),
+                          np.einsum("rig,rgk->rik", t, sg).reshape(n, -1)], 1)
+    tol = (1e-12 if precision == "fp64" else 6e-6) * G
+    np.testing.assert_allclose(st.jacobian(torch.from_numpy(s).cuda()).cpu().numpy(), ref, rtol=0,
+                               atol=tol)
+    c = st.jacobian(torch.from_numpy(s).cuda(), center=True).cpu().numpy()
+    np.testing.assert_allclose(c, (ref - ref.mean(0)) / np.sqrt(n), rtol=0, atol=tol)
