@@ -10,7 +10,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libnqs.so")
-SOURCES = ["tables.hip", "theta.hip", "sampler.hip", "eloc.hip", "sr.hip", "tsum.hip", "qgt.hip", "dense.hip",
+SOURCES = ["tables.hip", "theta.hip", "sampler.hip", "eloc.hip", "sr.hip", "tsum.hip", "qgt.hip", "cgsmall.hip", "dense.hip",
            "holo.hip", "symm.hip", "chol.hip", "probe.hip", "api.hip"]
 ARCH = os.environ.get("NQS_ARCH", "gfx950")
 # Packed FP32 VALU forms are switched off: the compiler must not emit them.

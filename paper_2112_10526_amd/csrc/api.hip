@@ -633,10 +633,14 @@ void issue_dense_setup(nqs_ctx* c, double tol, int maxiter, double shift) {
                    maxiter, shift);
 }
 
+// the context's on-the-fly CG runs as one launch
+bool cg_small(const nqs_ctx* c) { return cg_small_fits(c->d, c->prec, c->Ns); }
+
 void issue_cg_init(nqs_ctx* c, double tol, int maxiter, double shift) {
     c->cg_iter = 0;
     c->cg_tol = tol;
     c->cg_maxiter = maxiter;
+    if (cg_small(c)) return;  // (one launch does it all, from the force)
     launch_qgt_init(c->stream, c->d, c->prec, c->b.grad, c->b.x, c->b.r, c->b.p, c->b.p2,
                     c->b.Pop, c->b.rrp, c->b.wbuf, c->Ns, tol, maxiter, shift, c->b.sc);
 }
@@ -776,6 +780,7 @@ struct CgRun {
     int kind = 0, every = 1, limit = 0;
     double shift = 0.0;
     bool use_graphs = false, stop = false;
+    bool small = false;  // one launch for the whole solve
     int launched = 0, issued = 0, checked = 0;
 
     void init(nqs_ctx* ctx, int k, double sh, int maxiter) {
@@ -787,12 +792,24 @@ struct CgRun {
         every = (c->prof_mask & CG_CLASSES) ? 1 : cg_check_interval();
         // the on-the-fly form tests convergence at the start of an iteration
         limit = kind == NQS_QGT_ONTHEFLY ? maxiter + 1 : maxiter;
+        small = kind == NQS_QGT_ONTHEFLY && cg_small(c);
         use_graphs = c->graphs && every % 2 == 0 && !(c->prof_mask & CG_CLASSES);
     }
     bool finished() const { return stop || (checked >= issued && launched >= limit); }
     int issue_batch() {
-        const int k = (limit - launched) < every ? (limit - launched) : every;
         const int slot = issued & 1;
+        if (small) {
+            {
+                PROF(NQS_PROF_QGT_W);
+                launch_cg_small(c->stream, c->d, c->b.q, c->b.tsm, c->Ns, c->b.grad, c->b.x,
+                                c->cg_tol, c->cg_maxiter, shift, c->b.sc, &c->h_flag[0]);
+            }
+            launched = limit;
+            HIPCHK(c, hipEventRecord(c->flag_ev[slot], c->stream));
+            ++issued;
+            return NQS_OK;
+        }
+        const int k = (limit - launched) < every ? (limit - launched) : every;
         // (the on-the-fly form alternates buffers: its graph starts on an even iteration)
         if (use_graphs && k == every && (kind != NQS_QGT_ONTHEFLY || c->cg_iter % 2 == 0)) {
             hipGraphExec_t& g = kind == NQS_QGT_ONTHEFLY ? c->cg_graph : c->cg_graph_dense;
@@ -1238,9 +1255,17 @@ int s_issue_solve(nqs_ctx* c, double diag_shift, double tol, int maxiter) {
     return run_cg(c, NQS_QGT_JACOBIAN_DENSE, diag_shift, mi);
 }
 
-__global__ void k_check_finite(const double* a, long n, int* flag) {
-    const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < n && !isfinite(a[e])) *flag = 1;
+// b = a, and the host word flagged if any value is not finite
+__global__ void k_copy_finite(const double* __restrict__ a, double* __restrict__ b, long n,
+                              volatile int32_t* flag) {
+    bool bad = false;
+    for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < n;
+         e += (long)gridDim.x * blockDim.x) {
+        const double v = a[e];
+        b[e] = v;
+        bad = bad || !isfinite(v);
+    }
+    if (bad) *flag = 1;
 }
 
 }  // namespace
@@ -1300,7 +1325,7 @@ int nqs_create(nqs_ctx** out, int device, void* hip_stream) {
     if (hipSetDevice(device) != hipSuccess ||
         hipHostMalloc((void**)&c->h_sc, sizeof(CgScalars), hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void**)&c->h_stats, 8 * sizeof(double), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void**)&c->h_flag, 2 * sizeof(int32_t), hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc((void**)&c->h_flag, 3 * sizeof(int32_t), hipHostMallocDefault) != hipSuccess ||
         hipEventCreateWithFlags(&c->flag_ev[0], hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&c->flag_ev[1], hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&c->step_ev, hipEventDisableTiming) != hipSuccess ||

@@ -226,6 +226,15 @@ void cg_group_plan(CgGroupTable& t, CgGroupPlan& plan);
 void launch_cg_group_iter(hipStream_t st, const CgGroupTable* t_dev, const CgGroupPlan& plan,
                           int par, int write_flag);
 
+// cgsmall.hip: the whole CG solve of a small FP64 system in one launch (one
+// workgroup), from the force f to the direction x, scalars and stop flag as the
+// iteration kernels leave them.  cg_small_fits: the sizes it is built for and
+// faster at; activations [n][Mw], spins as laid out by launch_qgt_prepare.
+bool cg_small_fits(const Dims& d, int prec, long n);
+void launch_cg_small(hipStream_t st, const Dims& d, const QgtBatch& q, const void* tact, long n,
+                     const double* f, double* x, double tol, int maxiter, double shift,
+                     CgScalars* sc, int32_t* host_flag);
+
 // dense.hip
 // n rows of dJ = (O - cs / nmean) / sqrt(nmean) (cs: column sums over the whole
 // batch of nmean samples); split (FP32 entries only): each
