@@ -111,7 +111,7 @@ struct nqs_ctx {
     bool params_set = false, chains_dirty = true, have_samples = false, have_grad = false;
     double acceptance = 0.0;
     CgScalars* h_sc = nullptr;  // pinned
-    int32_t* h_flag = nullptr;  // pinned [2]: CG stop flag after a batch of iterations
+    int32_t* h_flag = nullptr;  // pinned [3]: CG stop flag after a batch; [2] bad parameter
     hipEvent_t flag_ev[2] = {nullptr, nullptr};
     double* h_stats = nullptr;  // pinned [4]
     uint32_t* h_acc = nullptr;  // pinned [C]
@@ -1570,44 +1570,47 @@ int nqs_set_params(nqs_ctx* c, const double* p, int on_device) {
     int st = set_device(c);
     if (st) return st;
     const size_t np = param_doubles(c);
-    std::vector<double> h(np);
+    // staging: the values are checked before any parameter changes (device values as
+    // they are copied into a scratch vector, one pass and one wait; host values here)
+    double* in = c->cplx ? (double*)c->b.hmean : c->b.tmpv;
+    std::vector<double> h;
     if (on_device) {
-        HIPCHK(c, hipMemcpyAsync(h.data(), p, 8 * np, hipMemcpyDeviceToHost, c->stream));
+        c->h_flag[2] = 0;
+        const unsigned nb = (unsigned)std::min<size_t>((np + 255) / 256, 1024);
+        k_copy_finite<<<nb, 256, 0, c->stream>>>(p, in, (long)np, &c->h_flag[2]);
         HIPCHK(c, hipStreamSynchronize(c->stream));
+        if (c->h_flag[2]) return fail(c, NQS_ENUMERIC, "non-finite parameter");
     } else {
-        std::memcpy(h.data(), p, 8 * np);
+        h.assign(p, p + np);
+        for (size_t k = 0; k < np; ++k)
+            if (!std::isfinite(h[k])) return fail(c, NQS_ENUMERIC, "non-finite parameter");
+        HIPCHK(c, hipMemcpyAsync(in, h.data(), 8 * np, hipMemcpyHostToDevice, c->stream));
     }
-    for (size_t k = 0; k < np; ++k)
-        if (!std::isfinite(h[k])) return fail(c, NQS_ENUMERIC, "non-finite parameter");
+    const bool held = c->have_samples;  // the held batch's activations follow
     if (c->cplx) {
-        HIPCHK(c, hipMemcpyAsync(c->b.hp, h.data(), 8 * np, hipMemcpyHostToDevice, c->stream));
-        const bool held = c->have_samples;
+        HIPCHK(c, hipMemcpyAsync(c->b.hp, in, 8 * np, hipMemcpyDeviceToDevice, c->stream));
         h_params_changed(c);
-        if (held) {  // activations of the held batch follow the new parameters
+        if (held) {
             launch_h_theta(c->stream, c->N, c->M, c->b.hp, c->b.samples, c->Ns, c->b.htsm,
                            nullptr, 0);
             c->have_samples = true;
         }
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        c->params_set = true;
-        return last_launch(c);
-    }
-    if (c->symm) {  // the symmetric parameters, expanded to the plain RBM's
-        HIPCHK(c, hipMemcpyAsync(c->b.psym, h.data(), 8 * np, hipMemcpyHostToDevice, c->stream));
-        launch_symm_expand(c->stream, c->N, c->G, c->alpha, c->vb, c->hb, c->b.perms, c->b.psym,
-                           c->b.tmpv);
     } else {
-        HIPCHK(c, hipMemcpyAsync(c->b.tmpv, h.data(), 8 * c->P, hipMemcpyHostToDevice, c->stream));
+        if (c->symm) {  // the symmetric parameters, expanded to the plain RBM's
+            HIPCHK(c, hipMemcpyAsync(c->b.psym, in, 8 * np, hipMemcpyDeviceToDevice, c->stream));
+            launch_symm_expand(c->stream, c->N, c->G, c->alpha, c->vb, c->hb, c->b.perms,
+                               c->b.psym, c->b.tmpv);
+        }
+        launch_unpack(c->stream, c->d, c->b.tmpv, c->b.Pm, (int)c->P);
+        launch_tables(c->stream, c->d, c->prec, c->b.Pm, c->b.tab);
+        c->chains_dirty = true;
+        c->have_grad = false;
+        if (held)
+            launch_theta(c->stream, c->d, c->prec, c->b.tab, c->b.samples, (int)c->Ns, c->b.tsm,
+                         nullptr, 0);
     }
-    launch_unpack(c->stream, c->d, c->b.tmpv, c->b.Pm, (int)c->P);
-    launch_tables(c->stream, c->d, c->prec, c->b.Pm, c->b.tab);
-    HIPCHK(c, hipStreamSynchronize(c->stream));
+    if (!on_device) HIPCHK(c, hipStreamSynchronize(c->stream));  // (the host copy has been read)
     c->params_set = true;
-    c->chains_dirty = true;
-    c->have_grad = false;
-    if (c->have_samples)  // activations of the held batch follow the new parameters
-        launch_theta(c->stream, c->d, c->prec, c->b.tab, c->b.samples, (int)c->Ns, c->b.tsm,
-                     nullptr, 0);
     return last_launch(c);
 }
 
