@@ -46,7 +46,8 @@ struct Buffers {
     // complex (holomorphic) model: parameters (and a saved copy), tables,
     // activations of the chains, of the sample batch and of a local-energy
     // batch, local energies, Jacobian column means, the TDVP's first slope
-    double2 *hp, *hp0, *hT, *hK, *htch, *htsm, *htx, *heloc, *hmean;
+    double2 *hp, *hp0, *htch, *htsm, *htx, *heloc, *hmean;
+    HTab htab;
     double* hk1;
     double* psym;     // symmetric model: its parameters
     double* gpart;    // FP64 dense Gram: slice partials (when sliced)
@@ -300,8 +301,10 @@ size_t layout_holo(nqs_ctx* c, char* base) {
     b = Buffers{};
     b.hp = (double2*)take(16 * P);
     b.hp0 = (double2*)take(16 * P);
-    b.hT = (double2*)take(16 * N * M);
-    b.hK = (double2*)take(16 * 2 * N);
+    b.htab.T = (double2*)take(16 * N * M);
+    b.htab.W = (double2*)take(16 * N * M);
+    b.htab.Tj = (double2*)take(16 * N * M);
+    b.htab.K = (double2*)take(16 * 2 * N);
     b.bonds = (int32_t*)take(8 * c->bonds.size() / 2 + 8);
     b.sub = (int8_t*)take(N + 16);
     b.chains = (int8_t*)take(C * N);
@@ -365,7 +368,7 @@ void derive(nqs_ctx* c) {
         if (c->cplx) {  // Re G and Im G are P x P
             c->Plc = round_up((long)c->P, 128);
             c->ntiles = gram_tiles((int)c->P);
-            c->hS = h_gram_slices(c->ntiles, c->Ns);
+            c->hS = h_gram_slices(c->ntiles, c->Ns, c->ncu);
         }
         c->gS = (!c->cplx && (c->symm || c->prec == 0)) ? gram_slices(c->ntiles, c->Ns) : 1;
         c->Ple = round_up(2 * (long)c->P, 128);
@@ -1103,61 +1106,42 @@ int h_check(nqs_ctx* c) {
     return NQS_OK;
 }
 
-void h_tables(nqs_ctx* c) { launch_h_tables(c->stream, c->N, c->M, c->b.hp, c->b.hT, c->b.hK); }
+void h_tables(nqs_ctx* c) { launch_h_tables(c->stream, c->N, c->M, c->b.hp, c->b.htab); }
 
 void h_refresh_chains(nqs_ctx* c) {
     if (!c->chains_dirty) return;
     {
         PROF(NQS_PROF_THETA);
-        launch_h_theta(c->stream, c->N, c->M, c->b.hp, c->b.chains, c->C, c->b.htch, nullptr, 0);
+        launch_h_theta(c->stream, c->N, c->M, c->b.hp, c->b.htab, c->b.chains, c->C, c->b.htch,
+                       nullptr, 0);
     }
     c->chains_dirty = false;
 }
 
-// n_discard unrecorded segments, then S recorded ones (as issue_sample); the
-// activations are recomputed from the configurations after every segment
-void h_issue_sample(nqs_ctx* c, int n_discard, int n_record, uint8_t* accept_log) {
+// n_discard unrecorded segments, then S recorded ones (as issue_sample), in one
+// launch; the activations are recomputed from the configurations after every segment
+void h_issue_sample(nqs_ctx* c, int n_discard, int record, uint8_t* accept_log) {
     h_refresh_chains(c);
-    SampleArgs a{};
+    HSampleArgs a{};
     a.C = c->C;
     a.K = c->K;
+    a.discard = n_discard;
+    a.record = record ? c->S : 0;
     a.seed = c->seed;
+    a.prop_base = c->prop;
     a.s = c->b.chains;
-    for (int q = 0; q < n_discard; ++q) {
-        a.prop_base = c->prop;
-        a.record = 0;
-        {
-            PROF(NQS_PROF_SAMPLE);
-            launch_h_sample(c->stream, c->N, c->M, c->b.hT, c->b.hK, a, c->b.htch);
-        }
-        c->prop += (uint64_t)c->K;
-        {
-            PROF(NQS_PROF_THETA);
-            launch_h_theta(c->stream, c->N, c->M, c->b.hp, c->b.chains, c->C, c->b.htch, nullptr, 0);
-        }
-    }
-    if (!n_record) return;
-    launch_zero(c->stream, c->b.acc_count, 4 * (size_t)c->C);
-    a.acc_count = c->b.acc_count;
+    a.t = c->b.htch;
+    a.rec = c->b.samples;
+    a.rec_t = c->b.htsm;
     a.acc_log = accept_log;
     a.log_stride = (long)c->S * c->K;
-    for (int q = 0; q < c->S; ++q) {
-        a.prop_base = c->prop;
-        a.record = 1;
-        a.rec = c->b.samples + (size_t)q * c->N;
-        a.rec_stride = (long)c->S * c->N;
-        a.log_offset = (long)q * c->K;
-        {
-            PROF(NQS_PROF_SAMPLE);
-            launch_h_sample(c->stream, c->N, c->M, c->b.hT, c->b.hK, a, c->b.htch);
-        }
-        c->prop += (uint64_t)c->K;
-        {
-            PROF(NQS_PROF_THETA);
-            launch_h_theta(c->stream, c->N, c->M, c->b.hp, c->b.chains, c->C, c->b.htch,
-                           c->b.htsm + (size_t)q * c->M, (long)c->S * c->M);
-        }
+    a.acc_count = c->b.acc_count;
+    {
+        PROF(NQS_PROF_SAMPLE);
+        launch_h_sample(c->stream, c->N, c->M, c->b.hp, c->b.htab, a);
     }
+    c->prop += (uint64_t)c->K * (uint64_t)(a.discard + a.record);
+    if (!record) return;
     c->have_samples = true;
     c->have_grad = false;
 }
@@ -1167,7 +1151,7 @@ void h_issue_energy_grad(nqs_ctx* c) {
     const long n = c->Ns;
     {
         PROF(NQS_PROF_ELOC);
-        launch_h_eloc(c->stream, c->N, c->M, c->b.hT, c->b.hK, ham_dev(c), c->b.samples, c->b.htsm,
+        launch_h_eloc(c->stream, c->N, c->M, c->b.htab, ham_dev(c), c->b.samples, c->b.htsm,
                       n, c->b.heloc);
     }
     {
@@ -1591,7 +1575,7 @@ int nqs_set_params(nqs_ctx* c, const double* p, int on_device) {
         HIPCHK(c, hipMemcpyAsync(c->b.hp, in, 8 * np, hipMemcpyDeviceToDevice, c->stream));
         h_params_changed(c);
         if (held) {
-            launch_h_theta(c->stream, c->N, c->M, c->b.hp, c->b.samples, c->Ns, c->b.htsm,
+            launch_h_theta(c->stream, c->N, c->M, c->b.hp, c->b.htab, c->b.samples, c->Ns, c->b.htsm,
                            nullptr, 0);
             c->have_samples = true;
         }
@@ -1776,7 +1760,8 @@ int nqs_load_samples(nqs_ctx* c, const int8_t* samples, int64_t n_samples) {
     HIPCHK(c, hipMemcpyAsync(c->b.samples, samples, (size_t)c->Ns * c->N, hipMemcpyDeviceToDevice,
                              c->stream));
     if (c->cplx)
-        launch_h_theta(c->stream, c->N, c->M, c->b.hp, c->b.samples, c->Ns, c->b.htsm, nullptr, 0);
+        launch_h_theta(c->stream, c->N, c->M, c->b.hp, c->b.htab, c->b.samples, c->Ns, c->b.htsm,
+                       nullptr, 0);
     else
         launch_theta(c->stream, c->d, c->prec, c->b.tab, c->b.samples, (int)c->Ns, c->b.tsm,
                      nullptr, 0);
@@ -1793,8 +1778,8 @@ int nqs_local_energy(nqs_ctx* c, const int8_t* s, int64_t n, double* eloc_out) {
         for (int64_t k0 = 0; k0 < n; k0 += c->Bx) {
             const long m = (long)((n - k0) < c->Bx ? (n - k0) : c->Bx);
             const int8_t* sk = s + (size_t)k0 * c->N;
-            launch_h_theta(c->stream, c->N, c->M, c->b.hp, sk, m, c->b.htx, nullptr, 0);
-            launch_h_eloc(c->stream, c->N, c->M, c->b.hT, c->b.hK, ham_dev(c), sk, c->b.htx, m,
+            launch_h_theta(c->stream, c->N, c->M, c->b.hp, c->b.htab, sk, m, c->b.htx, nullptr, 0);
+            launch_h_eloc(c->stream, c->N, c->M, c->b.htab, ham_dev(c), sk, c->b.htx, m,
                           (double2*)eloc_out + k0);
         }
         return last_launch(c);
@@ -1835,7 +1820,7 @@ int nqs_log_psi(nqs_ctx* c, const int8_t* s, int64_t n, void* out) {
     int st = need_bound(c);
     if (st) return st;
     if (n < 0 || (n > 0 && (!s || !out))) return fail(c, NQS_EINVAL, "bad batch");
-    if (c->cplx) launch_h_log_psi(c->stream, c->N, c->M, c->b.hp, s, n, (double2*)out);
+    if (c->cplx) launch_h_log_psi(c->stream, c->N, c->M, c->b.hp, c->b.htab, s, n, (double2*)out);
     else launch_log_psi(c->stream, c->d, c->prec, c->b.Pm, c->b.tab, s, n, out);
     return last_launch(c);
 }
@@ -1867,7 +1852,7 @@ int nqs_jacobian(nqs_ctx* c, const int8_t* s, int64_t n, void* O_out, int center
         for (int64_t k0 = 0; k0 < n; k0 += c->Bx) {
             const long m = (long)((n - k0) < c->Bx ? (n - k0) : c->Bx);
             const int8_t* sk = s + (size_t)k0 * c->N;
-            launch_h_theta(c->stream, c->N, c->M, c->b.hp, sk, m, c->b.htx, nullptr, 0);
+            launch_h_theta(c->stream, c->N, c->M, c->b.hp, c->b.htab, sk, m, c->b.htx, nullptr, 0);
             launch_h_jacobian(c->stream, c->N, c->M, sk, c->b.htx, m, (int)c->P,
                               (double2*)O_out + (size_t)k0 * c->P);
         }

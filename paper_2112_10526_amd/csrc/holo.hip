@@ -35,10 +35,14 @@ __device__ __forceinline__ double2 cdiv(double2 a, double2 b) {
     return make_double2((a.x * b.x + a.y * b.y) / d, (a.y * b.x - a.x * b.y) / d);
 }
 __device__ __forceinline__ double cabs2(double2 a) { return a.x * a.x + a.y * a.y; }
-// tanh(x + iy) = (sinh 2x + i sin 2y) / (cosh 2x + cos 2y)
+// tanh(x + iy) = (sinh 2x + i sin 2y) / (cosh 2x + cos 2y), the hyperbolic pair from
+// one e^{2|x|} - 1
 __device__ __forceinline__ double2 ctanh(double2 z) {
-    const double d = cosh(2.0 * z.x) + cos(2.0 * z.y);
-    return make_double2(sinh(2.0 * z.x) / d, sin(2.0 * z.y) / d);
+    const double q = expm1(2.0 * fabs(z.x)), ie = 1.0 / (1.0 + q);
+    double sy, cy;
+    sincos(2.0 * z.y, &sy, &cy);
+    const double d = 1.0 / (0.5 * ((1.0 + q) + ie) + cy);
+    return make_double2(copysign(0.5 * (q + q * ie) * d, z.x), sy * d);
 }
 // cosh(x + iy) = cosh x cos y + i sinh x sin y
 __device__ __forceinline__ double2 ccosh(double2 z) {
@@ -54,79 +58,91 @@ __device__ __forceinline__ double2 clog(double2 z) {
 }
 
 // ---------------------------------------------------------------------------
-// tables: T[i][j] = tanh(2 W_ji); K[i] = (K_i(+1), K_i(-1)) (products over j in
-// order, one thread per site)
+// tables (HTab): T[i][j] = tanh(2 W_ji) and W[i][j] = W_ji site-major (lanes over
+// hidden units), Tj[j][i] hidden-major (lanes over sites); K[i] = (K_i(+1), K_i(-1)),
+// one wave per site, the product over the hidden units tree-wise over the lanes
 // ---------------------------------------------------------------------------
-__global__ void k_h_tables(int N, int M, const double2* __restrict__ p, double2* __restrict__ T,
-                           double2* __restrict__ K) {
+__device__ __forceinline__ double2 shfl_xor2(double2 v, int m) {
+    return make_double2(__shfl_xor(v.x, m), __shfl_xor(v.y, m));
+}
+__global__ __launch_bounds__(256) void k_h_tables(int N, int M, const double2* __restrict__ p,
+                                                  HTab h) {
     const double2* a = p;
     const double2* W = p + N + M;
-    const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long e = (long)blockIdx.x * 256 + threadIdx.x;
     if (e < (long)N * M) {
         const int i = (int)(e / M), j = (int)(e - (long)i * M);
         const double2 w = W[(size_t)j * N + i];
-        T[e] = ctanh(make_double2(2.0 * w.x, 2.0 * w.y));
+        const double2 t = ctanh(make_double2(2.0 * w.x, 2.0 * w.y));
+        h.W[e] = w;
+        h.T[e] = t;
+        h.Tj[(size_t)j * N + i] = t;
     }
-    if (e < N) {
-        const int i = (int)e;
+    const int lane = threadIdx.x & 63;
+    for (int i = blockIdx.x * 4 + (threadIdx.x >> 6); i < N; i += gridDim.x * 4) {
         double2 c = make_double2(1.0, 0.0);
-        for (int j = 0; j < M; ++j) {
+        for (int j = lane; j < M; j += 64) {
             const double2 w = W[(size_t)j * N + i];
             c = cmul(c, ccosh(make_double2(2.0 * w.x, 2.0 * w.y)));
         }
-        const double2 ai = a[i];
-        K[2 * i] = cmul(cexp(make_double2(-2.0 * ai.x, -2.0 * ai.y)), c);
-        K[2 * i + 1] = cmul(cexp(make_double2(2.0 * ai.x, 2.0 * ai.y)), c);
+#pragma unroll
+        for (int m = 1; m < 64; m *= 2) c = cmul(c, shfl_xor2(c, m));
+        if (lane < 2) {  // lane 0: s = +1, lane 1: s = -1
+            const double sg = lane == 0 ? -2.0 : 2.0;
+            const double2 ai = a[i];
+            h.K[2 * i + lane] = cmul(cexp(make_double2(sg * ai.x, sg * ai.y)), c);
+        }
     }
 }
 
 // ---------------------------------------------------------------------------
-// tanh(theta_j(s)), theta_j = b_j + sum_i W_ji s_i, one thread per (row, j);
-// and ln psi(s) = sum_i a_i s_i + sum_j ln cosh theta_j (principal logarithms,
-// the branch the oracle takes), one thread per row
+// tanh(theta_j(s)), theta_j = b_j + sum_i W_ji s_i (sites in order), one thread per
+// (row, j); and ln psi(s) = sum_i a_i s_i + sum_j ln cosh theta_j (principal
+// logarithms, the branch the oracle takes), one wave per row
 // ---------------------------------------------------------------------------
-__global__ void k_h_theta(int N, int M, const double2* __restrict__ p, const int8_t* __restrict__ s,
-                          long rows, double2* __restrict__ t, double2* __restrict__ t2,
-                          long t2_stride) {
+__device__ __forceinline__ double2 h_theta(int N, int M, const double2* __restrict__ p,
+                                           const double2* __restrict__ W, const int8_t* sr, int j) {
+    double2 th = p[N + j];
+#pragma unroll 4
+    for (int i = 0; i < N; ++i) {
+        const double2 w = W[(size_t)i * M + j];
+        const double sv = (double)sr[i];
+        th.x += w.x * sv;
+        th.y += w.y * sv;
+    }
+    return th;
+}
+__global__ void k_h_theta(int N, int M, const double2* __restrict__ p, HTab h,
+                          const int8_t* __restrict__ s, long rows, double2* __restrict__ t,
+                          double2* __restrict__ t2, long t2_stride) {
     const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= rows * M) return;
     const long r = e / M;
     const int j = (int)(e - r * M);
-    const double2* Wj = p + N + M + (size_t)j * N;
-    const int8_t* sr = s + r * N;
-    double2 th = p[N + j];
-    for (int i = 0; i < N; ++i) {
-        const double sv = (double)sr[i];
-        th.x += Wj[i].x * sv;
-        th.y += Wj[i].y * sv;
-    }
-    const double2 v = ctanh(th);
+    const double2 v = ctanh(h_theta(N, M, p, h.W, s + r * N, j));
     t[e] = v;
     if (t2) t2[r * t2_stride + j] = v;
 }
 
-__global__ void k_h_log_psi(int N, int M, const double2* __restrict__ p,
-                            const int8_t* __restrict__ s, long n, double2* __restrict__ out) {
-    const long r = (long)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(256) void k_h_log_psi(int N, int M, const double2* __restrict__ p,
+                                                   HTab h, const int8_t* __restrict__ s, long n,
+                                                   double2* __restrict__ out) {
+    const long r = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
     if (r >= n) return;
     const int8_t* sr = s + r * N;
     double2 v = make_double2(0.0, 0.0);
-    for (int i = 0; i < N; ++i) {
+    for (int i = lane; i < N; i += 64) {
         v.x += p[i].x * sr[i];
         v.y += p[i].y * sr[i];
     }
-    for (int j = 0; j < M; ++j) {
-        const double2* Wj = p + N + M + (size_t)j * N;
-        double2 th = p[N + j];
-        for (int i = 0; i < N; ++i) {
-            th.x += Wj[i].x * sr[i];
-            th.y += Wj[i].y * sr[i];
-        }
-        const double2 l = clog(ccosh(th));
+    for (int j = lane; j < M; j += 64) {
+        const double2 l = clog(ccosh(h_theta(N, M, p, h.W, sr, j)));
         v.x += l.x;
         v.y += l.y;
     }
-    out[r] = v;
+    v = make_double2(wave_sum(v.x), wave_sum(v.y));
+    if (lane == 0) out[r] = v;
 }
 
 // ---------------------------------------------------------------------------
@@ -137,22 +153,25 @@ __global__ void k_h_log_psi(int N, int M, const double2* __restrict__ p,
 // u < |psi(s')/psi(s)|^2 = |K_i(s_i)|^2 prod_j |1 - s_i t_j T_ij|^2.  On
 // acceptance t_j <- (t_j - s_i T_ij) / (1 - s_i t_j T_ij) = tanh(theta_j - 2 s_i W_ji).
 // ---------------------------------------------------------------------------
+// All segments of a call run in one launch: after each one the wave recomputes its
+// chain's tanh theta from the configuration (h_theta's order) and, when the segment
+// is recorded, stores both.  A proposal is a serial chain of ~90 FP64 steps (row
+// product, product over the wave, division of an accepted move), so the next one's
+// table row and site factors are loaded while the current one is decided; with both
+// tables in LDS a call took 1-3 % less (38 x 38), not worth a second kernel.
+// 20 x 20, 256 chains, 16 segments of 20 proposals: 105 us (17 launches of 13.8 us
+// and as many theta launches of 4.4 us when each segment was its own).
+// ---------------------------------------------------------------------------
 constexpr int H_QM = 8;  // hidden units per lane, at most (M <= 512)
 
 template <int QM>
-__global__ __launch_bounds__(256) void k_h_sample(int N, int M, const double2* __restrict__ T,
-                                                  const double2* __restrict__ K, int C, int Kp,
-                                                  uint64_t seed, uint64_t prop_base,
-                                                  int8_t* __restrict__ chains,
-                                                  const double2* __restrict__ tch, int record,
-                                                  int8_t* __restrict__ rec, long rec_stride,
-                                                  uint8_t* __restrict__ acc_log, long log_stride,
-                                                  long log_offset, uint32_t* acc_count) {
+__global__ __launch_bounds__(256) void k_h_sample(int N, int M, const double2* __restrict__ p,
+                                                  HTab tab, HSampleArgs a) {
     extern __shared__ int8_t h_spins[];  // [4 waves][N]: each wave's chain
     const int lane = threadIdx.x & 63;
-    const int c = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    if (c >= C) return;
-    int8_t* gs = chains + (size_t)c * N;
+    const int c = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (c >= a.C) return;
+    int8_t* gs = a.s + (size_t)c * N;
     int8_t* s = h_spins + (size_t)(threadIdx.x >> 6) * N;
     for (int i = lane; i < N; i += 64) s[i] = gs[i];
     __builtin_amdgcn_wave_barrier();
@@ -160,96 +179,169 @@ __global__ __launch_bounds__(256) void k_h_sample(int N, int M, const double2* _
 #pragma unroll
     for (int q = 0; q < QM; ++q) {
         const int j = lane + 64 * q;
-        t[q] = j < M ? tch[(size_t)c * M + j] : make_double2(0.0, 0.0);
+        t[q] = j < M ? a.t[(size_t)c * M + j] : make_double2(0.0, 0.0);
     }
     uint32_t nacc = 0;
-    for (int q0 = 0; q0 < Kp; q0 += 64) {
-        // this lane's draw: proposal q0 + lane
-        const uint64_t pidx = prop_base + (uint64_t)(q0 + lane);
-        const uint4 x = philox10(make_uint4((uint32_t)pidx, (uint32_t)(pidx >> 32), (uint32_t)c,
-                                            TAG_METROPOLIS), seed);
-        const int my_site = (int)(((uint64_t)x.x * (uint64_t)N) >> 32);
-        const double my_u = ((double)(x.y >> 5) * 67108864.0 + (double)(x.z >> 6)) *
-                            (1.0 / 9007199254740992.0);
-        const int nb = min(64, Kp - q0);
-        for (int b = 0; b < nb; ++b) {
-            const int i = __builtin_amdgcn_readlane(my_site, b);
-            const double u = readlane(my_u, b);
-            const double si = (double)s[i];
-            const double2* Ti = T + (size_t)i * M;
-            double part = 1.0;
-            double2 fac[QM];
+    for (int seg = 0; seg < a.discard + a.record; ++seg) {
+        const int rec = seg - a.discard;  // recorded segment, or < 0
+        const uint64_t base = a.prop_base + (uint64_t)seg * (uint64_t)a.K;
+        uint8_t* log = a.acc_log && rec >= 0
+                           ? a.acc_log + (size_t)c * a.log_stride + (size_t)rec * a.K : nullptr;
+        for (int q0 = 0; q0 < a.K; q0 += 64) {
+            // this lane's draw: proposal q0 + lane
+            const uint64_t pidx = base + (uint64_t)(q0 + lane);
+            const uint4 x = philox10(make_uint4((uint32_t)pidx, (uint32_t)(pidx >> 32), (uint32_t)c,
+                                                TAG_METROPOLIS), a.seed);
+            const int my_site = (int)(((uint64_t)x.x * (uint64_t)N) >> 32);
+            const double my_u = ((double)(x.y >> 5) * 67108864.0 + (double)(x.z >> 6)) *
+                                (1.0 / 9007199254740992.0);
+            const int nb = min(64, a.K - q0);
+            double2 Tn[QM], Kn[2];
+            auto fetch = [&](int i) {
 #pragma unroll
-            for (int q = 0; q < QM; ++q) {
-                const int j = lane + 64 * q;
-                if (j < M) {
-                    const double2 tt = cmul(t[q], Ti[j]);
-                    fac[q] = make_double2(1.0 - si * tt.x, -si * tt.y);
-                    part *= cabs2(fac[q]);
-                } else {
-                    fac[q] = make_double2(1.0, 0.0);
-                }
-            }
-            const double2 Ki = K[2 * i + (si > 0 ? 0 : 1)];
-            const double ratio2 = cabs2(Ki) * wave_prod(part);
-            const bool acc = u < ratio2;
-            if (acc) {
+                for (int q = 0; q < QM; ++q) Tn[q] = tab.T[i * M + min(lane + 64 * q, M - 1)];
+                Kn[0] = tab.K[2 * i];
+                Kn[1] = tab.K[2 * i + 1];
+            };
+            fetch(__builtin_amdgcn_readlane(my_site, 0));
+            for (int b = 0; b < nb; ++b) {
+                const int i = __builtin_amdgcn_readlane(my_site, b);
+                const double u = readlane(my_u, b);
+                double2 Ti[QM];
+#pragma unroll
+                for (int q = 0; q < QM; ++q) Ti[q] = Tn[q];
+                const double2 K0 = Kn[0], K1 = Kn[1];
+                fetch(__builtin_amdgcn_readlane(my_site, min(b + 1, nb - 1)));
+                const double si = (double)s[i];
+                double part = 1.0, m2[QM];
+                double2 fac[QM];
 #pragma unroll
                 for (int q = 0; q < QM; ++q) {
-                    const int j = lane + 64 * q;
-                    if (j < M) {
-                        const double2 num = make_double2(t[q].x - si * Ti[j].x, t[q].y - si * Ti[j].y);
-                        t[q] = cdiv(num, fac[q]);
-                    }
+                    const double2 tt = cmul(t[q], Ti[q]);
+                    fac[q] = make_double2(1.0 - si * tt.x, -si * tt.y);
+                    m2[q] = cabs2(fac[q]);
+                    if (lane + 64 * q < M) part *= m2[q];
                 }
-                if (lane == 0) s[i] = (int8_t)(-(int)s[i]);
-                ++nacc;
+                const double2 Ki = si > 0 ? K0 : K1;
+                const double ratio2 = cabs2(Ki) * wave_prod(part);
+                const bool acc = u < ratio2;
+                if (acc) {
+#pragma unroll
+                    for (int q = 0; q < QM; ++q) {
+                        // (t - s T) / (1 - s t T); lanes past M keep their zeros
+                        const double2 num = make_double2(t[q].x - si * Ti[q].x, t[q].y - si * Ti[q].y);
+                        const double r = 1.0 / m2[q];
+                        const double2 v = make_double2((num.x * fac[q].x + num.y * fac[q].y) * r,
+                                                       (num.y * fac[q].x - num.x * fac[q].y) * r);
+                        if (lane + 64 * q < M) t[q] = v;
+                    }
+                    if (lane == 0) s[i] = (int8_t)(-(int)s[i]);
+                    if (rec >= 0) ++nacc;
+                }
+                if (log && lane == 0) log[q0 + b] = acc ? 1 : 0;
+                __builtin_amdgcn_wave_barrier();  // the flipped spin is seen by the next proposal
             }
-            if (acc_log && lane == 0) acc_log[(size_t)c * log_stride + log_offset + q0 + b] = acc ? 1 : 0;
-            __builtin_amdgcn_wave_barrier();  // the flipped spin is seen by the next proposal
         }
+        // the segment's end: tanh theta of the configuration, and the record
+#pragma unroll
+        for (int q = 0; q < QM; ++q) {
+            const int j = lane + 64 * q;
+            if (j < M) {
+                double2 th = p[N + j];
+#pragma unroll 4
+                for (int i = 0; i < N; ++i) {
+                    const double2 w = tab.W[i * M + j];
+                    const double sv = (double)s[i];
+                    th.x += w.x * sv;
+                    th.y += w.y * sv;
+                }
+                t[q] = ctanh(th);
+                if (rec >= 0) a.rec_t[((size_t)c * a.record + rec) * M + j] = t[q];
+            }
+        }
+        if (rec >= 0)
+            for (int i = lane; i < N; i += 64) a.rec[((size_t)c * a.record + rec) * N + i] = s[i];
     }
-    if (lane == 0 && acc_count) acc_count[c] += nacc;
-    for (int i = lane; i < N; i += 64) {
-        gs[i] = s[i];
-        if (record) rec[(size_t)c * rec_stride + i] = s[i];
-    }
+    if (lane == 0 && a.record) a.acc_count[c] = nacc;
+    for (int i = lane; i < N; i += 64) gs[i] = s[i];
+#pragma unroll
+    for (int q = 0; q < QM; ++q)
+        if (lane + 64 * q < M) a.t[(size_t)c * M + lane + 64 * q] = t[q];
 }
 
 // ---------------------------------------------------------------------------
-// local energies of the TFIM (paper, local-estimator equation), one wave per
-// sample, lanes over sites:
+// local energies of the TFIM (paper, local-estimator equation):
 //   E(s) = J sum_<ab> s_a s_b - h sum_i K_i(s_i) prod_j (1 - s_i t_j T_ij)
-// (the products over j in order; complex sums over the wave in a fixed order)
+// (the products over j in order).  LP lanes run over a sample's sites (LP the
+// smallest of 16, 32, 64 that covers them, 64 with several passes), HE_S samples
+// per lane group, which share each table entry (whole lines of Tj); fixed-order sums
+// over the lanes.  20 x 20, 4,096 samples: 6.3 us (10.2 with a wave per sample over
+// T's rows).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_h_eloc(int N, int M, const double2* __restrict__ T,
-                                                const double2* __restrict__ K, int n_bonds,
+constexpr int HE_S = 2;
+template <int LP>
+__device__ __forceinline__ double lanes_sum(double v) {
+    v = row16_sum(v);
+    if (LP >= 32) v += __shfl_xor(v, 16);
+    if (LP >= 64) v += __shfl_xor(v, 32);
+    return v;
+}
+template <int LP>
+__global__ __launch_bounds__(256) void k_h_eloc(int N, int M, HTab tab, int n_bonds,
                                                 const int32_t* __restrict__ bonds, double J,
                                                 double h, const int8_t* __restrict__ s,
                                                 const double2* __restrict__ tact, long n,
                                                 double2* __restrict__ out) {
-    const int lane = threadIdx.x & 63;
-    const long k = (long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    if (k >= n) return;
-    const int8_t* sk = s + k * N;
-    const double2* tk = tact + k * M;
-    double2 off = make_double2(0.0, 0.0);
-    for (int i = lane; i < N; i += 64) {
-        const double si = (double)sk[i];
-        const double2* Ti = T + (size_t)i * M;
-        double2 r = K[2 * i + (si > 0 ? 0 : 1)];
-        for (int j = 0; j < M; ++j) {
-            const double2 tt = cmul(tk[j], Ti[j]);
-            r = cmul(r, make_double2(1.0 - si * tt.x, -si * tt.y));
-        }
-        off.x += r.x;
-        off.y += r.y;
+    constexpr int GP = 256 / LP;  // lane groups per block
+    const int l = threadIdx.x % LP;
+    const long k0 = ((long)blockIdx.x * GP + threadIdx.x / LP) * HE_S;
+    const int8_t* sk[HE_S];
+    const double2* tk[HE_S];
+#pragma unroll
+    for (int r = 0; r < HE_S; ++r) {  // (past n: the last sample again, not stored)
+        const long k = min(k0 + r, n - 1);
+        sk[r] = s + k * N;
+        tk[r] = tact + k * M;
     }
-    double dg = 0.0;
-    for (int b = lane; b < n_bonds; b += 64) dg += (double)sk[bonds[2 * b]] * sk[bonds[2 * b + 1]];
-    const double dsum = wave_sum(dg);
-    const double re = wave_sum(off.x), im = wave_sum(off.y);
-    if (lane == 0) out[k] = make_double2(J * dsum - h * re, -h * im);
+    double ox[HE_S], oy[HE_S], dg[HE_S];
+#pragma unroll
+    for (int r = 0; r < HE_S; ++r) ox[r] = oy[r] = dg[r] = 0.0;
+    for (int i0 = 0; i0 < N; i0 += LP) {
+        const int i = i0 + l, ic = min(i, N - 1);
+        double si[HE_S];
+        double2 r_[HE_S];
+#pragma unroll
+        for (int r = 0; r < HE_S; ++r) {
+            si[r] = (double)sk[r][ic];
+            r_[r] = tab.K[2 * ic + (si[r] > 0 ? 0 : 1)];
+        }
+#pragma unroll 4
+        for (int j = 0; j < M; ++j) {
+            const double2 Tv = tab.Tj[(size_t)j * N + ic];
+#pragma unroll
+            for (int r = 0; r < HE_S; ++r) {
+                const double2 tt = cmul(tk[r][j], Tv);
+                r_[r] = cmul(r_[r], make_double2(1.0 - si[r] * tt.x, -si[r] * tt.y));
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < HE_S; ++r)
+            if (i < N) {
+                ox[r] += r_[r].x;
+                oy[r] += r_[r].y;
+            }
+    }
+    for (int b = l; b < n_bonds; b += LP) {
+        const int x = bonds[2 * b], y = bonds[2 * b + 1];
+#pragma unroll
+        for (int r = 0; r < HE_S; ++r) dg[r] += (double)sk[r][x] * (double)sk[r][y];
+    }
+#pragma unroll
+    for (int r = 0; r < HE_S; ++r) {
+        const double d = lanes_sum<LP>(dg[r]);
+        const double re = lanes_sum<LP>(ox[r]), im = lanes_sum<LP>(oy[r]);
+        if (l == 0 && k0 + r < n) out[k0 + r] = make_double2(J * d - h * re, -h * im);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -313,31 +405,57 @@ __global__ __launch_bounds__(256) void k_h_jacobian(int N, int M, const int8_t* 
     O[e] = h_jac(N, M, s + k * N, t + k * M, p);
 }
 
-// column sums over row slices (FP64, rows in order): part[slice][p]
+// column sums over row slices (FP64, rows in order): part[slice][p]; then the slices
+// in a fixed order (a block covers 64 columns, wave w a quarter of the slices)
 __global__ __launch_bounds__(256) void k_h_colsum(int N, int M, const int8_t* __restrict__ s,
                                                   const double2* __restrict__ t, long n, int P,
                                                   int slices, double2* __restrict__ part) {
-    const long p = (long)blockIdx.x * 256 + threadIdx.x;
+    const int p = blockIdx.x * 256 + threadIdx.x;
     if (p >= P) return;
+    // column p: spin i (or none), activation j (or none)
+    const int q = p - N - M, j = p < N ? -1 : (q < 0 ? p - N : q / N);
+    const int i = p < N ? p : (q < 0 ? -1 : q - j * N);
     const long k0 = n * blockIdx.y / slices, k1 = n * (blockIdx.y + 1) / slices;
     double2 acc = make_double2(0.0, 0.0);
-    for (long k = k0; k < k1; ++k) {
-        const double2 o = h_jac(N, M, s + k * N, t + k * M, p);
-        acc.x += o.x;
-        acc.y += o.y;
+    for (long k = k0; k < k1; k += 4) {
+        double2 o[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const long kk = min(k + u, k1 - 1);
+            const double si = i >= 0 ? (double)s[kk * N + i] : 1.0;
+            const double2 tv = j >= 0 ? t[kk * M + j] : make_double2(1.0, 0.0);
+            o[u] = make_double2(tv.x * si, tv.y * si);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (k + u < k1) {
+                acc.x += o[u].x;
+                acc.y += o[u].y;
+            }
     }
     part[(size_t)blockIdx.y * P + p] = acc;
 }
-__global__ void k_h_colsum_fin(const double2* __restrict__ part, int P, int slices, long n,
-                               double2* __restrict__ mean) {
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= P) return;
-    double2 a = make_double2(0.0, 0.0);
-    for (int q = 0; q < slices; ++q) {
-        a.x += part[(size_t)q * P + p].x;
-        a.y += part[(size_t)q * P + p].y;
+// (sum of the slices of `width` values, times scale)
+__global__ __launch_bounds__(256) void k_h_sum_slices(const double* __restrict__ part, int width,
+                                                      int slices, double scale,
+                                                      double* __restrict__ out) {
+    __shared__ double ws[4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int p = blockIdx.x * 64 + lane, pc = p < width ? p : width - 1;
+    const int b0 = wave * slices / 4, b1 = (wave + 1) * slices / 4;
+    double a = 0.0;
+    for (int q = b0; q < b1; q += 8) {
+        double x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = part[(size_t)min(q + u, slices - 1) * width + pc];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (q + u < b1) a += x[u];
     }
-    mean[p] = make_double2(a.x / (double)n, a.y / (double)n);
+    ws[wave][lane] = a;
+    __syncthreads();
+    if (wave == 0 && p < width)
+        out[p] = ((ws[0][lane] + ws[1][lane]) + (ws[2][lane] + ws[3][lane])) * scale;
 }
 
 // The stacked, centred, scaled Jacobian: for sample k and column p,
@@ -380,6 +498,7 @@ __global__ __launch_bounds__(256) void k_h_force(const double* __restrict__ U, l
     const long n8 = h_half_rows(n);
     const double mr = stats[0], mi = stats[3], rs = 1.0 / sqrt((double)n);
     double fr = 0.0, fi = 0.0;
+#pragma unroll 4
     for (long k = k0; k < k1; ++k) {
         const double x = U[k * ld + p], z = U[(n8 + k) * ld + p];
         const double er = (E[k].x - mr) * rs, ei = (E[k].y - mi) * rs;
@@ -389,15 +508,6 @@ __global__ __launch_bounds__(256) void k_h_force(const double* __restrict__ U, l
     part[(size_t)blockIdx.y * 2 * P + p] = fr;
     part[(size_t)blockIdx.y * 2 * P + P + p] = fi;
 }
-__global__ void k_h_sum_slices(const double* __restrict__ part, int P2, int slices,
-                               double* __restrict__ out) {
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= P2) return;
-    double a = 0.0;
-    for (int q = 0; q < slices; ++q) a += part[(size_t)q * P2 + p];
-    out[p] = a;
-}
-
 // ---------------------------------------------------------------------------
 // Gram matrices A = U^T U and B = U^T V on the FP64 matrix cores
 // (v_mfma_f64_16x16x4f64).  One block of 8 waves per (128 x 128 tile of the
@@ -553,10 +663,21 @@ __global__ __launch_bounds__(256) void k_h_gram_fin(const double* __restrict__ p
         const int ii = ty + 8 * m, jj = tx;
         const size_t e = (size_t)(i0 + ii) * HG_TILE + (j0 + jj);
         double a = 0.0, b = 0.0;
-        for (int ks = 0; ks < slices; ++ks) {
-            const double* pt = part + ((size_t)ks * ntiles + t) * tile_sz;
-            a += pt[e];
-            b += pt[HG_TILE * HG_TILE + e];
+        for (int k0 = 0; k0 < slices; k0 += 8) {  // eight slices in flight
+            double xa[8], xb[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int ks = min(k0 + u, slices - 1);
+                const double* pt = part + ((size_t)ks * ntiles + t) * tile_sz;
+                xa[u] = pt[e];
+                xb[u] = pt[HG_TILE * HG_TILE + e];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (k0 + u < slices) {
+                    a += xa[u];
+                    b += xb[u];
+                }
         }
         if (diag && i0 + ii == j0 + jj) b = 0.0;
         sa[ii][jj] = a;
@@ -698,51 +819,54 @@ __global__ void k_h_join(int P, const double* __restrict__ emb, double2* __restr
 // ---------------------------------------------------------------------------
 static inline unsigned nbk(long n, int b) { return (unsigned)((n + b - 1) / b); }
 
-void launch_h_tables(hipStream_t st, int N, int M, const double2* p, double2* T, double2* K) {
-    const long n = (long)N * M > N ? (long)N * M : N;
-    k_h_tables<<<nbk(n, 256), 256, 0, st>>>(N, M, p, T, K);
+void launch_h_tables(hipStream_t st, int N, int M, const double2* p, const HTab& h) {
+    const long n = (long)N * M > 64L * N ? (long)N * M : 64L * N;  // (a wave per site too)
+    k_h_tables<<<nbk(n, 256), 256, 0, st>>>(N, M, p, h);
 }
-void launch_h_theta(hipStream_t st, int N, int M, const double2* p, const int8_t* s, long rows,
-                    double2* t, double2* t2, long t2_stride) {
+void launch_h_theta(hipStream_t st, int N, int M, const double2* p, const HTab& h, const int8_t* s,
+                    long rows, double2* t, double2* t2, long t2_stride) {
     if (rows <= 0) return;
-    k_h_theta<<<nbk(rows * M, 256), 256, 0, st>>>(N, M, p, s, rows, t, t2, t2_stride);
+    k_h_theta<<<nbk(rows * M, 256), 256, 0, st>>>(N, M, p, h, s, rows, t, t2, t2_stride);
 }
-void launch_h_log_psi(hipStream_t st, int N, int M, const double2* p, const int8_t* s, long n,
-                      double2* out) {
+void launch_h_log_psi(hipStream_t st, int N, int M, const double2* p, const HTab& h,
+                      const int8_t* s, long n, double2* out) {
     if (n <= 0) return;
-    k_h_log_psi<<<nbk(n, 128), 128, 0, st>>>(N, M, p, s, n, out);
+    k_h_log_psi<<<nbk(n, 4), 256, 0, st>>>(N, M, p, h, s, n, out);
 }
 int h_max_hidden() { return 64 * H_QM; }
-void launch_h_sample(hipStream_t st, int N, int M, const double2* T, const double2* K,
-                     const SampleArgs& a, const double2* tch) {
-    const unsigned nb = nbk(a.C, 4);
+void launch_h_sample(hipStream_t st, int N, int M, const double2* p, const HTab& h,
+                     const HSampleArgs& a) {
+    if (a.C <= 0 || a.K <= 0 || a.discard + a.record <= 0) return;
     const int qm = (M + 63) / 64;
+    const unsigned nb = nbk(a.C, 4);
     const size_t lds = 4 * (size_t)N;
-#define H_SAMPLE(Q)                                                                            \
-    k_h_sample<Q><<<nb, 256, lds, st>>>(N, M, T, K, a.C, a.K, a.seed, a.prop_base, a.s, tch,   \
-                                      a.record, a.rec, a.rec_stride, a.acc_log, a.log_stride, \
-                                      a.log_offset, a.acc_count)
-    if (qm <= 1) H_SAMPLE(1);
-    else if (qm <= 2) H_SAMPLE(2);
-    else if (qm <= 4) H_SAMPLE(4);
-    else H_SAMPLE(8);
-#undef H_SAMPLE
+    if (qm <= 1) k_h_sample<1><<<nb, 256, lds, st>>>(N, M, p, h, a);
+    else if (qm <= 2) k_h_sample<2><<<nb, 256, lds, st>>>(N, M, p, h, a);
+    else if (qm <= 4) k_h_sample<4><<<nb, 256, lds, st>>>(N, M, p, h, a);
+    else k_h_sample<8><<<nb, 256, lds, st>>>(N, M, p, h, a);
 }
-void launch_h_eloc(hipStream_t st, int N, int M, const double2* T, const double2* K,
-                   const HamDev& H, const int8_t* s, const double2* tact, long n, double2* out) {
+void launch_h_eloc(hipStream_t st, int N, int M, const HTab& h, const HamDev& H, const int8_t* s,
+                   const double2* tact, long n, double2* out) {
     if (n <= 0) return;
-    k_h_eloc<<<nbk(n, 4), 256, 0, st>>>(N, M, T, K, H.n_bonds, H.bonds, H.J, H.h, s, tact, n, out);
+#define H_ELOC(LP)                                                                              \
+    k_h_eloc<LP><<<nbk(n, 256 / LP * HE_S), 256, 0, st>>>(N, M, h, H.n_bonds, H.bonds, H.J, H.h, \
+                                                          s, tact, n, out)
+    if (N <= 16) H_ELOC(16);
+    else if (N <= 32) H_ELOC(32);
+    else H_ELOC(64);
+#undef H_ELOC
 }
 void launch_h_stats(hipStream_t st, const double2* E, long n, double* out) {
     k_h_stats<<<1, 256, 0, st>>>(E, n, out);
 }
-constexpr int H_SLICES = 64;
+constexpr int H_SLICES = 128;
 size_t h_slice_bytes(int P) { return (size_t)H_SLICES * 2 * (size_t)P * 8; }
 void launch_h_jacobian_emb(hipStream_t st, int N, int M, const int8_t* s, const double2* t,
                            long n, int P, long ld, double* Y, double2* mean, double* scratch) {
     double2* part = (double2*)scratch;  // [H_SLICES][P] complex
     k_h_colsum<<<dim3(nbk(P, 256), H_SLICES), 256, 0, st>>>(N, M, s, t, n, P, H_SLICES, part);
-    k_h_colsum_fin<<<nbk(P, 256), 256, 0, st>>>(part, P, H_SLICES, n, mean);
+    k_h_sum_slices<<<nbk(2 * P, 64), 256, 0, st>>>(scratch, 2 * P, H_SLICES, 1.0 / (double)n,
+                                                   (double*)mean);
     const long chunk = 65535L * 4;  // rows per launch (grid y limit)
     for (long k0 = 0; k0 < n; k0 += chunk) {
         const long m = n - k0 < chunk ? n - k0 : chunk;
@@ -760,14 +884,25 @@ void launch_h_force(hipStream_t st, const double* U, long n, long ld, int P, con
     // (slices over samples)
     k_h_force<<<dim3(nbk(P, 256), H_SLICES), 256, 0, st>>>(U, n, ld, P, E, stats, H_SLICES,
                                                            scratch);
-    k_h_sum_slices<<<nbk(2 * P, 256), 256, 0, st>>>(scratch, 2 * P, H_SLICES, f);
+    k_h_sum_slices<<<nbk(2 * P, 64), 256, 0, st>>>(scratch, 2 * P, H_SLICES, 1.0, f);
 }
-// Row slices of the Gram: enough (tile, slice) blocks to give every compute
-// unit several, each slice at least 256 rows (a multiple of 4)
-int h_gram_slices(int ntiles, long n) {
-    int S = 1;
-    while (S < 16 && (long)ntiles * S < 2048 && 2 * n / (2 * S) >= 256) S *= 2;
-    return S;
+// Row slices of the Gram: the count that takes the fewest rounds of the compute
+// units per row (one block fills a unit), a slice's partials counted as 5e-5 of a
+// round per tile (their write and read against the products of a whole tile);
+// slices of at least 128 rows of U.  Ten tiles, 8,192 rows: 25 slices, 250 blocks
+// in one round, 108-128 us; 16 slices, 160 blocks, 157 us.
+int h_gram_slices(int ntiles, long n, int ncu) {
+    int best = 1;
+    double least = 1e30;
+    for (int S = 1; S <= 64 && (S == 1 || 2 * n / S >= 128); ++S) {
+        const long rounds = ((long)ntiles * S + ncu - 1) / ncu;
+        const double cost = (double)rounds / S + 5e-5 * ntiles * S;
+        if (cost < least) {
+            least = cost;
+            best = S;
+        }
+    }
+    return best;
 }
 size_t h_gram_part_bytes(int ntiles, int slices) {
     return (size_t)ntiles * slices * 2 * HG_TILE * HG_TILE * 8;

@@ -265,16 +265,34 @@ void launch_dense_matvec(hipStream_t st, int prec, const void* G, int P, long ld
 
 // holo.hip: complex-parameter (holomorphic) RBM, complex FP64 (double2)
 int h_max_hidden();
-void launch_h_tables(hipStream_t st, int N, int M, const double2* p, double2* T, double2* K);
+// tables of the complex model (holo.hip): site-major T = tanh(2 W) and W [N][M],
+// hidden-major Tj [M][N], site factors K [N][2]
+struct HTab {
+    double2 *T, *W, *Tj, *K;
+};
+void launch_h_tables(hipStream_t st, int N, int M, const double2* p, const HTab& h);
 // tanh(theta) of `rows` configurations into t [rows][M] (and t2 with row stride t2_stride)
-void launch_h_theta(hipStream_t st, int N, int M, const double2* p, const int8_t* s, long rows,
-                    double2* t, double2* t2, long t2_stride);
-void launch_h_log_psi(hipStream_t st, int N, int M, const double2* p, const int8_t* s, long n,
-                      double2* out);
-void launch_h_sample(hipStream_t st, int N, int M, const double2* T, const double2* K,
-                     const SampleArgs& a, const double2* tch);
-void launch_h_eloc(hipStream_t st, int N, int M, const double2* T, const double2* K,
-                   const HamDev& H, const int8_t* s, const double2* tact, long n, double2* out);
+void launch_h_theta(hipStream_t st, int N, int M, const double2* p, const HTab& h, const int8_t* s,
+                    long rows, double2* t, double2* t2, long t2_stride);
+void launch_h_log_psi(hipStream_t st, int N, int M, const double2* p, const HTab& h,
+                      const int8_t* s, long n, double2* out);
+// discard unrecorded segments of K proposals, then `record` recorded ones, with the
+// activations of the chains (t, in and out) and of the records
+struct HSampleArgs {
+    int C, K, discard, record;
+    uint64_t seed, prop_base;
+    int8_t* s;              // [C][N] chains (in/out)
+    double2* t;             // [C][M] their tanh(theta) (in/out)
+    int8_t* rec;            // [C][record][N]
+    double2* rec_t;         // [C][record][M]
+    uint8_t* acc_log;       // [C][log_stride] accept flags of the recorded proposals, or null
+    long log_stride;
+    uint32_t* acc_count;    // [C] accepted recorded proposals (written when record > 0)
+};
+void launch_h_sample(hipStream_t st, int N, int M, const double2* p, const HTab& h,
+                     const HSampleArgs& a);
+void launch_h_eloc(hipStream_t st, int N, int M, const HTab& h, const HamDev& H, const int8_t* s,
+                   const double2* tact, long n, double2* out);
 void launch_h_stats(hipStream_t st, const double2* E, long n, double* out);
 // scratch bytes the Jacobian embedding and the force need (slice partials)
 size_t h_slice_bytes(int P);
@@ -290,7 +308,7 @@ void launch_h_force(hipStream_t st, const double* U, long n, long ld, int P, con
                     const double* stats, double* f, double* scratch);
 // A = Re G (G [P][ld]) and B = Im G (G + P ld) from U; tiles from fill_gram_tiles(P);
 // part: h_gram_part_bytes(ntiles, slices) of scratch
-int h_gram_slices(int ntiles, long n);
+int h_gram_slices(int ntiles, long n, int ncu);
 size_t h_gram_part_bytes(int ntiles, int slices);
 void launch_h_gram(hipStream_t st, const double* U, long n, long ld, int P, const int* tiles,
                    int ntiles, int slices, double* part, double* G);
