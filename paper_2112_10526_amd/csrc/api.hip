@@ -103,6 +103,7 @@ struct nqs_ctx {
     Buffers b{};
     long Ns = 0, Bx = 0;
     int ksplit = 1, ndpart = 1, Pld = 0, ntiles = 0;
+    int tri = 0;        // dense product's form; the Jacobian's buffer is its scratch
     size_t lds_limit = 65536;
     int ncu = 256;  // compute units of the device
     long cg_iter = 0;
@@ -372,6 +373,10 @@ void derive(nqs_ctx* c) {
         }
         c->gS = (!c->cplx && (c->symm || c->prec == 0)) ? gram_slices(c->ntiles, c->Ns) : 1;
         c->Ple = round_up(2 * (long)c->P, 128);
+        if (!c->cplx) {
+            const size_t des = c->symm ? 8 : esize(c->prec);
+            c->tri = dense_tri(c->Pd, des, des * (size_t)c->Ns * c->Pld);
+        }
         long nd = (long)d.Ma * d.Na / 256 + 2;
         const long nd2 = c->Bx / 64 + 2, nd3 = (long)c->Pd / 4 + 2;
         if (nd2 > nd) nd = nd2;
@@ -629,7 +634,7 @@ void issue_dense_setup(nqs_ctx* c, double tol, int maxiter, double shift) {
                                (double*)c->b.G, c->b.tiles, c->ntiles, c->gS, c->b.gpart);
         else
             launch_gram(c->stream, c->prec, c->b.O, c->Ns, c->Pld, P, c->b.G, c->b.tiles,
-                        c->ntiles);
+                        c->ntiles, c->tri == 0);
     }
     launch_pack(c->stream, c->d, c->b.grad, c->b.fp, P);
     launch_cg_init(c->stream, P, c->b.fp, c->b.xp, c->b.rp, c->b.pp, c->b.dpart, c->b.sc, tol,
@@ -690,12 +695,12 @@ void issue_cg_iters(nqs_ctx* c, int kind, double shift, int iters, int32_t* host
                                     c->b.App, c->b.dpart, c->b.sc);
                 else
                     launch_dense_matvec(c->stream, c->symm ? 0 : c->prec, c->b.G, c->Pd, c->Pld,
-                                        c->b.pp, c->b.App, c->b.dpart, c->b.sc);
+                                        c->b.pp, c->b.App, c->b.dpart, c->b.sc, c->tri, c->b.O);
             }
             {
                 PROF(NQS_PROF_CGVEC);
                 launch_cg_update(c->stream, c->Pd, c->b.xp, c->b.rp, c->b.pp, c->b.App, c->b.dpart,
-                                 c->cplx ? h_matvec_blocks((int)c->P) : dense_matvec_blocks(c->Pd),
+                                 c->cplx ? h_matvec_blocks((int)c->P) : dense_matvec_blocks(c->Pd, c->tri),
                                  c->b.sc, it + 1 == iters ? host_flag : nullptr);
             }
         }

@@ -216,12 +216,14 @@ __global__ __launch_bounds__(256) void k_jac_rows(Dims d, const int8_t* __restri
     }
 }
 
-// G[p][q] = sum_k A[k][p] A[k][q] for the upper block triangle, mirrored.
+// G[p][q] = sum_k A[k][p] A[k][q] for the upper block triangle, mirrored where the
+// products read the lower one too.
 // Block = 4 waves = a 128 x 128 tile of G; each wave a 64 x 64 quarter as
 // 4 x 4 MFMA tiles of 16 x 16 sharing its operand fragments.
 template <typename R>
 __global__ __launch_bounds__(256) void k_gram(const R* __restrict__ A, long n, long ld, int P,
-                                              R* __restrict__ G, const int* __restrict__ tiles) {
+                                              R* __restrict__ G, const int* __restrict__ tiles,
+                                              bool mirror) {
     const int tp = tiles[2 * blockIdx.x], tq = tiles[2 * blockIdx.x + 1];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int lr = lane & 15, lk = lane >> 4;
@@ -261,7 +263,7 @@ __global__ __launch_bounds__(256) void k_gram(const R* __restrict__ A, long n, l
                 const long p = p0 + a * 16 + acc_row<R>(lk, i), q = q0 + b * 16 + lr;
                 if (p < P && q < P) {
                     G[p * ld + q] = acc[a][b][i];
-                    if (tp != tq) G[q * ld + p] = acc[a][b][i];
+                    if (mirror && tp != tq) G[q * ld + p] = acc[a][b][i];
                 }
             }
 }
@@ -361,7 +363,7 @@ typedef short v8s_g __attribute__((ext_vector_type(8)));
 
 __global__ __launch_bounds__(256) void k_gram_split(const uint32_t* __restrict__ A, long n, long ld,
                                                     int P, float* __restrict__ G,
-                                                    const int* __restrict__ tiles) {
+                                                    const int* __restrict__ tiles, bool mirror) {
     __shared__ __align__(16) uint16_t Ls[2][2][128 * GS_KP];  // [panel p/q][hi/lo][col][sample]
     const int tp = tiles[2 * blockIdx.x], tq = tiles[2 * blockIdx.x + 1];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -441,7 +443,7 @@ __global__ __launch_bounds__(256) void k_gram_split(const uint32_t* __restrict__
                 const long q = base[1] + qr + b * 16 + lr;
                 if (p < P && q < P) {
                     G[p * ld + q] = acc[a][b][i];
-                    if (tp != tq) G[q * ld + p] = acc[a][b][i];
+                    if (mirror && tp != tq) G[q * ld + p] = acc[a][b][i];
                 }
             }
 }
@@ -516,7 +518,187 @@ __global__ __launch_bounds__(256) void k_dense_matvec(const R* __restrict__ G, i
     if (threadIdx.x == 0) dpart[blockIdx.x] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
-int dense_matvec_blocks(int P) { return (P + 4 * DMV_RW - 1) / (4 * DMV_RW); }
+// The same product from the upper triangle of a large G, which halves what an
+// iteration reads: block (segment, panel) takes rows 128 panel .. + 127 against NC x
+// 256 of the columns from 128 panel on.  A lane holds 4 columns of each 256 and a
+// wave 8 rows at a time; every entry right of the panel's diagonal tile also gives
+// its mirror's product, summed per column in registers over the wave's 32 rows and
+// over the four waves through LDS.  The diagonal tile is used whole: its two halves
+// are products of their own (the split BF16 products add lo.hi and hi.lo in the other
+// order there).  Row sums go to rowp[segment][P], column sums to colp[panel][P];
+// k_tri_sum adds them in that order, with the shift, and forms the partials of v . out.
+// Memory bound, 5.1 TB/s of G's upper half at P = 25,024 (FP32): 253 us with the sum,
+// 430 over the whole matrix.
+constexpr int TRI_H = 128;
+template <typename R, int NC>
+__global__ __launch_bounds__(256) void k_tri_matvec(const R* __restrict__ G, int P, long ld,
+                                                    const double* __restrict__ v,
+                                                    double* __restrict__ rowp,
+                                                    double* __restrict__ colp,
+                                                    const CgScalars* __restrict__ sc) {
+    constexpr int W = 256 * NC;
+    if (sc->done) return;
+    __shared__ __align__(16) double vs[W];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r0 = blockIdx.y * TRI_H, q0 = r0 + blockIdx.x * W;
+    if (q0 >= P) return;
+    for (int i = threadIdx.x; i < W; i += 256) vs[i] = q0 + i < P ? v[q0 + i] : 0.0;
+    __syncthreads();
+    double cs[NC][4];
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) cs[c][e] = 0.0;
+    for (int g = 0; g < 4; ++g) {
+        const int p0 = r0 + 32 * wave + 8 * g;
+        if (p0 >= P) break;
+        double rs[8], x[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            rs[r] = 0.0;
+            x[r] = p0 + r < P ? v[p0 + r] : 0.0;
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const int qc = q0 + 256 * c;
+            if (qc >= P) break;
+            const bool ragged = qc + 256 > P;  // (entries past P are stored as anything)
+            const long q = min((long)qc + 4 * lane, ld - 4);
+            const double2 v01 = *(const double2*)&vs[256 * c + 4 * lane];
+            const double2 v23 = *(const double2*)&vs[256 * c + 4 * lane + 2];
+            R t[8][4];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const R* a = G + (long)min(p0 + r, P - 1) * ld + q;
+                if constexpr (sizeof(R) == 4) {
+                    const float4 f = *(const float4*)a;
+                    t[r][0] = f.x; t[r][1] = f.y; t[r][2] = f.z; t[r][3] = f.w;
+                } else {
+                    const double2 f = *(const double2*)a, h = *(const double2*)(a + 2);
+                    t[r][0] = f.x; t[r][1] = f.y; t[r][2] = h.x; t[r][3] = h.y;
+                }
+            }
+            if (ragged) {
+#pragma unroll
+                for (int r = 0; r < 8; ++r)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (qc + 4 * lane + e >= P) t[r][e] = R(0);
+            }
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const double g0 = t[r][0], g1 = t[r][1], g2 = t[r][2], g3 = t[r][3];
+                rs[r] += (g0 * v01.x + g1 * v01.y) + (g2 * v23.x + g3 * v23.y);
+                cs[c][0] += g0 * x[r];
+                cs[c][1] += g1 * x[r];
+                cs[c][2] += g2 * x[r];
+                cs[c][3] += g3 * x[r];
+            }
+        }
+        // row r's sum to the lanes with lane % 8 == r: halve the rows held by
+        // exchanges over three lane bits, then add over the other three
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+            const bool up = (lane >> m) & 1;
+#pragma unroll
+            for (int i = 0; i < (4 >> m); ++i) {
+                const double keep = up ? rs[2 * i + 1] : rs[2 * i];
+                const double send = up ? rs[2 * i] : rs[2 * i + 1];
+                rs[i] = keep + __shfl_xor(send, 1 << m);
+            }
+        }
+        rs[0] += __shfl_xor(rs[0], 8);
+        rs[0] += __shfl_xor(rs[0], 16);
+        rs[0] += __shfl_xor(rs[0], 32);
+        if (lane < 8 && p0 + lane < P) rowp[(size_t)blockIdx.x * P + p0 + lane] = rs[0];
+    }
+    __syncthreads();
+    for (int w = 0; w < 4; ++w) {
+        if (wave == w) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    double& o = vs[256 * c + 4 * lane + e];
+                    o = w ? o + cs[c][e] : cs[c][e];
+                }
+        }
+        __syncthreads();
+    }
+    for (int i = threadIdx.x; i < W; i += 256) {
+        const int q = q0 + i;
+        if (q >= r0 + TRI_H && q < P) colp[(size_t)blockIdx.y * P + q] = vs[i];
+    }
+}
+
+__global__ __launch_bounds__(256) void k_tri_sum(const double* __restrict__ rowp,
+                                                 const double* __restrict__ colp, int P, int W,
+                                                 const double* __restrict__ v,
+                                                 double* __restrict__ out,
+                                                 double* __restrict__ dpart,
+                                                 const CgScalars* __restrict__ sc) {
+    if (sc->done) return;
+    __shared__ double ws[4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int p = blockIdx.x * 64 + lane, pc = min(p, P - 1);
+    const int panel = blockIdx.x * 64 / TRI_H;  // (its segments and the panels above it)
+    const int ns = (P - panel * TRI_H + W - 1) / W, n = ns + panel;
+    const int b0 = wave * n / 4, b1 = (wave + 1) * n / 4;
+    double a = 0.0;
+    for (int q = b0; q < b1; q += 8) {
+        double x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int e = min(q + u, n - 1);
+            x[u] = e < ns ? rowp[(size_t)e * P + pc] : colp[(size_t)(e - ns) * P + pc];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (q + u < b1) a += x[u];
+    }
+    ws[wave][lane] = a;
+    __syncthreads();
+    if (wave == 0) {
+        const double o = ((ws[0][lane] + ws[1][lane]) + (ws[2][lane] + ws[3][lane])) +
+                         sc->shift * v[pc];
+        if (p < P) out[p] = o;
+        const double dot = wave_sum(p < P ? o * v[pc] : 0.0);
+        if (lane == 0) dpart[blockIdx.x] = dot;
+    }
+}
+
+// Columns per block of the triangle product in units of 256, or 0 for the product
+// over all of G: the triangle form where G (entries of `elem` bytes) is more than the
+// XCDs' L2s hold together, 32 MiB.  FP32, product and sum against the whole product:
+// P = 2,143 (18 MB) 12.2 against 9.6 us, 3,320 (44 MB) 14.2 against 19.4, 16,704 118
+// against 200, 25,024 253 against 430.  512 columns from 20,480 on, where that leaves
+// enough blocks (25,024: 253 us, 258 with 256; 16,704: 122, 118).  `scratch` bytes must
+// hold the row and column partials.
+int dense_tri(int P, size_t elem, size_t scratch) {
+    if (elem * P * P <= (size_t)32 << 20) return 0;
+    const int nc = P < 20480 ? 1 : 2;
+    const size_t rows = (size_t)(P + 256 * nc - 1) / (256 * nc) + (P + TRI_H - 1) / TRI_H;
+    return 8 * rows * P <= scratch ? nc : 0;
+}
+int dense_matvec_blocks(int P, int tri) {
+    return tri ? (P + 63) / 64 : (P + 4 * DMV_RW - 1) / (4 * DMV_RW);
+}
+template <typename R, int NC>
+static void tri_matvec(hipStream_t st, const R* G, int P, long ld, const double* v, double* out,
+                       double* dpart, const CgScalars* sc, double* scratch) {
+    const int ns = (P + 256 * NC - 1) / (256 * NC), np = (P + TRI_H - 1) / TRI_H;
+    double* colp = scratch + (size_t)ns * P;
+    k_tri_matvec<R, NC><<<dim3(ns, np), 256, 0, st>>>(G, P, ld, v, scratch, colp, sc);
+    k_tri_sum<<<(P + 63) / 64, 256, 0, st>>>(scratch, colp, P, 256 * NC, v, out, dpart, sc);
+}
+template <typename R>
+static void dense_matvec(hipStream_t st, const R* G, int P, long ld, const double* v, double* out,
+                         double* dpart, const CgScalars* sc, int tri, double* scratch) {
+    if (tri == 1) tri_matvec<R, 1>(st, G, P, ld, v, out, dpart, sc, scratch);
+    else if (tri == 2) tri_matvec<R, 2>(st, G, P, ld, v, out, dpart, sc, scratch);
+    else
+        k_dense_matvec<R><<<dense_matvec_blocks(P, 0), 256, 0, st>>>(G, P, ld, v, out, dpart, sc);
+}
 
 // ---------------------------------------------------------------------------
 // rows per block: long enough to pay for finding the columns (64), shorter where
@@ -624,7 +806,7 @@ size_t gram_part_bytes(int ntiles, int slices) {
 void launch_gram_sliced(hipStream_t st, const double* A, long n, long ld, int P, double* G,
                         const int* tiles, int ntiles, int slices, double* part) {
     if (slices <= 1 || !part) {
-        k_gram<double><<<ntiles, 256, 0, st>>>(A, n, ld, P, G, tiles);
+        k_gram<double><<<ntiles, 256, 0, st>>>(A, n, ld, P, G, tiles, true);
         return;
     }
     long rps = (n + slices - 1) / slices;
@@ -633,21 +815,18 @@ void launch_gram_sliced(hipStream_t st, const double* A, long n, long ld, int P,
     k_gram_fin<<<(unsigned)(ntiles * 256), 256, 0, st>>>(part, ntiles, slices, tiles, P, ld, G);
 }
 void launch_gram(hipStream_t st, int prec, const void* A, long n, long ld, int P, void* G,
-                 const int* tiles, int ntiles) {
-    if (prec == 0)
-        k_gram<double><<<ntiles, 256, 0, st>>>((const double*)A, n, ld, P, (double*)G, tiles);
-    else if (prec == 1)
-        k_gram<float><<<ntiles, 256, 0, st>>>((const float*)A, n, ld, P, (float*)G, tiles);
+                 const int* tiles, int ntiles, bool mirror) {
+    if (prec == 1)
+        k_gram<float><<<ntiles, 256, 0, st>>>((const float*)A, n, ld, P, (float*)G, tiles, mirror);
     else  // (split pairs from the centring; ld a multiple of 128: panel loads stay in their row)
-        k_gram_split<<<ntiles, 256, 0, st>>>((const uint32_t*)A, n, ld, P, (float*)G, tiles);
+        k_gram_split<<<ntiles, 256, 0, st>>>((const uint32_t*)A, n, ld, P, (float*)G, tiles, mirror);
 }
 void launch_dense_matvec(hipStream_t st, int prec, const void* G, int P, long ld, const double* v,
-                         double* out, double* dpart, CgScalars* sc) {
-    const int nb = dense_matvec_blocks(P);
+                         double* out, double* dpart, const CgScalars* sc, int tri, void* scratch) {
     if (prec == 0)
-        k_dense_matvec<double><<<nb, 256, 0, st>>>((const double*)G, P, ld, v, out, dpart, sc);
+        dense_matvec(st, (const double*)G, P, ld, v, out, dpart, sc, tri, (double*)scratch);
     else
-        k_dense_matvec<float><<<nb, 256, 0, st>>>((const float*)G, P, ld, v, out, dpart, sc);
+        dense_matvec(st, (const float*)G, P, ld, v, out, dpart, sc, tri, (double*)scratch);
 }
 
 }  // namespace nqs
