@@ -104,7 +104,6 @@ struct nqs_ctx {
     long Ns = 0, Bx = 0;
     int ksplit = 1, ndpart = 1, Pld = 0, ntiles = 0;
     int tri = 0;        // dense product's form; the Jacobian's buffer is its scratch
-    size_t lds_limit = 65536;
     int ncu = 256;  // compute units of the device
     long cg_iter = 0;
     double cg_tol = 1e-6;
@@ -543,7 +542,7 @@ void issue_energy_grad(nqs_ctx* c) {
     {
         PROF(NQS_PROF_ELOC);
         launch_eloc(c->stream, c->d, c->prec, c->b.tab, ham_dev(c), c->b.samples, c->b.tsm, n,
-                    c->b.eloc, c->lds_limit);
+                    c->b.eloc);
     }
     {
         PROF(NQS_PROF_STATS);
@@ -1303,10 +1302,6 @@ int nqs_create(nqs_ctx** out, int device, void* hip_stream) {
     nqs_ctx* c = new nqs_ctx();
     c->device = device;
     c->stream = (hipStream_t)hip_stream;
-    int lds = 0;
-    if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) == hipSuccess &&
-        lds > 0)
-        c->lds_limit = (size_t)lds;
     int ncu = 0;
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess &&
         ncu > 0)
@@ -1793,8 +1788,7 @@ int nqs_local_energy(nqs_ctx* c, const int8_t* s, int64_t n, double* eloc_out) {
         const long m = (long)((n - k0) < c->Bx ? (n - k0) : c->Bx);
         const int8_t* sk = s + (size_t)k0 * c->N;
         launch_theta(c->stream, c->d, c->prec, c->b.tab, sk, (int)m, c->b.tx, nullptr, 0);
-        launch_eloc(c->stream, c->d, c->prec, c->b.tab, ham_dev(c), sk, c->b.tx, m, eloc_out + k0,
-                    c->lds_limit);
+        launch_eloc(c->stream, c->d, c->prec, c->b.tab, ham_dev(c), sk, c->b.tx, m, eloc_out + k0);
     }
     return last_launch(c);
 }
@@ -1817,7 +1811,7 @@ int nqs_local_energy_noalloc(nqs_ctx* c, const int8_t* s, int64_t n, double* elo
     // (each sample's result does not depend on how the batch is cut)
     launch_theta(c->stream, c->d, c->prec, c->b.tab, s, (int)n, c->scratch_dev, nullptr, 0);
     launch_eloc(c->stream, c->d, c->prec, c->b.tab, ham_dev(c), s, c->scratch_dev, (long)n,
-                eloc_out, c->lds_limit);
+                eloc_out);
     return last_launch(c);
 }
 

@@ -8,18 +8,24 @@
 // with tanh(theta) of each sample taken from the activation rows written by
 // the theta contraction.
 //
-// Layout: a block of 4 waves handles 4 SB samples; lanes run over sites (TFIM)
-// or bonds (Heisenberg), up to ICH chunks of 64 per pass.  The hidden-major
-// table T = tanh(2W) is staged in LDS JC hidden units at a time and shared by
-// the block's samples; each sample's tanh(theta_j) is a wave-uniform operand,
-// loaded for the whole chunk into the lanes (lane l: hidden unit j0 + l) and
-// read out with v_readlane.
+// Layout: a wave handles SB samples and lanes run over sites (TFIM) or bonds
+// (Heisenberg), ICH chunks of 64 at a time: an item group.  The 4 waves of a block
+// are IW item groups of each of 4 / IW sample groups; with more item groups than IW,
+// each wave takes every IW-th.  The table T = tanh(2W) is staged in LDS JC hidden
+// units at a time and shared by the block, JU hidden units of a site together (one
+// 16-byte read); the samples' tanh(theta_j) are wave-uniform and come through the
+// scalar cache, JU at a time.
+// Bound by the vector ALU: a factor is three operations in this order (the sign times
+// the activation, the fused multiply-add, the product), so what a hidden unit costs
+// besides is spread over SB samples and ICH chunks, and the waves of a compute unit
+// come from item groups too.  16,384 samples, with theta: Heisenberg 16x16, 1,024
+// hidden units, FP32: 999 us (1,500 with one wave over all bonds of 8 samples and
+// activations read out of the lanes; its operations alone take 730); TFIM 10x10, 200
+// hidden units, FP64: 114 us (125), 16x16, 256 hidden units: 313 us (437).
 #include "kernels.h"
 
 namespace nqs {
 
-constexpr int SB = 8;         // samples per wave
-constexpr int ICH = 2;        // site / bond chunks of 64 per pass
 constexpr int LOGCHUNK = 64;  // FP32: fold partial products into logs this often
 
 template <typename R>
@@ -28,130 +34,142 @@ __device__ __forceinline__ double ratio_from(R prod, R logacc, R kfac) {
     else return (double)__expf(kfac + logacc + __logf(prod));
 }
 
-// Stage table rows [j0, j0 + jn) (all Nw columns) into LDS.
+template <typename R> struct Quad;  // 16 bytes: JU hidden units
+template <> struct Quad<float> {
+    float v[4];
+};
+template <> struct Quad<double> {
+    double v[2];
+};
+
+// Stage table rows [j0, j0 + jn) (all Nw columns, jn a multiple of JU) into LDS as
+// [jn / JU][Nw][JU].
 template <typename R>
 __device__ __forceinline__ void stage_rows(R* __restrict__ dst, const R* __restrict__ Tj, int j0,
                                            int jn, int Nw) {
-    const int total = jn * Nw;
+    constexpr int JU = 16 / sizeof(R), U = sizeof(R) == 4 ? 2 : 4;
+    const int total = jn / JU * Nw;
     const R* src = Tj + (size_t)j0 * Nw;
-    for (int base = 0; base < total; base += 256 * 8) {
-        R v[8];
+    for (int base = 0; base < total; base += 256 * U) {
+        Quad<R> q[U];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int e = base + u * 256 + threadIdx.x;
-            v[u] = e < total ? src[e] : (R)0;
+        for (int u = 0; u < U; ++u) {
+            const int e = min(base + u * 256 + (int)threadIdx.x, total - 1);
+            const int g = e / Nw, i = e - g * Nw;
+#pragma unroll
+            for (int k = 0; k < JU; ++k) q[u].v[k] = src[(size_t)(g * JU + k) * Nw + i];
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < U; ++u) {
             const int e = base + u * 256 + threadIdx.x;
-            if (e < total) dst[e] = v[u];
+            if (e < total) ((Quad<R>*)dst)[e] = q[u];
         }
     }
 }
 
-template <typename R, int KIND>
+template <typename R, int KIND, int SB, int ICH>
 __global__ __launch_bounds__(256) void k_eloc(Dims d, const R* __restrict__ Tj,
                                               const R* __restrict__ Ks, HamDev H,
                                               const int8_t* __restrict__ s,
                                               const R* __restrict__ tact, long n,
-                                              double* __restrict__ out, int JC) {
+                                              double* __restrict__ out, int JC, int IW) {
+    constexpr int JU = 16 / sizeof(R);
     extern __shared__ __align__(16) char lds_raw[];
-    R* Ts = (R*)lds_raw;  // [JC][Nw]
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const long k0 = ((long)blockIdx.x * 4 + wave) * SB;
+    R* Ts = (R*)lds_raw;  // [JC / JU][Nw][JU]
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int iw = wave % IW;
+    const long k0 = ((long)blockIdx.x * (4 / IW) + wave / IW) * SB;
     const int N = d.N, M = d.M, Mw = d.Mw, Nw = d.Nw;
     const int n_items = KIND == 0 ? N : H.n_bonds;
     long kr[SB];
 #pragma unroll
-    for (int r = 0; r < SB; ++r) kr[r] = (k0 + r < n) ? k0 + r : (k0 < n ? k0 : 0);
-    double acc[SB], diag[SB];
+    for (int r = 0; r < SB; ++r) kr[r] = min(k0 + r, n - 1);
+    double acc[SB];
 #pragma unroll
-    for (int r = 0; r < SB; ++r) { acc[r] = 0.0; diag[r] = 0.0; }
+    for (int r = 0; r < SB; ++r) acc[r] = 0.0;
 
-    for (int g0 = 0; g0 < n_items; g0 += 64 * ICH) {
+    for (int gb = 0; gb < n_items; gb += 64 * ICH * IW) {
+        const int g0 = gb + 64 * ICH * iw;  // (past the items: staging only)
         int ia[ICH], ib[ICH];
         R sa[ICH][SB], prod[ICH][SB], lacc[ICH][SB];
 #pragma unroll
         for (int c = 0; c < ICH; ++c) {
             const int it = g0 + 64 * c + lane;
             const bool valid = it < n_items;
-            if (KIND == 0) {
-                ia[c] = valid ? it : 0;
-                ib[c] = 0;
-            } else {
-                ia[c] = valid ? H.bonds[2 * it] : 0;
-                ib[c] = valid ? H.bonds[2 * it + 1] : 0;
-            }
+            ia[c] = KIND == 0 ? (valid ? it : 0) : (valid ? H.bonds[2 * it] : 0);
+            ib[c] = KIND == 0 ? 0 : (valid ? H.bonds[2 * it + 1] : 0);
 #pragma unroll
             for (int r = 0; r < SB; ++r) {
                 const int xa = s[kr[r] * N + ia[c]];
-                sa[c][r] = valid ? (R)xa : (R)0;
-                if (KIND == 1 && valid) diag[r] += (double)(xa * s[kr[r] * N + ib[c]]);
+                sa[c][r] = (R)xa;
+                if (KIND == 1) {
+                    const int x = xa * s[kr[r] * N + ib[c]];
+                    if (valid) acc[r] += H.J * (double)x;
+                }
                 prod[c][r] = (R)1;
                 lacc[c][r] = (R)0;
             }
         }
         for (int j0 = 0; j0 < M; j0 += JC) {
-            const int jn = min(JC, M - j0);
-            // the chunk's activations of the wave's samples, lane l holding hidden
-            // unit j0 + l (JC <= 64), loaded ahead of the staging; the loop takes
-            // each as a wave-uniform value with v_readlane
-            R tv[SB];
-#pragma unroll
-            for (int r = 0; r < SB; ++r) tv[r] = tact[kr[r] * Mw + j0 + min(lane, jn - 1)];
+            // (rows M .. Mw - 1 of the table and of the activations are zero: factors 1)
+            const int jn = min(JC, (M - j0 + JU - 1) / JU * JU);
             __syncthreads();
             stage_rows<R>(Ts, Tj, j0, jn, Nw);
             __syncthreads();
-            if (k0 < n) {
-                // the table entries of hidden unit jl + 1 are read while unit jl's
-                // products are formed (the last unit's again at the end: the reads
-                // stay unconditional)
-                R na[ICH], nb[ICH];
+            if (k0 >= n || g0 >= n_items) continue;
+            // the table entries and activations of the next JU hidden units are read
+            // while these ones' products are formed (the last ones' again at the end:
+            // the reads stay unconditional)
+            Quad<R> na[ICH], nb[ICH], nt[SB];
+            auto fetch = [&](int jl) {
+                const Quad<R>* row = (const Quad<R>*)Ts + jl / JU * Nw;
 #pragma unroll
                 for (int c = 0; c < ICH; ++c) {
-                    na[c] = Ts[ia[c]];
-                    nb[c] = KIND == 1 ? Ts[ib[c]] : (R)0;
+                    na[c] = row[ia[c]];
+                    if (KIND == 1) nb[c] = row[ib[c]];
                 }
-                for (int jl = 0; jl < jn; ++jl) {
-                    R tj[SB];
 #pragma unroll
-                    for (int r = 0; r < SB; ++r) tj[r] = readlane(tv[r], jl);
-                    R ca[ICH], cb[ICH];
+                for (int r = 0; r < SB; ++r) nt[r] = *(const Quad<R>*)(tact + kr[r] * Mw + j0 + jl);
+            };
+            fetch(0);
+            for (int jl = 0; jl < jn; jl += JU) {
+                Quad<R> ca[ICH], cb[ICH], ct[SB];
+#pragma unroll
+                for (int c = 0; c < ICH; ++c) {
+                    ca[c] = na[c];
+                    if (KIND == 1) cb[c] = nb[c];
+                }
+#pragma unroll
+                for (int r = 0; r < SB; ++r) ct[r] = nt[r];
+                fetch(min(jl + JU, jn - JU));
+#pragma unroll
+                for (int u = 0; u < JU; ++u)
 #pragma unroll
                     for (int c = 0; c < ICH; ++c) {
-                        ca[c] = na[c];
-                        cb[c] = nb[c];
-                    }
-                    const R* nrow = Ts + min(jl + 1, jn - 1) * Nw;
-#pragma unroll
-                    for (int c = 0; c < ICH; ++c) {
-                        na[c] = nrow[ia[c]];
-                        if (KIND == 1) nb[c] = nrow[ib[c]];
-                    }
-#pragma unroll
-                    for (int c = 0; c < ICH; ++c) {
-                        if (g0 + 64 * c >= n_items) continue;
                         if (KIND == 0) {
-                            const R Tv = ca[c];
+                            const R Tv = ca[c].v[u];
 #pragma unroll
-                            for (int r = 0; r < SB; ++r) prod[c][r] *= (R)1 - sa[c][r] * tj[r] * Tv;
+                            for (int r = 0; r < SB; ++r)
+                                prod[c][r] *= (R)1 - sa[c][r] * ct[r].v[u] * Tv;
                         } else {
-                            const R ta = ca[c], tb = cb[c];
+                            const R ta = ca[c].v[u], tb = cb[c].v[u];
                             const R TT = (R)1 - ta * tb, Td = ta - tb;
 #pragma unroll
-                            for (int r = 0; r < SB; ++r) prod[c][r] *= TT - sa[c][r] * tj[r] * Td;
+                            for (int r = 0; r < SB; ++r)
+                                prod[c][r] *= TT - sa[c][r] * ct[r].v[u] * Td;
                         }
                     }
-                    if constexpr (sizeof(R) == 4) {
-                        if (((j0 + jl + 1) % LOGCHUNK) == 0) {
+                if constexpr (sizeof(R) == 4) {
+                    const int j = j0 + jl + JU;
+                    if (j % LOGCHUNK == 0 && j <= M) {
 #pragma unroll
-                            for (int c = 0; c < ICH; ++c)
+                        for (int c = 0; c < ICH; ++c)
 #pragma unroll
-                                for (int r = 0; r < SB; ++r) {
-                                    lacc[c][r] += __logf(prod[c][r]);
-                                    prod[c][r] = (R)1;
-                                }
-                        }
+                            for (int r = 0; r < SB; ++r) {
+                                lacc[c][r] += __logf(prod[c][r]);
+                                prod[c][r] = (R)1;
+                            }
                     }
                 }
             }
@@ -165,7 +183,7 @@ __global__ __launch_bounds__(256) void k_eloc(Dims d, const R* __restrict__ Tj,
 #pragma unroll
                 for (int r = 0; r < SB; ++r) {
                     const R kf = Ks[2 * ia[c] + (sa[c][r] < 0)];
-                    acc[r] += ratio_from<R>(prod[c][r], lacc[c][r], kf);
+                    acc[r] -= H.h * ratio_from<R>(prod[c][r], lacc[c][r], kf);
                 }
             } else {
                 double elem = 2.0 * H.J;
@@ -183,48 +201,67 @@ __global__ __launch_bounds__(256) void k_eloc(Dims d, const R* __restrict__ Tj,
             }
         }
     }
-    if (k0 >= n) return;
     if (KIND == 0) {
-        for (int b = lane; b < H.n_bonds; b += 64) {
+        for (int b = 64 * iw + lane; b < H.n_bonds; b += 64 * IW) {
             const int a0 = H.bonds[2 * b], b0 = H.bonds[2 * b + 1];
 #pragma unroll
-            for (int r = 0; r < SB; ++r) diag[r] += (double)(s[kr[r] * N + a0] * s[kr[r] * N + b0]);
+            for (int r = 0; r < SB; ++r)
+                acc[r] += H.J * (double)(s[kr[r] * N + a0] * s[kr[r] * N + b0]);
         }
     }
+    __syncthreads();
+    double* es = (double*)lds_raw;  // [4 waves][SB]
 #pragma unroll
     for (int r = 0; r < SB; ++r) {
-        const double e = KIND == 0 ? H.J * wave_sum(diag[r]) - H.h * wave_sum(acc[r])
-                                   : H.J * wave_sum(diag[r]) + wave_sum(acc[r]);
-        if (lane == 0 && k0 + r < n) out[k0 + r] = e;
+        const double e = wave_sum(acc[r]);
+        if (lane == 0) es[wave * SB + r] = e;
+    }
+    __syncthreads();
+    if (iw == 0 && lane < SB && k0 + lane < n) {
+        double e = es[wave * SB + lane];
+        for (int w = 1; w < IW; ++w) e += es[(wave + w) * SB + lane];
+        out[k0 + lane] = e;
     }
 }
 
-template <typename R, int KIND>
+template <typename R, int KIND, int SB, int ICH>
 static void launch_k(hipStream_t st, const Dims& d, const Tables& t, const HamDev& H,
-                     const int8_t* s, const void* tact, long n, double* out, size_t lds_limit) {
-    const size_t es = sizeof(R);
-    // hidden rows of the table staged per chunk: as many as fit (down to one row,
-    // for the largest lattices)
+                     const int8_t* s, const void* tact, long n, double* out, int IW) {
+    constexpr int JU = 16 / sizeof(R);
+    // hidden rows of the table staged per chunk: at most 32 KiB, so that five blocks
+    // fit a compute unit (Heisenberg 16x16: 999 us, 1,186 with 64 KiB); at least JU,
+    // which for the most sites, 4,096, are 64 KiB
     int JC = 64;
-    while (JC > 1 && (size_t)JC * d.Nw * es > lds_limit) JC /= 2;
-    const size_t lds = (size_t)JC * d.Nw * es;
-    if (lds > 65536)
-        (void)hipFuncSetAttribute((const void*)k_eloc<R, KIND>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    const int nb = (int)((n + 4 * SB - 1) / (4 * SB));
-    k_eloc<R, KIND><<<nb, 256, lds, st>>>(d, (const R*)t.Tj, (const R*)t.Ks, H, s, (const R*)tact,
-                                          n, out, JC);
+    while (JC > JU && (size_t)JC * d.Nw * sizeof(R) > 32768) JC /= 2;
+    const size_t rows = (size_t)JC * d.Nw * sizeof(R), sums = 8 * 4 * SB;
+    const int per = 4 / IW * SB;
+    k_eloc<R, KIND, SB, ICH><<<(unsigned)((n + per - 1) / per), 256, rows > sums ? rows : sums, st>>>(
+        d, (const R*)t.Tj, (const R*)t.Ks, H, s, (const R*)tact, n, out, JC, IW);
+}
+
+// Samples and chunks per wave.  One chunk where the items fit it (7x7 TFIM, FP64: 44
+// us, 53 with room for two); eight samples only where the waves still fill every SIMD
+// eight deep (Heisenberg 16x16, FP32: 16,384 samples 999 us, 1,075 with four; 8,192
+// samples 605, 582 with four; 10x10, 2,000 samples 57, 40 with four).
+template <typename R, int KIND>
+static void launch_items(hipStream_t st, const Dims& d, const Tables& t, const HamDev& H,
+                         const int8_t* s, const void* tact, long n, double* out) {
+    const int items = KIND == 0 ? d.N : H.n_bonds;
+    const int groups = (items + 127) / 128, IW = groups <= 1 ? 1 : groups == 2 ? 2 : 4;
+    if (items <= 64) launch_k<R, KIND, 4, 1>(st, d, t, H, s, tact, n, out, 1);
+    else if (n / 8 * IW >= 8192) launch_k<R, KIND, 8, 2>(st, d, t, H, s, tact, n, out, IW);
+    else launch_k<R, KIND, 4, 2>(st, d, t, H, s, tact, n, out, IW);
 }
 
 void launch_eloc(hipStream_t st, const Dims& d, int prec, const Tables& t, const HamDev& H,
-                 const int8_t* s, const void* tact, long n, double* out, size_t lds_limit) {
+                 const int8_t* s, const void* tact, long n, double* out) {
     if (n <= 0) return;
     if (prec == 0) {
-        if (H.kind == 0) launch_k<double, 0>(st, d, t, H, s, tact, n, out, lds_limit);
-        else launch_k<double, 1>(st, d, t, H, s, tact, n, out, lds_limit);
+        if (H.kind == 0) launch_items<double, 0>(st, d, t, H, s, tact, n, out);
+        else launch_items<double, 1>(st, d, t, H, s, tact, n, out);
     } else {
-        if (H.kind == 0) launch_k<float, 0>(st, d, t, H, s, tact, n, out, lds_limit);
-        else launch_k<float, 1>(st, d, t, H, s, tact, n, out, lds_limit);
+        if (H.kind == 0) launch_items<float, 0>(st, d, t, H, s, tact, n, out);
+        else launch_items<float, 1>(st, d, t, H, s, tact, n, out);
     }
 }
 

@@ -96,7 +96,7 @@ struct HamDev {
     double J, h;
 };
 void launch_eloc(hipStream_t st, const Dims& d, int prec, const Tables& t, const HamDev& H,
-                 const int8_t* s, const void* tact, long n, double* out, size_t lds_limit);
+                 const int8_t* s, const void* tact, long n, double* out);
 
 // sr.hip
 void launch_stats(hipStream_t st, const double* E, long n, double* out3);
