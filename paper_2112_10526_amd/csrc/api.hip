@@ -353,6 +353,8 @@ void derive(nqs_ctx* c) {
     d.Kb = round_up(d.Na, 32);
     d.Kq = round_up(d.Na, 128);
     d.QM = (c->M + 63) / 64;
+    d.lpc = sampler_lanes(d.QM, c->prec, c->C);
+    d.Q = 64 * qmax / d.lpc;
     d.vb = c->vb;
     d.hb = c->hb;
     c->P = (size_t)(c->vb ? c->N : 0) + (c->hb ? c->M : 0) + (size_t)c->M * c->N;

@@ -38,6 +38,7 @@ struct Dims {
     int Kb;       // round_up(Na, 32): K extent of the BF16 theta operand
     int Kq;       // round_up(Na, 128): site extent of the CG operands (whole k-groups)
     int QM;       // ceil(M / 64): hidden units per lane in the sampler
+    int lpc, Q;  // the sampler\'s lanes per chain and hidden units per lane
     int vb, hb;   // visible / hidden bias present
 };
 
@@ -73,16 +74,17 @@ __device__ __forceinline__ double unit53(uint32_t x1, uint32_t x2) {
 
 // ---------------------------------------------------------------------------
 // wave64 reductions with DPP inside rows of 16 lanes, then readlane across
-// the four rows.  Every lane of the wave must be active.
+// the four rows.  Every lane of the wave must be active (every source lane is then
+// valid; the bound control only lets the FP32 move fold into the addition).
 // ---------------------------------------------------------------------------
 template <int CTRL>
 __device__ __forceinline__ float dpp(float v) {
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, false));
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
 }
 template <int CTRL>
 __device__ __forceinline__ double dpp(double v) {
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, false);
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true);
     return __hiloint2double(hi, lo);
 }
 // DPP controls: quad_perm [1,0,3,2] = 0xB1, [2,3,0,1] = 0x4E, row_ror:4 = 0x124,

@@ -10,7 +10,7 @@ namespace nqs {
 
 // Derived per-parameter tables in the compute precision R (double for FP64,
 // float otherwise):
-//   Tt [N][Mw]  tanh(2 W_ji) at [i][j]  (site-major; sampler rows)
+//   Tt [N][Mw]  tanh(2 W_ji) in row i at sampler_pos(j)  (site-major; sampler rows)
 //   Tj [Mw][Nw] tanh(2 W_ji) at [j][i]  (hidden-major; local energies)
 //   Ks [N][2]   site factor K_i(+1), K_i(-1) (FP64) or their logs (FP32)
 //   Wa [Na][Mw] W~^T: W_ji at [i][j], b_j at [N][j] (theta contraction)
@@ -66,7 +66,16 @@ void launch_theta(hipStream_t st, const Dims& d, int prec, const Tables& t, cons
 void launch_log_psi(hipStream_t st, const Dims& d, int prec, const double* Pm, const Tables& t,
                     const int8_t* s, long n, void* out);
 
-// sampler.hip
+// sampler.hip: order of a table row, so that lane l of a chain's `lpc` lanes reads its
+// hidden units l + lpc q (q < Q) in vectors of V
+constexpr __host__ __device__ int sampler_vec(int Q, size_t es) {
+    return Q * es < 16 ? Q : (int)(16 / es);
+}
+__host__ __device__ inline int sampler_pos(int j, int lpc, int V) {
+    const int q = j / lpc, l = j - q * lpc;
+    return q / V * (lpc * V) + l * V + q % V;
+}
+int sampler_lanes(int QM, int prec, int C);  // lanes per chain
 struct SampleArgs {
     int C;                 // chains
     int K;                 // proposals in this launch

@@ -5,8 +5,7 @@
 // Lane l of a chain's L lanes keeps tanh(theta_j) for hidden units j = l + L q
 // in registers for the whole launch, and the chain's configuration sits in
 // LDS.  Random draws are made L at a time: lane l evaluates the Philox block
-// of proposal p0 + l, and proposal p0 + q reads lane q's site/bond and
-// uniform with v_readlane.
+// of proposal p0 + l and leaves its site/bond and uniform in LDS.
 //
 // Single flip of site i (local rule):
 //   psi(s')/psi(s) = K_i(s_i) prod_j f_j,  f_j = 1 - s_i t_j T_ij,
@@ -35,52 +34,89 @@ __device__ __forceinline__ double recip(double x) {
 }
 __device__ __forceinline__ float recip(float x) { return __builtin_amdgcn_rcpf(x); }
 
-// Lanes of chain h of a wave: 64 / CPW consecutive lanes (CPW = 1 or 2 chains per
-// wave).  With two chains per wave one cross-lane reduction and one accept/update
-// sequence serve two proposals; each chain owns whole 16-lane rows, so the row
-// reductions never mix the chains.
-template <int CPW>
-__device__ __forceinline__ int pick(int v, int q, int h) {  // chain h's lane q
-    if constexpr (CPW == 1) return __builtin_amdgcn_readlane(v, q);
-    else {
-        const int v0 = __builtin_amdgcn_readlane(v, q), v1 = __builtin_amdgcn_readlane(v, 32 + q);
-        return h ? v1 : v0;
-    }
+// Sum / product over the chain's lanes, in every lane of the chain: rows of 16 lanes,
+// then pairs of rows, then (one chain per wave) the two halves.  With two chains per
+// wave (64 / CPW consecutive lanes each) one cross-lane reduction and one
+// accept/update sequence serve two proposals.
+__device__ __forceinline__ void swap16(float v, float& a, float& b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_int(v), __float_as_int(v), false, false);
+    a = __int_as_float(r[0]);
+    b = __int_as_float(r[1]);
+}
+__device__ __forceinline__ void swap32(float v, float& a, float& b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_int(v), __float_as_int(v), false, false);
+    a = __int_as_float(r[0]);
+    b = __int_as_float(r[1]);
+}
+__device__ __forceinline__ void swap16(double v, double& a, double& b) {
+    const int lo = __double2loint(v), hi = __double2hiint(v);
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto u = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    a = __hiloint2double(u[0], l[0]);
+    b = __hiloint2double(u[1], l[1]);
+}
+__device__ __forceinline__ void swap32(double v, double& a, double& b) {
+    const int lo = __double2loint(v), hi = __double2hiint(v);
+    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto u = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    a = __hiloint2double(u[0], l[0]);
+    b = __hiloint2double(u[1], l[1]);
 }
 template <int CPW, typename T>
-__device__ __forceinline__ T pick(T v, int q, int h) {
-    if constexpr (CPW == 1) return readlane(v, q);
-    else {
-        const T v0 = readlane(v, q), v1 = readlane(v, 32 + q);
-        return h ? v1 : v0;
+__device__ __forceinline__ T chain_sum(T v) {
+    T a, b;
+    swap16(row16_sum(v), a, b);
+    v = a + b;
+    if constexpr (CPW == 1) {
+        swap32(v, a, b);
+        v = a + b;
     }
-}
-// sum / product over the chain's lanes (rows 4h / CPW ..), fixed order
-template <int CPW, typename T>
-__device__ __forceinline__ T chain_sum(T v, int h) {
-    v = row16_sum(v);
-    if constexpr (CPW == 1) return (readlane(v, 0) + readlane(v, 16)) + (readlane(v, 32) + readlane(v, 48));
-    else {
-        const T s0 = readlane(v, 0) + readlane(v, 16), s1 = readlane(v, 32) + readlane(v, 48);
-        return h ? s1 : s0;
-    }
+    return v;
 }
 template <int CPW, typename T>
-__device__ __forceinline__ T chain_prod(T v, int h) {
-    v = row16_prod(v);
-    if constexpr (CPW == 1) return (readlane(v, 0) * readlane(v, 16)) * (readlane(v, 32) * readlane(v, 48));
-    else {
-        const T s0 = readlane(v, 0) * readlane(v, 16), s1 = readlane(v, 32) * readlane(v, 48);
-        return h ? s1 : s0;
+__device__ __forceinline__ T chain_prod(T v) {
+    T a, b;
+    swap16(row16_prod(v), a, b);
+    v = a * b;
+    if constexpr (CPW == 1) {
+        swap32(v, a, b);
+        v = a * b;
     }
+    return v;
 }
 
+// One proposal's random draw: site(s) and the uniform, or its logarithm (FP32)
+template <typename R> struct alignas(16) Draw;
+template <> struct alignas(16) Draw<float> {
+    int ia, ib;
+    float u, pad;
+};
+template <> struct alignas(16) Draw<double> {
+    int ia, ib;
+    double u;
+};
+template <typename R, int V> struct alignas(V * sizeof(R)) Vec {
+    R v[V];
+};
+
 // QMAX: hidden units per lane at one chain per wave (the row covers 64 QMAX).
+//
+// A proposal is a chain of some hundred dependent operations, and with two waves per
+// SIMD (4,096 chains in pairs) the chain's length and its instructions count alike:
+// the draws go through LDS, two proposals ahead, so that a chain's own site and
+// uniform take one read; its table row comes in 16-byte loads and the spins are read
+// while the proposal before is decided, and corrected if that one flips them; sums
+// cross the rows of 16 lanes with lane swaps.  10x10, 200 hidden
+// units, 100 proposals of 4,096 chains, FP32: 46.6 us (58.7 with the draws read out of
+// the lanes, single-word rows and spins read when needed).
 template <typename R, int QMAX, int RULE, int CPW>
 __global__ __launch_bounds__(256) void k_sample(Dims d, const R* __restrict__ Tt,
                                                 const R* __restrict__ Ks, SampleArgs a) {
     constexpr int LPC = 64 / CPW;  // lanes per chain
     constexpr int Q = QMAX * CPW;  // hidden units per lane
+    constexpr int V = sampler_vec(Q, sizeof(R));
+    typedef Vec<R, V> vec;
+    __shared__ Draw<R> draws[4 * 64];
     extern __shared__ int8_t lds_s[];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int h = lane / LPC, hl = lane % LPC;
@@ -89,6 +125,7 @@ __global__ __launch_bounds__(256) void k_sample(Dims d, const R* __restrict__ Tt
     const int c = c0 + h;
     const int N = d.N, Mw = d.Mw;
     int8_t* s = lds_s + (wave * CPW + h) * round_up(N, 16);
+    Draw<R>* dr = draws + wave * 64 + h * LPC;  // this chain's
     int8_t* sg = a.s + (size_t)c * N;
     for (int i = hl; i < N; i += LPC) s[i] = sg[i];
     __builtin_amdgcn_wave_barrier();
@@ -98,63 +135,58 @@ __global__ __launch_bounds__(256) void k_sample(Dims d, const R* __restrict__ Tt
 #pragma unroll
     for (int q = 0; q < Q; ++q) t[q] = tc[hl + LPC * q];
 
+    // (byte offsets in 32 bits: at most 4,096 rows of 16 KiB)
+    const uint32_t rowb = (uint32_t)Mw * sizeof(R), lofs = hl * V * sizeof(R);
     uint32_t n_acc = 0;
     for (int p0 = 0; p0 < a.K; p0 += LPC) {
         const uint64_t pidx = a.prop_base + (uint64_t)(p0 + hl);
         const uint4 x = philox10(make_uint4((uint32_t)pidx, (uint32_t)(pidx >> 32), (uint32_t)c,
                                             TAG_METROPOLIS), a.seed);
-        int ia_l, ib_l = 0;
-        if (RULE == 0) {
-            ia_l = mulshift(x.x, N);
-        } else {
-            const int k = mulshift(x.x, a.n_bonds);
-            ia_l = a.bonds[2 * k];
-            ib_l = a.bonds[2 * k + 1];
-        }
-        const double u_l = unit53(x.y, x.z);
-        // FP32 path compares logarithms; u = 0 gives -inf and always accepts
-        const float lu_l = sizeof(R) == 8 ? 0.0f : logf((float)u_l);
-        const int np = min(LPC, a.K - p0);
-        // table rows and site factors of the next proposal are loaded one
-        // proposal ahead
-        R Ta[Q], Tb[Q];
-        R ka_n[2], kb_n[2];
         {
-            const int ia0 = pick<CPW>(ia_l, 0, h);
-            const int ib0 = pick<CPW>(ib_l, 0, h);
-#pragma unroll
-            for (int qq = 0; qq < Q; ++qq) {
-                Ta[qq] = Tt[(size_t)ia0 * Mw + hl + LPC * qq];
-                Tb[qq] = RULE == 1 ? Tt[(size_t)ib0 * Mw + hl + LPC * qq] : (R)0;
+            Draw<R> w{};
+            if (RULE == 0) {
+                w.ia = w.ib = mulshift(x.x, N);
+            } else {
+                const int k = mulshift(x.x, a.n_bonds);
+                w.ia = a.bonds[2 * k];
+                w.ib = a.bonds[2 * k + 1];
             }
-            ka_n[0] = Ks[2 * ia0];
-            ka_n[1] = Ks[2 * ia0 + 1];
-            kb_n[0] = RULE == 1 ? Ks[2 * ib0] : (R)0;
-            kb_n[1] = RULE == 1 ? Ks[2 * ib0 + 1] : (R)0;
+            const double u = unit53(x.y, x.z);
+            // FP32 path compares logarithms; u = 0 gives -inf and always accepts
+            w.u = sizeof(R) == 8 ? (R)u : (R)logf((float)u);
+            dr[hl] = w;
         }
+        __builtin_amdgcn_wave_barrier();
+        const int np = min(LPC, a.K - p0);
+        Draw<R> cur = dr[0], nxt = dr[min(1, np - 1)];
+        vec Ta[Q / V], Tb[Q / V];  // the next proposal's table rows and site factors
+        Vec<R, 2> ka_n, kb_n;
+        auto fetch = [&](const Draw<R>& w) {
+            const uint32_t ra = lofs + __umul24(w.ia, rowb), rb = lofs + __umul24(w.ib, rowb);
+#pragma unroll
+            for (int g = 0; g < Q / V; ++g) {
+                constexpr int step = LPC * V * sizeof(R);
+                Ta[g] = *(const vec*)((const char*)Tt + ra + g * step);
+                if (RULE == 1) Tb[g] = *(const vec*)((const char*)Tt + rb + g * step);
+            }
+            ka_n = *(const Vec<R, 2>*)((const char*)Ks + (uint32_t)w.ia * (2 * sizeof(R)));
+            if (RULE == 1)
+                kb_n = *(const Vec<R, 2>*)((const char*)Ks + (uint32_t)w.ib * (2 * sizeof(R)));
+        };
+        fetch(cur);
+        int sa = s[cur.ia], sb = RULE == 1 ? s[cur.ib] : 0;
         for (int q = 0; q < np; ++q) {
-            const int ia = pick<CPW>(ia_l, q, h);
-            const int sa = s[ia];
             R Tv[Q], Tw[Q];
 #pragma unroll
-            for (int qq = 0; qq < Q; ++qq) { Tv[qq] = Ta[qq]; Tw[qq] = Tb[qq]; }
-            const R ka_c[2] = {ka_n[0], ka_n[1]};
-            const R kb_c[2] = {kb_n[0], kb_n[1]};
-            if (q + 1 < np) {
-                const int ian = pick<CPW>(ia_l, q + 1, h);
-                const int ibn = pick<CPW>(ib_l, q + 1, h);
-#pragma unroll
-                for (int qq = 0; qq < Q; ++qq) {
-                    Ta[qq] = Tt[(size_t)ian * Mw + hl + LPC * qq];
-                    if (RULE == 1) Tb[qq] = Tt[(size_t)ibn * Mw + hl + LPC * qq];
-                }
-                ka_n[0] = Ks[2 * ian];
-                ka_n[1] = Ks[2 * ian + 1];
-                if (RULE == 1) {
-                    kb_n[0] = Ks[2 * ibn];
-                    kb_n[1] = Ks[2 * ibn + 1];
-                }
+            for (int qq = 0; qq < Q; ++qq) {
+                Tv[qq] = Ta[qq / V].v[qq % V];
+                Tw[qq] = RULE == 1 ? Tb[qq / V].v[qq % V] : (R)0;
             }
+            const Vec<R, 2> ka_c = ka_n, kb_c = RULE == 1 ? kb_n : ka_n;
+            fetch(nxt);  // (the last proposal's again at the end)
+            int sa_n = s[nxt.ia], sb_n = RULE == 1 ? s[nxt.ib] : 0;
+            const Draw<R> nn = dr[min(q + 2, np - 1)];
+            __builtin_amdgcn_sched_barrier(0);  // (the reads stay ahead of the decision)
             bool accept;
             if (RULE == 0) {
                 R f[Q];
@@ -164,22 +196,21 @@ __global__ __launch_bounds__(256) void k_sample(Dims d, const R* __restrict__ Tt
                     f[qq] = (R)1 - (R)sa * t[qq] * Tv[qq];
                     prod *= f[qq];
                 }
-                const R kf = sa < 0 ? ka_c[1] : ka_c[0];
+                const R kf = sa < 0 ? ka_c.v[1] : ka_c.v[0];
                 if constexpr (sizeof(R) == 8) {
-                    const double r = chain_prod<CPW>(prod, h) * kf;
-                    accept = pick<CPW>(u_l, q, h) < r * r;
+                    const double r = chain_prod<CPW>(prod) * kf;
+                    accept = cur.u < r * r;
                 } else {
-                    const float lr = chain_sum<CPW>(__logf(prod), h) + kf;
-                    accept = pick<CPW>(lu_l, q, h) < 2.0f * lr;
+                    const float lr = chain_sum<CPW>(__logf(prod)) + kf;
+                    accept = cur.u < 2.0f * lr;
                 }
                 if (accept) {
 #pragma unroll
                     for (int qq = 0; qq < Q; ++qq) t[qq] = (t[qq] - (R)sa * Tv[qq]) * recip(f[qq]);
-                    s[ia] = (int8_t)-sa;  // every lane of the chain stores the same value
+                    s[cur.ia] = (int8_t)-sa;  // every lane of the chain stores the same value
+                    if (nxt.ia == cur.ia) sa_n = -sa;
                 }
             } else {
-                const int ib = pick<CPW>(ib_l, q, h);
-                const int sb = s[ib];
                 // the ratio is formed for every chain of the wave (the cross-lane
                 // reduction runs outside divergent code); a bond with equal spins
                 // is the identity move, accepted with ratio 1
@@ -193,28 +224,35 @@ __global__ __launch_bounds__(256) void k_sample(Dims d, const R* __restrict__ Tt
                     g[qq] = TT[qq] - t[qq] * Td[qq];
                     prod *= g[qq];
                 }
-                const R ka = sa < 0 ? ka_c[1] : ka_c[0], kb = sb < 0 ? kb_c[1] : kb_c[0];
+                const R ka = sa < 0 ? ka_c.v[1] : ka_c.v[0], kb = sb < 0 ? kb_c.v[1] : kb_c.v[0];
                 bool take;
                 if constexpr (sizeof(R) == 8) {
-                    const double r = chain_prod<CPW>(prod, h) * ka * kb;
-                    take = pick<CPW>(u_l, q, h) < r * r;
+                    const double r = chain_prod<CPW>(prod) * ka * kb;
+                    take = cur.u < r * r;
                 } else {
-                    const float lr = chain_sum<CPW>(__logf(prod), h) + ka + kb;
-                    take = pick<CPW>(lu_l, q, h) < 2.0f * lr;
+                    const float lr = chain_sum<CPW>(__logf(prod)) + ka + kb;
+                    take = cur.u < 2.0f * lr;
                 }
                 const bool ident = sa == sb;
                 accept = ident || take;
                 if (!ident && take) {
 #pragma unroll
                     for (int qq = 0; qq < Q; ++qq) t[qq] = (t[qq] * TT[qq] - Td[qq]) * recip(g[qq]);
-                    s[ia] = (int8_t)sb;
-                    s[ib] = (int8_t)sa;
+                    s[cur.ia] = (int8_t)sb;
+                    s[cur.ib] = (int8_t)sa;
+                    sa_n = nxt.ia == cur.ia ? sb : nxt.ia == cur.ib ? sa : sa_n;
+                    sb_n = nxt.ib == cur.ia ? sb : nxt.ib == cur.ib ? sa : sb_n;
                 }
             }
             n_acc += accept ? 1u : 0u;
             if (a.acc_log && hl == 0)
                 a.acc_log[(size_t)c * a.log_stride + a.log_offset + p0 + q] = accept ? 1 : 0;
+            cur = nxt;
+            nxt = nn;
+            sa = sa_n;
+            sb = sb_n;
         }
+        __builtin_amdgcn_wave_barrier();
     }
     __builtin_amdgcn_wave_barrier();
     for (int i = hl; i < N; i += LPC) {
@@ -224,13 +262,21 @@ __global__ __launch_bounds__(256) void k_sample(Dims d, const R* __restrict__ Tt
     if (a.acc_count && hl == 0) a.acc_count[c] += n_acc;
 }
 
+// Two chains per wave when the chains pair up and a lane's registers allow (FP32 up to
+// 8 x 2 hidden units per lane, FP64 up to 4 x 2).  FP64 takes one chain per wave below
+// 2,048 chains, where the shorter chain of operations counts and not their number
+// (10x10, 200 hidden units, 4 sweeps: 1,024 chains 171 us, 207 in pairs; 4,096 chains
+// 349, 328 in pairs); in FP32 the grouping fixes the rounding, so it stays.
+int sampler_lanes(int QM, int prec, int C) {
+    const bool pair = prec == 0 ? QM <= 4 && C >= 2048 : QM <= 8;
+    return pair && C % 2 == 0 ? 32 : 64;
+}
+
 template <typename R, int QMAX>
 static void launch_q(hipStream_t st, const Dims& d, int rule, const Tables& t,
                      const SampleArgs& a) {
-    // two chains per wave when the chains pair up and a lane's registers allow
-    // (FP32 up to 8 x 2 hidden units per lane, FP64 up to 4 x 2)
     constexpr bool PAIR = QMAX <= (sizeof(R) == 4 ? 8 : 4);
-    const int cpw = (PAIR && a.C % 2 == 0) ? 2 : 1;
+    const int cpw = 64 / d.lpc;
     const dim3 grid((a.C + 4 * cpw - 1) / (4 * cpw));
     const size_t lds = 4 * cpw * (size_t)round_up(d.N, 16);
     if constexpr (PAIR) {

@@ -57,7 +57,9 @@ __global__ void k_tables(Dims d, const double* __restrict__ Pm, R* __restrict__ 
     Wa[e] = (R)w;
     if (i < d.N) {
         const double t = (j < d.M) ? tanh(2.0 * w) : 0.0;
-        Tt[(size_t)i * d.Mw + j] = (R)t;
+        const int row = d.lpc * d.Q;  // (Mw may be longer)
+        const int pos = j < row ? sampler_pos(j, d.lpc, sampler_vec(d.Q, sizeof(R))) : j;
+        Tt[(size_t)i * d.Mw + pos] = (R)t;
         Tj[(size_t)j * d.Nw + i] = (R)t;
     }
 }
