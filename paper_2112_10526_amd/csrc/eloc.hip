@@ -112,7 +112,7 @@ __global__ __launch_bounds__(256) void k_eloc(Dims d, const R* __restrict__ Tj,
             }
         }
         for (int j0 = 0; j0 < M; j0 += JC) {
-            // (rows M .. Mw - 1 of the table and of the activations are zero: factors 1)
+            // (the table's rows past M are zero, the activations there finite: factors 1)
             const int jn = min(JC, (M - j0 + JU - 1) / JU * JU);
             __syncthreads();
             stage_rows<R>(Ts, Tj, j0, jn, Nw);

@@ -98,9 +98,57 @@ __device__ __forceinline__ double row16_prod1(double f) {
     return mul(f, dpp<0x128>(f));
 }
 
+// Spins i0 .. i0 + 4 W - 1 of the block's rows into LDS (row stride LD bytes),
+// augmented (1 at site N, then 0); eight words per thread loaded together (items past
+// the end repeat the last one).  Rows start at any byte: the words are loaded as they
+// lie (the row's last one from its last four bytes, shifted).
+template <int W>
+__device__ __forceinline__ void stage_spins(int8_t* lds, int LD, const int8_t* __restrict__ s, int N,
+                                            long r0, int nr, int RB, int i0, int tid, int nth) {
+    const int items = RB * W;
+    auto fill = [&](auto word, auto finish) {
+#pragma unroll 1
+        for (int e0 = tid; e0 < items; e0 += TH_ST * nth) {
+            uint32_t v[TH_ST];
+            int at[TH_ST], i[TH_ST];
+#pragma unroll
+            for (int u = 0; u < TH_ST; ++u) {
+                const int e = min(e0 + u * nth, items - 1);
+                const int row = e / W, q = 4 * (e - row * W);
+                at[u] = row * LD + q;
+                i[u] = i0 + q;
+                v[u] = word(s + (r0 + min(row, nr - 1)) * N, i[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < TH_ST; ++u) *(uint32_t*)(lds + at[u]) = finish(v[u], i[u]);
+        }
+    };
+    auto load = [&](const int8_t* p, int i) {
+        uint32_t v;
+        __builtin_memcpy(&v, p + min(i, N - 4), 4);
+        return v;
+    };
+    auto augment = [&](uint32_t v, int i) {
+        return i <= N && N < i + 4 ? v | 1u << (8 * (N - i)) : v;
+    };
+    if (N % 4 == 0)  // (a word is all spins or all constants)
+        fill(load, [&](uint32_t v, int i) { return i < N ? v : (i == N ? 1u : 0u); });
+    else if (N >= 4)
+        fill(load, [&](uint32_t v, int i) {
+            return augment(i < N ? v >> (8 * max(i - (N - 4), 0)) : 0u, i);
+        });
+    else
+        fill([&](const int8_t* p, int i) {
+                uint32_t v = 0;
+                if (i == 0)
+                    for (int q = 0; q < N; ++q) v |= (uint32_t)(uint8_t)p[q] << (8 * q);
+                return v;
+            }, augment);
+}
+
 template <typename R, int G, int RT, int EPI, bool MULTI>
 __global__ __launch_bounds__(EPI ? 512 : 256) void k_theta(
-    Dims d, const int8_t* __restrict__ s, long rows, int words, int RB, const R* __restrict__ Wa,
+    Dims d, const int8_t* __restrict__ s, long rows, int RB, const R* __restrict__ Wa,
     R* __restrict__ dst1, R* __restrict__ dst2, long dst2_stride, const double* __restrict__ av) {
     extern __shared__ __align__(16) int8_t th_lds[];
     typedef typename std::conditional<sizeof(R) == 8, v4d, v4f>::type acc_t;
@@ -113,42 +161,8 @@ __global__ __launch_bounds__(EPI ? 512 : 256) void k_theta(
     const int ng = d.Na / 16;
     const int nch = MULTI ? (ng + G - 1) / G : 1;  // site chunks
     double* red = (double*)(th_lds + (size_t)RB * LD);  // EPI 1: [nw][RB]
-    // spins of chunk c, rows of the block, augmented (1 at site N, then 0); eight
-    // words per thread loaded together (items past the end repeat the last one)
     auto stage = [&](int c) {
-        constexpr int W = 4 * G;
-        const int i0 = 16 * G * c, items = RB * W;
-        auto fill = [&](auto word) {
-#pragma unroll 1
-            for (int e0 = tid; e0 < items; e0 += TH_ST * nth) {
-                uint32_t v[TH_ST];
-                int at[TH_ST];
-#pragma unroll
-                for (int u = 0; u < TH_ST; ++u) {
-                    const int e = min(e0 + u * nth, items - 1);
-                    const int row = e / W, i = 4 * (e - row * W);
-                    at[u] = row * LD + i;
-                    v[u] = word(s + (r0 + min(row, nr - 1)) * d.N, i0 + i);
-                }
-#pragma unroll
-                for (int u = 0; u < TH_ST; ++u) *(uint32_t*)(th_lds + at[u]) = v[u];
-            }
-        };
-        if (words)  // (N is a multiple of 4: a word is all spins or all constants)
-            fill([&](const int8_t* p, int i) {
-                const uint32_t v = *(const uint32_t*)(p + min(i, d.N - 4));
-                return i < d.N ? v : (i == d.N ? 1u : 0u);
-            });
-        else
-            fill([&](const int8_t* p, int i) {
-                uint32_t v = 0;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const uint32_t x = (uint8_t)p[min(i + q, d.N - 1)];
-                    v |= (i + q < d.N ? x : (i + q == d.N ? 1u : 0u)) << (8 * q);
-                }
-                return v;
-            });
+        stage_spins<4 * G>(th_lds, LD, s, d.N, r0, nr, RB, 16 * G * c, tid, nth);
     };
     const int tiles = EPI ? (d.M + 15) / 16 : d.Mw / 16;
     R wf[4 * G];
@@ -282,116 +296,115 @@ __global__ __launch_bounds__(EPI ? 512 : 256) void k_theta(
 
 typedef short v8s __attribute__((ext_vector_type(8)));
 
-// BF16 form: spins are exact in BF16 (+1 = 0x3F80, -1 = 0xBF80).
-__device__ __forceinline__ v8bf spins_bf16(const int8_t* __restrict__ s, int N, int r, int rows,
-                                           int k0) {
-    v8s v;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const int k = k0 + e;
-        short bits = 0;
-        if (r < rows && k <= N) {
-            const int sv = k == N ? 1 : (int)s[(size_t)r * N + k];
-            bits = sv > 0 ? (short)0x3F80 : (short)0xBF80;
-        }
-        v[e] = bits;
-    }
+// BF16 form: eight spins (bytes, 0 past the bias site) as BF16, +1 = 0x3F80,
+// -1 = 0xBF80 (0 comes out as +1: its weights are zero)
+__device__ __forceinline__ v8bf spins_bf16(uint2 b) {
+    uint4 v;
+    v.x = (__builtin_amdgcn_perm(b.x, b.x, 0x010c000cu) & 0x80008000u) | 0x3F803F80u;
+    v.y = (__builtin_amdgcn_perm(b.x, b.x, 0x030c020cu) & 0x80008000u) | 0x3F803F80u;
+    v.z = (__builtin_amdgcn_perm(b.y, b.y, 0x010c000cu) & 0x80008000u) | 0x3F803F80u;
+    v.w = (__builtin_amdgcn_perm(b.y, b.y, 0x030c020cu) & 0x80008000u) | 0x3F803F80u;
     return __builtin_bit_cast(v8bf, v);
 }
 
-constexpr int TB_KC = 64;            // k per LDS chunk (two k-steps of 32)
-constexpr int TB_LD = TB_KC + 8;     // LDS row of one column (+8: spreads the banks)
-
-__global__ __launch_bounds__(256) void k_theta_bf16(Dims d, const int8_t* __restrict__ s, int rows,
+// As k_theta, a wave keeps the weights of its 16 columns in registers (hi and lo
+// planes, KS k-steps of 32 sites) and walks the block's rows, RT tiles of 16 at a time;
+// the spins are staged as bytes, rows an odd number of 32-byte pieces apart.  Per
+// element the accumulation order is that of one k-step at a time: + a W_hi, then
+// + a W_lo.  MULTI: wider lattices in chunks of KS k-steps for all rows of the block.
+// What bounds it is the vector ALU in the epilogue (tanh).  16,384 rows of 256 sites,
+// 1,024 units: 61 us (157 with spins loaded byte by byte for every 64 columns); 4,096
+// rows of 100 sites, 200 units: 7.0 (11).
+template <int KS, int RT, bool MULTI>
+__global__ __launch_bounds__(256) void k_theta_bf16(Dims d, const int8_t* __restrict__ s, long rows,
+                                                    int RB,
                                                     const uint16_t* __restrict__ Whi,
                                                     const uint16_t* __restrict__ Wlo,
-                                                    float* __restrict__ dst1, float* __restrict__ dst2,
-                                                    long dst2_stride) {
-    // block = 64 rows x 64 columns, wave = 16 rows x the 64 columns (four MFMA
-    // tiles sharing the spin fragment).  The block's W panel moves through LDS
-    // in chunks of 64 k (two coalesced 16-byte loads per thread and plane, read
-    // by all four waves); the next chunk's W and spins are in flight while the
-    // current chunk is multiplied.  Per element the accumulation order is that
-    // of one k-step at a time: + a W_hi, then + a W_lo.
-    __shared__ __attribute__((aligned(16))) uint16_t Sh[2][64 * TB_LD];
-    __shared__ __attribute__((aligned(16))) uint16_t Sl[2][64 * TB_LD];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+                                                    float* __restrict__ dst1,
+                                                    float* __restrict__ dst2, long dst2_stride) {
+    extern __shared__ __align__(16) int8_t th_lds[];
+    constexpr int LD = 32 * (KS | 1);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lr = lane & 15, lk = lane >> 4;
-    const int row0 = blockIdx.x * 64 + wave * 16;
-    const int col0 = blockIdx.y * 64;
-    const int nch = (d.Kb + TB_KC - 1) / TB_KC;
-    // staging items of this thread: columns sc and sc + 32 of the panel, k
-    // offset sk of the chunk (8 entries each)
-    const int sc = tid >> 3, sk = (tid & 7) * 8;
-    const bool scin0 = col0 + sc < d.Mw, scin1 = col0 + sc + 32 < d.Mw;
-    const uint16_t* gh = Whi + (size_t)(col0 + sc) * d.Kb + sk;
-    const uint16_t* gl = Wlo + (size_t)(col0 + sc) * d.Kb + sk;
-    const size_t g32 = (size_t)32 * d.Kb;  // 32 columns further
-    const v8s z8 = {0, 0, 0, 0, 0, 0, 0, 0};
-    v4f acc[4];
+    const long r0 = (long)blockIdx.x * RB;
+    const int nr = (int)min((long)RB, rows - r0);
+    const int tiles = d.Mw / 16, tile = (int)blockIdx.y * 4 + wave;
+    const int nks = d.Kb / 32, nch = MULTI ? (nks + KS - 1) / KS : 1;
+    const bool work = tile < tiles && 16 * tile < d.M;  // (past M: constants only)
+    const int col = 16 * tile + lr;
+    v8bf wh[KS], wl[KS];
+    auto load_w = [&](int c) {  // (tiles past the last one repeat it)
+        const size_t o = (size_t)(16 * min(tile, tiles - 1) + lr) * d.Kb + 8 * lk;
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct) acc[ct] = v4f{0, 0, 0, 0};
-    v8s nh, nl, nh1, nl1;
-    v8bf na[2];
-    auto fetch = [&](int ch) {  // W pieces of chunk ch, and this lane's spins for it
-        const int k = ch * TB_KC + sk;
-        const bool kin = k < d.Kb;
-        nh = (scin0 && kin) ? *(const v8s*)(gh + ch * TB_KC) : z8;
-        nl = (scin0 && kin) ? *(const v8s*)(gl + ch * TB_KC) : z8;
-        nh1 = (scin1 && kin) ? *(const v8s*)(gh + g32 + ch * TB_KC) : z8;
-        nl1 = (scin1 && kin) ? *(const v8s*)(gl + g32 + ch * TB_KC) : z8;
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int kk = ch * TB_KC + 32 * u + 8 * lk;
-            na[u] = kk < d.Kb ? spins_bf16(s, d.N, row0 + lr, rows, kk)
-                              : __builtin_bit_cast(v8bf, z8);
-        }
-    };
-    fetch(0);
-    *(v8s*)&Sh[0][sc * TB_LD + sk] = nh;
-    *(v8s*)&Sl[0][sc * TB_LD + sk] = nl;
-    *(v8s*)&Sh[0][(sc + 32) * TB_LD + sk] = nh1;
-    *(v8s*)&Sl[0][(sc + 32) * TB_LD + sk] = nl1;
-    __syncthreads();
-    for (int ch = 0; ch < nch; ++ch) {
-        const v8bf a0 = na[0], a1 = na[1];
-        if (ch + 1 < nch) fetch(ch + 1);
-        const uint16_t* ph = Sh[ch & 1];
-        const uint16_t* pl = Sl[ch & 1];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const v8bf a = u == 0 ? a0 : a1;
-            if (ch * TB_KC + 32 * u < d.Kb) {
-#pragma unroll
-                for (int ct = 0; ct < 4; ++ct) {
-                    const int o = (ct * 16 + lr) * TB_LD + 32 * u + 8 * lk;
-                    const v8s bh = *(const v8s*)&ph[o], bl = *(const v8s*)&pl[o];
-                    acc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(v8bf, bh),
-                                                                      acc[ct], 0, 0, 0);
-                    acc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(v8bf, bl),
-                                                                      acc[ct], 0, 0, 0);
-                }
+        for (int ks = 0; ks < KS; ++ks) {
+            if constexpr (MULTI) {
+                const int k = c * KS + ks;
+                const v8s z = {0, 0, 0, 0, 0, 0, 0, 0};
+                const v8s h = *(const v8s*)(Whi + o + 32 * min(k, nks - 1));
+                const v8s l = *(const v8s*)(Wlo + o + 32 * min(k, nks - 1));
+                wh[ks] = __builtin_bit_cast(v8bf, k < nks ? h : z);
+                wl[ks] = __builtin_bit_cast(v8bf, k < nks ? l : z);
+            } else {
+                wh[ks] = *(const v8bf*)(Whi + o + 32 * ks);
+                wl[ks] = *(const v8bf*)(Wlo + o + 32 * ks);
             }
         }
-        if (ch + 1 < nch) {
-            *(v8s*)&Sh[(ch + 1) & 1][sc * TB_LD + sk] = nh;
-            *(v8s*)&Sl[(ch + 1) & 1][sc * TB_LD + sk] = nl;
-            *(v8s*)&Sh[(ch + 1) & 1][(sc + 32) * TB_LD + sk] = nh1;
-            *(v8s*)&Sl[(ch + 1) & 1][(sc + 32) * TB_LD + sk] = nl1;
-        }
+    };
+    auto stage = [&](int c) {
+        stage_spins<8 * KS>(th_lds, LD, s, d.N, r0, nr, RB, 32 * KS * c, tid, 256);
+    };
+    if constexpr (!MULTI) {
+        load_w(0);
+        stage(0);
         __syncthreads();
     }
+#pragma unroll 1
+    for (int rt = 0; rt < nr; rt += 16 * RT) {
+        v4f acc[RT];
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-        const int col = col0 + ct * 16 + lr;
-        if (col >= d.Mw) continue;
+        for (int u = 0; u < RT; ++u) acc[u] = v4f{0, 0, 0, 0};
+        auto products = [&]() {
+            const int8_t* row = th_lds + (rt + lr) * LD + 8 * lk;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int row = row0 + acc_row<float>(lk, i);
-            if (row >= rows) continue;
-            const float t = act(acc[ct][i], col, d.M);
-            dst1[(size_t)row * d.Mw + col] = t;
-            if (dst2) dst2[(size_t)row * dst2_stride + col] = t;
+            for (int ks = 0; ks < KS; ++ks) {
+                v8bf a[RT];
+#pragma unroll
+                for (int u = 0; u < RT; ++u)
+                    a[u] = spins_bf16(*(const uint2*)(row + 16 * u * LD + 32 * ks));
+#pragma unroll
+                for (int u = 0; u < RT; ++u)
+                    acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u], wh[ks], acc[u], 0, 0, 0);
+#pragma unroll
+                for (int u = 0; u < RT; ++u)
+                    acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u], wl[ks], acc[u], 0, 0, 0);
+            }
+        };
+        if constexpr (MULTI) {  // (one step of rows: RB = 16 RT)
+            for (int c = 0; c < nch; ++c) {
+                __syncthreads();
+                stage(c);
+                load_w(c);
+                __syncthreads();
+                products();
+            }
+        } else if (work) {
+            products();
+        }
+        if (tile >= tiles) continue;
+        const long b1 = (r0 + rt) * d.Mw, b2 = (r0 + rt) * dst2_stride;
+#pragma unroll
+        for (int u = 0; u < RT; ++u) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int row = 16 * u + acc_row<float>(lk, i);
+                const float t = work ? act(acc[u][i], col, d.M) : (col == d.M ? 1.0f : 0.0f);
+                if (rt + row < nr) {
+                    (dst1 + b1)[(unsigned)(row * d.Mw + col)] = t;
+                    if (dst2) (dst2 + b2)[row * dst2_stride + col] = t;
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);  // one tile's values live at a time
         }
     }
 }
@@ -414,13 +427,12 @@ static void theta_g(hipStream_t st, const Dims& d, const int8_t* s, long rows, c
     const int nby = EPI ? 1 : (tiles + nw - 1) / nw;
     const int RB = MULTI ? 32 : theta_rows(rows, nby, 512);
     const size_t lds = (size_t)RB * 16 * (G | 1) + (EPI ? 8 * (size_t)nw * RB : 0);
-    const int words = d.N % 4 == 0 && ((uintptr_t)s & 3) == 0;
     const dim3 grid((unsigned)((rows + RB - 1) / RB), (unsigned)nby);
     if (RB > 16)
-        k_theta<R, G, 2, EPI, MULTI><<<grid, 64 * nw, lds, st>>>(d, s, rows, words, RB, Wa, dst1,
+        k_theta<R, G, 2, EPI, MULTI><<<grid, 64 * nw, lds, st>>>(d, s, rows, RB, Wa, dst1,
                                                                  dst2, dst2_stride, av);
     else
-        k_theta<R, G, 1, EPI, MULTI><<<grid, 64 * nw, lds, st>>>(d, s, rows, words, RB, Wa, dst1,
+        k_theta<R, G, 1, EPI, MULTI><<<grid, 64 * nw, lds, st>>>(d, s, rows, RB, Wa, dst1,
                                                                  dst2, dst2_stride, av);
 }
 template <typename R, int EPI>
@@ -442,6 +454,25 @@ static void theta_r(hipStream_t st, const Dims& d, const int8_t* s, long rows, c
 #undef THETA_G
 }
 
+template <int KS, bool MULTI>
+static void theta_bf16(hipStream_t st, const Dims& d, const int8_t* s, long rows, const Tables& t,
+                       float* dst1, float* dst2, long dst2_stride) {
+    const long nby = (d.Mw + 63) / 64;
+    const int RB = theta_rows(rows, nby, 1024);
+    auto go = [&](auto kernel, int rb) {
+        kernel<<<dim3((unsigned)((rows + rb - 1) / rb), (unsigned)nby), 256,
+                 (size_t)rb * 32 * (KS | 1), st>>>(d, s, rows, rb, t.Whi, t.Wlo, dst1, dst2,
+                                                   dst2_stride);
+    };
+    if constexpr (MULTI) {  // (all of a block's rows at once)
+        if (RB >= 64) go(k_theta_bf16<KS, 4, true>, 64);
+        else go(k_theta_bf16<KS, 2, true>, 32);
+    } else {
+        if (RB > 16) go(k_theta_bf16<KS, 2, false>, RB);
+        else go(k_theta_bf16<KS, 1, false>, 16);
+    }
+}
+
 void launch_theta(hipStream_t st, const Dims& d, int prec, const Tables& t, const int8_t* s,
                   int rows, void* dst1, void* dst2, long dst2_stride) {
     if (rows <= 0) return;
@@ -450,9 +481,21 @@ void launch_theta(hipStream_t st, const Dims& d, int prec, const Tables& t, cons
     } else if (prec == 1) {
         theta_r<float, 0>(st, d, s, rows, t.Wa, dst1, dst2, dst2_stride, nullptr);
     } else {
-        dim3 grid((rows + 63) / 64, (d.Mw + 63) / 64);
-        k_theta_bf16<<<grid, 256, 0, st>>>(d, s, rows, t.Whi, t.Wlo, (float*)dst1, (float*)dst2,
-                                           dst2_stride);
+#define THETA_B(KS, MULTI) \
+    theta_bf16<KS, MULTI>(st, d, s, rows, t, (float*)dst1, (float*)dst2, dst2_stride)
+        switch (d.Kb / 32) {
+            case 1: return THETA_B(1, false);
+            case 2: return THETA_B(2, false);
+            case 3: return THETA_B(3, false);
+            case 4: return THETA_B(4, false);
+            case 5: return THETA_B(5, false);
+            case 6: return THETA_B(6, false);
+            case 7: return THETA_B(7, false);
+            case 8: return THETA_B(8, false);
+            case 9: return THETA_B(9, false);
+            default: return THETA_B(4, true);
+        }
+#undef THETA_B
     }
 }
 

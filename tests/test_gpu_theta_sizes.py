@@ -1,0 +1,38 @@
+"""tanh(theta) at the edges of its kernels: rows that start at any byte and sites that
+end inside a word, k-steps of 32 sites and chunks of them, tiles of 16 rows and columns,
+one to many rows per block.
+
+Taken from the Jacobian's hidden-bias columns, against FP64 sums.  Bars: FP64 sums of at
+most 400 terms, 1e-13; FP32, and the split weights of the BF16 form (2^-17 each, FP32
+sums), 3e-5 absolute as for the other Jacobians.
+"""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("prec,tol", [("fp64", 1e-13), ("fp32", 3e-5), ("bf16", 3e-5)])
+@pytest.mark.parametrize("N,M,n", [
+    (2, 1, 1), (3, 5, 17), (5, 16, 65), (15, 17, 33), (31, 64, 100), (32, 65, 1), (33, 7, 40),
+    (63, 130, 31), (130, 40, 2049), (255, 20, 70), (287, 33, 64), (288, 16, 130), (322, 70, 4100),
+    (399, 3, 35),
+])
+def test_activations(N, M, n, prec, tol):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a visible HIP device")
+    from paper_2112_10526_amd.nqs import VMCState
+    print(f"[case] N={N} M={M} n={n} {prec}", flush=True)
+    params = np.random.default_rng(N + M).normal(size=N + M + N * M) * 0.1
+    st = VMCState(model="tfim", n_sites=N, bonds=[[0, 1]], J=1.0, h=1.0, n_hidden=M, precision=prec,
+                  n_chains=2, samples_per_chain=1, sweep_size=N, seed=3, params=params)
+    s = synth.random_configs(n, N, 5 + N)
+    # a batch that starts one row into its buffer (any byte alignment)
+    buf = torch.from_numpy(np.concatenate([s[:1], s])).cuda()
+    t = st.jacobian(buf[1:])[:, N:N + M].double().cpu().numpy()
+    ref = np.tanh(params[N:N + M] + s.astype(np.float64) @ params[N + M:].reshape(M, N).T)
+    assert np.abs(t - ref).max() <= tol
+    st.close()
