@@ -103,6 +103,7 @@ struct nqs_ctx {
     Buffers b{};
     long Ns = 0, Bx = 0;
     int ksplit = 1, ndpart = 1, Pld = 0, ntiles = 0;
+    int gedge = 128;    // edge of the Gram's tiles
     int tri = 0;        // dense product's form; the Jacobian's buffer is its scratch
     int ncu = 256;  // compute units of the device
     long cg_iter = 0;
@@ -264,7 +265,7 @@ size_t layout(nqs_ctx* c, char* base) {
     if (c->qgt == NQS_QGT_JACOBIAN_DENSE) {
         // (a symmetric model's Jacobian and Gram are FP64, P_sym columns)
         const size_t des = c->symm ? 8 : es;
-        b.O = take(des * (size_t)c->Ns * c->Pld);
+        b.O = take(des * (size_t)(c->prec == 2 ? (c->Ns + 31) / 32 * 32 : c->Ns) * c->Pld);
         b.G = take(des * (size_t)c->Pd * c->Pld);
         b.colsum = (double*)take(8 * (size_t)c->Pld);
         b.gpart = c->gS > 1 ? (double*)take(gram_part_bytes(c->ntiles, c->gS)) : nullptr;
@@ -377,6 +378,8 @@ void derive(nqs_ctx* c) {
         if (!c->cplx) {
             const size_t des = c->symm ? 8 : esize(c->prec);
             c->tri = dense_tri(c->Pd, des, des * (size_t)c->Ns * c->Pld);
+            c->gedge = !c->symm && c->prec == 2 ? gram_edge(c->Pd, c->tri == 0) : 128;
+            c->ntiles = gram_tiles(c->Pd, c->gedge);
         }
         long nd = (long)d.Ma * d.Na / 256 + 2;
         const long nd2 = c->Bx / 64 + 2, nd3 = (long)c->Pd / 4 + 2;
@@ -625,17 +628,24 @@ void issue_dense_setup(nqs_ctx* c, double tol, int maxiter, double shift) {
         PROF(NQS_PROF_JACOBIAN);
         launch_colsum(c->stream, c->d, c->prec, c->b.samples, c->b.tsm, c->Ns, c->b.part,
                       part_bytes(c), c->ncu, c->b.gacc, true, true, c->b.colsum);
-        launch_jacobian_centred(c->stream, c->d, c->prec, c->b.samples, c->b.tsm, c->Ns, c->Ns,
-                                c->b.O, P, c->Pld, c->b.colsum, c->prec == 2);
+        if (c->prec == 2)
+            launch_jacobian_frags(c->stream, c->d, c->b.samples, (const float*)c->b.tsm, c->Ns,
+                                  c->b.O, P, c->Pld, c->b.colsum);
+        else
+            launch_jacobian_centred(c->stream, c->d, c->prec, c->b.samples, c->b.tsm, c->Ns, c->Ns,
+                                    c->b.O, P, c->Pld, c->b.colsum);
     }
     {
         PROF(NQS_PROF_GRAM);
         if (c->prec == 0)
             launch_gram_sliced(c->stream, (const double*)c->b.O, c->Ns, c->Pld, P,
                                (double*)c->b.G, c->b.tiles, c->ntiles, c->gS, c->b.gpart);
+        else if (c->prec == 1)
+            launch_gram(c->stream, (const float*)c->b.O, c->Ns, c->Pld, P, (float*)c->b.G,
+                        c->b.tiles, c->ntiles, c->tri == 0);
         else
-            launch_gram(c->stream, c->prec, c->b.O, c->Ns, c->Pld, P, c->b.G, c->b.tiles,
-                        c->ntiles, c->tri == 0);
+            launch_gram_frags(c->stream, c->b.O, c->Ns, c->Pld, P, (float*)c->b.G, c->b.tiles,
+                              c->ntiles, c->gedge, c->tri == 0);
     }
     launch_pack(c->stream, c->d, c->b.grad, c->b.fp, P);
     launch_cg_init(c->stream, P, c->b.fp, c->b.xp, c->b.rp, c->b.pp, c->b.dpart, c->b.sc, tol,
@@ -1534,7 +1544,7 @@ int nqs_bind_workspace(nqs_ctx* c, void* dev_ptr, size_t bytes) {
                                  hipMemcpyHostToDevice, c->stream));
     if (c->qgt == NQS_QGT_JACOBIAN_DENSE) {
         std::vector<int> t(2 * (size_t)c->ntiles);
-        fill_gram_tiles(c->cplx ? (int)c->P : c->Pd, t.data());
+        fill_gram_tiles(c->cplx ? (int)c->P : c->Pd, c->gedge, t.data());
         HIPCHK(c, hipMemcpyAsync(c->b.tiles, t.data(), 4 * t.size(), hipMemcpyHostToDevice,
                                  c->stream));
         HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -1896,7 +1906,7 @@ int nqs_jacobian(nqs_ctx* c, const int8_t* s, int64_t n, void* O_out, int center
         char* rows = (char*)O_out + es * (size_t)k0 * c->P;
         if (center)
             launch_jacobian_centred(c->stream, c->d, c->prec, sk, c->b.tx, m, (long)n, rows,
-                                    (int)c->P, (long)c->P, c->b.tmpv, false);
+                                    (int)c->P, (long)c->P, c->b.tmpv);
         else
             launch_jacobian(c->stream, c->d, c->prec, sk, c->b.tx, m, rows, (int)c->P, (long)c->P);
     }

@@ -265,13 +265,6 @@ __device__ __forceinline__ void chol_back_block(const double (*Yk)[CH_NB + 1], c
     xk[c] = (a[0] + a[1]) + (a[2] + a[3]);
 }
 
-// A barrier for data passed through LDS only: loads from memory stay in flight.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // L^T x = y in one workgroup, Q columns per thread (n <= 1024 Q), the columns'
 // running right-hand side in registers: per diagonal block its 32 values meet in
 // LDS, x_k, then every earlier column loses its part.  The block's rows of L are

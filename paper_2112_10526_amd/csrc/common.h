@@ -125,6 +125,13 @@ __device__ __forceinline__ T wave_prod(T v) {
     return (readlane(v, 0) * readlane(v, 16)) * (readlane(v, 32) * readlane(v, 48));
 }
 
+// A barrier for data passed through LDS only: loads from memory stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // Row of the 16 x 16 accumulator held in slot i by a lane with lk = lane / 16

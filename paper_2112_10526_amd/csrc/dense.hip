@@ -48,20 +48,6 @@ __global__ __launch_bounds__(256) void k_colsum_fin(const double* __restrict__ p
     __syncthreads();
     if (wave == 0 && p < P) cs[p] = (ws[0][lane] + ws[1][lane]) + (ws[2][lane] + ws[3][lane]);
 }
-// SPLIT (FP32 entries, dense form of the BF16 precision): each centred entry x
-// is stored in its own 4 bytes as the BF16 pair (hi << 16) | lo, hi = bf16(x),
-// lo = bf16(x - hi), the operand form of the BF16 Gram.
-template <typename R, bool SPLIT>
-__device__ __forceinline__ R center_store(double v) {
-    if constexpr (SPLIT) {
-        const float x = (float)v;
-        const uint16_t hi = f32_to_bf16_bits(x);
-        const uint16_t lo = f32_to_bf16_bits(x - bf16_bits_to_f32(hi));
-        return __builtin_bit_cast(float, ((uint32_t)hi << 16) | lo);
-    } else {
-        return (R)v;
-    }
-}
 __global__ __launch_bounds__(256) void k_center_scale(double* __restrict__ O, long n, long ld,
                                                       int P, const double* __restrict__ cs,
                                                       int vec) {
@@ -123,7 +109,7 @@ __device__ __forceinline__ JacCol jac_col(const Dims& d, long p, int P) {
 __device__ const int8_t k_one_s = 1, k_zero_s = 0;
 template <typename R>
 __device__ const R k_one_t = (R)1;
-template <typename R, bool CENTER, bool SPLIT, bool VEC>
+template <typename R, bool CENTER, bool VEC>
 __global__ __launch_bounds__(256) void k_jac_rows(Dims d, const int8_t* __restrict__ s,
                                                   const R* __restrict__ tact, long rows, int rpb,
                                                   double inv, double rs, int P, long ld,
@@ -152,7 +138,7 @@ __global__ __launch_bounds__(256) void k_jac_rows(Dims d, const int8_t* __restri
     const long k0 = (long)blockIdx.y * rpb, k1 = min(rows, k0 + rpb);
     auto entry = [&](R t, int sv, int e) -> R {
         if constexpr (CENTER)
-            return center_store<R, SPLIT>(((double)t * (double)sv - mean[e]) * rs);
+            return (R)(((double)t * (double)sv - mean[e]) * rs);
         else
             return t * (R)sv;
     };
@@ -349,101 +335,161 @@ __global__ __launch_bounds__(256) void k_gram_fin(const double* __restrict__ par
     if (p != q) G[q * ld + p] = a;
 }
 
-// BF16 form: the same Gram on the BF16 matrix cores.  The centring kernel has
-// stored every entry x as the BF16 pair (hi << 16) | lo with x ~= hi + lo;
-// three products (hi hi + hi lo + lo hi) are accumulated in FP32: about 2^-16
-// relative error per product at BF16 rates.  A slice of GS_K samples of the
-// block's two 128-column panels is loaded (each thread: 4 consecutive samples x
-// 4 consecutive columns of each panel, 16 bytes per sample), regrouped into
-// hi and lo planes and stored in LDS transposed ([column][sample], the
-// contracted index contiguous for the MFMA operands, 4 samples per 8-byte
-// store); the next slice's loads are issued before the current slice's MFMAs.
-constexpr int GS_K = 32, GS_KP = GS_K + 8;  // samples per slice; LDS row stride (halves)
+// The BF16 form's Gram: each centred entry x as the pair hi = bf16(x), lo = bf16(x -
+// hi), and G = sum over samples of hi.hi, then hi.lo, then lo.hi of every 32 samples on
+// the 16x16x32 BF16 MFMA, in FP32.
+//
+// The Jacobian is written as that instruction's operands: fragment (kb, ct) holds
+// samples 32 kb .. + 31 of columns 16 ct .. + 15, plane hi, then lo, each [lane][8
+// samples], lane = column + 16 (sample / 8); samples past n and columns past P are zero.
+// A wave takes one tile of columns through `kbs` k-blocks.  16,384 x 33,344 entries
+// (2.19 GB) in 685 us.
 typedef short v8s_g __attribute__((ext_vector_type(8)));
+__global__ __launch_bounds__(256) void k_jac_frags(Dims d, const int8_t* __restrict__ s,
+                                                   const float* __restrict__ tact, long n, int nkb,
+                                                   int kbs, double inv, double rs, int P, int nct,
+                                                   const double* __restrict__ cs,
+                                                   uint4* __restrict__ F) {
+    const int lane = threadIdx.x & 63, ct = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (ct >= nct) return;
+    const long p = 16L * ct + (lane & 15);
+    const JacCol c = jac_col(d, p, P);
+    const bool has_s = c.kind == 0 || c.kind == 2, has_t = c.kind == 1 || c.kind == 2;
+    const int8_t* sp = has_s ? s + c.i : (c.kind == 3 ? &k_zero_s : &k_one_s);
+    const float* tp = has_t ? tact + c.j : &k_one_t<float>;
+    const int ss = has_s ? d.N : 0, ts = has_t ? d.Mw : 0;
+    const double mean = c.kind != 3 ? cs[p] * inv : 0.0;
+    const int kb1 = min(nkb, (int)(blockIdx.y + 1) * kbs);
+    for (int kb = blockIdx.y * kbs; kb < kb1; ++kb) {
+        const long k0 = 32L * kb + 8 * (lane >> 4);
+        float t[8];
+        int sv[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const long k = min(k0 + e, n - 1);
+            t[e] = tp[k * ts];
+            sv[e] = sp[k * ss];
+        }
+        uint32_t hi[8], lo[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float x = k0 + e < n ? (float)(((double)t[e] * (double)sv[e] - mean) * rs) : 0.0f;
+            hi[e] = f32_to_bf16_bits(x);
+            lo[e] = f32_to_bf16_bits(x - bf16_bits_to_f32((uint16_t)hi[e]));
+        }
+        uint4* f = F + ((size_t)kb * nct + ct) * 128 + lane;
+        f[0] = make_uint4(hi[0] | hi[1] << 16, hi[2] | hi[3] << 16, hi[4] | hi[5] << 16,
+                          hi[6] | hi[7] << 16);
+        f[64] = make_uint4(lo[0] | lo[1] << 16, lo[2] | lo[3] << 16, lo[4] | lo[5] << 16,
+                           lo[6] | lo[7] << 16);
+    }
+}
 
-__global__ __launch_bounds__(256) void k_gram_split(const uint32_t* __restrict__ A, long n, long ld,
-                                                    int P, float* __restrict__ G,
-                                                    const int* __restrict__ tiles, bool mirror) {
-    __shared__ __align__(16) uint16_t Ls[2][2][128 * GS_KP];  // [panel p/q][hi/lo][col][sample]
-    const int tp = tiles[2 * blockIdx.x], tq = tiles[2 * blockIdx.x + 1];
+// A block of WP x WQ waves takes a tile of G of 16 WP AT rows and 16 WQ BT columns,
+// each wave AT x BT MFMA tiles; both panels' fragments of a k-block move through one of
+// two LDS buffers, the next k-block's in registers while this one is multiplied.  The
+// products of one kind run over a row of tiles before the next kind, so that none
+// waits for the one before.
+// A product reads (AT + BT) / (3 AT BT) fragment pairs from LDS: a wave's 64 x 64 part
+// of a 128 x 128 tile keeps LDS as busy as the matrix cores, 128 x 64 of 256 x 256
+// needs a quarter less, and half the writes.  D: k-blocks the loads run ahead.  16,384
+// samples, P = 33,344: 48 ms, 1.14 PFLOP/s (the library's plain BF16 product reaches 1.2
+// here), 68 ms with pairs regrouped on the way into LDS; 4,096 samples, P = 860: 43 us,
+// 202.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+template <int WP, int WQ, int AT, int BT, int D, int SUB>
+__global__ __launch_bounds__(64 * WP * WQ, 2) void k_gram_frags(const u32x4* __restrict__ F, int nkb,
+                                                             int nct, long ld, int P,
+                                                             float* __restrict__ G,
+                                                             const int* __restrict__ tiles,
+                                                             bool mirror) {
+    constexpr int PA = WP * AT, PB = WQ * BT, T = 64 * WP * WQ, NP = (PA + PB) * 128 / T;
+    extern __shared__ __align__(16) u32x4 Lf[];  // [2][PA + PB][128]
+    // SUB x SUB blocks share a listed tile
+    const int lt = blockIdx.x / (SUB * SUB), sub = blockIdx.x % (SUB * SUB);
+    const int lp = tiles[2 * lt], lq = tiles[2 * lt + 1];
+    const int tp = lp * SUB + sub / SUB, tq = lq * SUB + sub % SUB;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int lr = lane & 15, lk = lane >> 4;
-    const long base[2] = {(long)tp * 128, (long)tq * 128};
-    const int rg = tid & 7, c4 = tid >> 3;  // rows 4 rg .. 4 rg + 3, columns 4 c4 .. 4 c4 + 3
-    uint4 ra[2][4];
-    auto load = [&](long k0) {
+    const int wp = wave / WQ, wq = wave % WQ;
+    const u32x4* src[NP];
 #pragma unroll
-        for (int op = 0; op < 2; ++op)
+    for (int m = 0; m < NP; ++m) {  // (a ragged tile's missing columns: the last ones again)
+        const int f = (tid + m * T) >> 7;
+        const int ct = min(f < PA ? tp * PA + f : tq * PB + f - PA, nct - 1);
+        src[m] = F + (size_t)ct * 128 + (tid & 127);
+    }
+    const size_t step = (size_t)nct * 128;
+    v4f acc[AT][BT];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const long k = k0 + 4 * rg + j;
-                ra[op][j] = k < n ? *(const uint4*)(A + k * ld + base[op] + 4 * c4)
-                                  : make_uint4(0u, 0u, 0u, 0u);
-            }
+    for (int a = 0; a < AT; ++a)
+#pragma unroll
+        for (int b = 0; b < BT; ++b) acc[a][b] = v4f{0, 0, 0, 0};
+    auto load = [&](u32x4 (&g)[NP], int kb) {
+        const size_t o = (size_t)min(kb, nkb - 1) * step;
+#pragma unroll
+        for (int m = 0; m < NP; ++m) g[m] = src[m][o];
     };
-    auto stage = [&]() {
+    auto put = [&](const u32x4 (&g)[NP], int kb) {
+        u32x4* L = Lf + (kb & 1) * (PA + PB) * 128;
 #pragma unroll
-        for (int op = 0; op < 2; ++op)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                uint32_t w[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    w[j] = e == 0 ? ra[op][j].x : e == 1 ? ra[op][j].y : e == 2 ? ra[op][j].z : ra[op][j].w;
-                // samples (j, j + 1) -> one word per plane, the earlier sample in the low half
-                const uint2 hi = make_uint2((w[1] & 0xFFFF0000u) | (w[0] >> 16),
-                                            (w[3] & 0xFFFF0000u) | (w[2] >> 16));
-                const uint2 lo = make_uint2((w[1] << 16) | (w[0] & 0xFFFFu),
-                                            (w[3] << 16) | (w[2] & 0xFFFFu));
-                const int off = (4 * c4 + e) * GS_KP + 4 * rg;
-                *(uint2*)&Ls[op][0][off] = hi;
-                *(uint2*)&Ls[op][1][off] = lo;
-            }
+        for (int m = 0; m < NP; ++m) L[tid + m * T] = g[m];
     };
-    v4f acc[4][4];
+    // k-block kb; `in` takes k-block kb + D, `next` holds kb + 1
+    auto block = [&](int kb, u32x4 (&in)[NP], const u32x4 (&next)[NP]) {
+        load(in, kb + D);
+        __builtin_amdgcn_sched_barrier(0);  // (the loads stay ahead of the products)
+        const u32x4* L = Lf + (kb & 1) * (PA + PB) * 128;
+        const u32x4* La = L + wp * AT * 128 + lane;
+        const u32x4* Lb = L + (PA + wq * BT) * 128 + lane;
+        v8bf bh[BT], bl[BT];
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = v4f{0, 0, 0, 0};
-    const int pr = (wave >> 1) * 64, qr = (wave & 1) * 64;  // the wave's quarter
-    load(0);
-    for (long k0 = 0; k0 < n; k0 += GS_K) {
-        __syncthreads();  // the previous slice is no longer read
-        stage();
-        __syncthreads();
-        if (k0 + GS_K < n) load(k0 + GS_K);
-        v8s_g ah[4], al[4], bh[4], bl[4];
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            const int cp = (pr + a * 16 + lr) * GS_KP + 8 * lk;
-            const int cq = (qr + a * 16 + lr) * GS_KP + 8 * lk;
-            ah[a] = *(const v8s_g*)&Ls[0][0][cp];
-            al[a] = *(const v8s_g*)&Ls[0][1][cp];
-            bh[a] = *(const v8s_g*)&Ls[1][0][cq];
-            bl[a] = *(const v8s_g*)&Ls[1][1][cq];
+        for (int b = 0; b < BT; ++b) {
+            bh[b] = __builtin_bit_cast(v8bf, Lb[b * 128]);
+            bl[b] = __builtin_bit_cast(v8bf, Lb[b * 128 + 64]);
         }
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
+        for (int a = 0; a < AT; ++a) {
+            const v8bf xh = __builtin_bit_cast(v8bf, La[a * 128]);
+            const v8bf xl = __builtin_bit_cast(v8bf, La[a * 128 + 64]);
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const v8bf xh = __builtin_bit_cast(v8bf, ah[a]), xl = __builtin_bit_cast(v8bf, al[a]);
-                const v8bf yh = __builtin_bit_cast(v8bf, bh[b]), yl = __builtin_bit_cast(v8bf, bl[b]);
-                acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh, yh, acc[a][b], 0, 0, 0);
-                acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh, yl, acc[a][b], 0, 0, 0);
-                acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xl, yh, acc[a][b], 0, 0, 0);
-            }
+            for (int b = 0; b < BT; ++b)
+                acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh, bh[b], acc[a][b], 0, 0, 0);
+#pragma unroll
+            for (int b = 0; b < BT; ++b)
+                acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh, bl[b], acc[a][b], 0, 0, 0);
+#pragma unroll
+            for (int b = 0; b < BT; ++b)
+                acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xl, bh[b], acc[a][b], 0, 0, 0);
+        }
+        put(next, kb + 1);
+        lds_barrier();
+    };
+    u32x4 g0[NP], g1[D > 1 ? NP : 1];
+    load(g0, 0);
+    put(g0, 0);
+    if constexpr (D > 1) load(g1, 1);
+    lds_barrier();
+    if constexpr (D > 1) {
+        for (int kb = 0; kb + 1 < nkb; kb += 2) {
+            block(kb, g0, g1);
+            block(kb + 1, g1, g0);
+        }
+        if (nkb & 1) block(nkb - 1, g0, g1);
+    } else {
+        for (int kb = 0; kb < nkb; ++kb) block(kb, g0, g0);
     }
+    const int lr = lane & 15, lk = lane >> 4;
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < AT; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
+        for (int b = 0; b < BT; ++b)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const long p = base[0] + pr + a * 16 + acc_row<float>(lk, i);
-                const long q = base[1] + qr + b * 16 + lr;
+                const long p = 16L * (tp * PA + wp * AT + a) + acc_row<float>(lk, i);
+                const long q = 16L * (tq * PB + wq * BT + b) + lr;
                 if (p < P && q < P) {
                     G[p * ld + q] = acc[a][b][i];
-                    if (mirror && tp != tq) G[q * ld + p] = acc[a][b][i];
+                    if (mirror && lp != lq) G[q * ld + p] = acc[a][b][i];
                 }
             }
 }
@@ -703,7 +749,7 @@ static void dense_matvec(hipStream_t st, const R* G, int P, long ld, const doubl
 // ---------------------------------------------------------------------------
 // rows per block: long enough to pay for finding the columns (64), shorter where
 // that leaves fewer than about four blocks per compute unit
-template <typename R, bool CENTER, bool SPLIT>
+template <typename R, bool CENTER>
 static void jac_rows(hipStream_t st, const Dims& d, const int8_t* s, const void* tact, long n,
                      long nmean, void* O, int P, long ld, const double* cs) {
     const long cb = (ld + 1023) / 1024;
@@ -719,27 +765,35 @@ static void jac_rows(hipStream_t st, const Dims& d, const int8_t* s, const void*
         const R* tr = (const R*)tact + r0 * d.Mw;
         R* orow = (R*)O + r0 * ld;
         if (vec)
-            k_jac_rows<R, CENTER, SPLIT, true><<<g, 256, 0, st>>>(d, sr, tr, m, rpb, inv, rs, P, ld,
+            k_jac_rows<R, CENTER, true><<<g, 256, 0, st>>>(d, sr, tr, m, rpb, inv, rs, P, ld,
                                                                   cs, orow);
         else
-            k_jac_rows<R, CENTER, SPLIT, false><<<g, 256, 0, st>>>(d, sr, tr, m, rpb, inv, rs, P,
+            k_jac_rows<R, CENTER, false><<<g, 256, 0, st>>>(d, sr, tr, m, rpb, inv, rs, P,
                                                                    ld, cs, orow);
     }
 }
 void launch_jacobian(hipStream_t st, const Dims& d, int prec, const int8_t* s, const void* tact,
                      long n, void* O, int P, long ld) {
     if (n <= 0) return;
-    if (prec == 0) jac_rows<double, false, false>(st, d, s, tact, n, n, O, P, ld, nullptr);
-    else jac_rows<float, false, false>(st, d, s, tact, n, n, O, P, ld, nullptr);
+    if (prec == 0) jac_rows<double, false>(st, d, s, tact, n, n, O, P, ld, nullptr);
+    else jac_rows<float, false>(st, d, s, tact, n, n, O, P, ld, nullptr);
 }
 // `n` rows of a centred, scaled Jacobian over nmean samples with column sums cs
 void launch_jacobian_centred(hipStream_t st, const Dims& d, int prec, const int8_t* s,
                              const void* tact, long n, long nmean, void* O, int P, long ld,
-                             const double* cs, bool split) {
+                             const double* cs) {
     if (n <= 0) return;
-    if (prec == 0) jac_rows<double, true, false>(st, d, s, tact, n, nmean, O, P, ld, cs);
-    else if (split) jac_rows<float, true, true>(st, d, s, tact, n, nmean, O, P, ld, cs);
-    else jac_rows<float, true, false>(st, d, s, tact, n, nmean, O, P, ld, cs);
+    if (prec == 0) jac_rows<double, true>(st, d, s, tact, n, nmean, O, P, ld, cs);
+    else jac_rows<float, true>(st, d, s, tact, n, nmean, O, P, ld, cs);
+}
+// all n rows as operand fragments of the BF16 Gram, (n + 31) / 32 * 32 rows
+void launch_jacobian_frags(hipStream_t st, const Dims& d, const int8_t* s, const float* tact, long n,
+                           void* F, int P, long ld, const double* cs) {
+    const int nct = (int)(ld / 16), nkb = (int)((n + 31) / 32);
+    int kbs = 16;  // k-blocks per wave: enough blocks first
+    while (kbs > 1 && (long)((nct + 3) / 4) * ((nkb + kbs - 1) / kbs) < 2048) kbs /= 2;
+    k_jac_frags<<<dim3((nct + 3) / 4, (nkb + kbs - 1) / kbs), 256, 0, st>>>(
+        d, s, tact, n, nkb, kbs, 1.0 / (double)n, 1.0 / sqrt((double)n), P, nct, cs, (uint4*)F);
 }
 
 void launch_center_cols(hipStream_t st, double* O, long n, long ld, int P, double* cs,
@@ -754,8 +808,16 @@ void launch_center_cols(hipStream_t st, double* O, long n, long ld, int P, doubl
     k_center_scale<<<g2, 256, 0, st>>>(O, n, ld, P, cs, vec);
 }
 
-int gram_tiles(int P) {
-    const int nt = (P + 127) / 128;
+// Edge of the BF16 Gram's tiles: 256 where nothing reads the mirrored half (a tile on
+// the diagonal holds two of G's 128 x 128 tiles of one triangle) and they are enough
+// for half the compute units (4,096 samples: P = 4,224, 153 tiles of 256, 271 us, 326
+// with 128; 3,320, 91 tiles, 254, 197 with 128).
+int gram_edge(int P, bool mirror) {
+    const int nt = (P + 255) / 256;
+    return !mirror && nt * (nt + 1) / 2 >= 128 ? 256 : 128;
+}
+int gram_tiles(int P, int edge) {
+    const int nt = (P + edge - 1) / edge;
     return nt * (nt + 1) / 2;
 }
 // Tile order, XCD-aware.  The hardware deals consecutive blocks to the 8 XCDs
@@ -766,8 +828,8 @@ int gram_tiles(int P) {
 // instead of each streaming a panel of its own.  Every tile appears once; the
 // ragged end (XCDs with fewer tiles) is filled in order.
 constexpr int GT_XCD = 8, GT_SUPER = 8;
-void fill_gram_tiles(int P, int* host_tiles) {
-    const int nt = (P + 127) / 128, ns = (nt + GT_SUPER - 1) / GT_SUPER;
+void fill_gram_tiles(int P, int edge, int* host_tiles) {
+    const int nt = (P + edge - 1) / edge, ns = (nt + GT_SUPER - 1) / GT_SUPER;
     std::vector<std::vector<int>> seq(GT_XCD);
     int sid = 0;
     for (int A = 0; A < ns; ++A)
@@ -814,12 +876,30 @@ void launch_gram_sliced(hipStream_t st, const double* A, long n, long ld, int P,
     k_gram_slices<<<(unsigned)(ntiles * slices), 256, 0, st>>>(A, n, ld, ntiles, rps, tiles, part);
     k_gram_fin<<<(unsigned)(ntiles * 256), 256, 0, st>>>(part, ntiles, slices, tiles, P, ld, G);
 }
-void launch_gram(hipStream_t st, int prec, const void* A, long n, long ld, int P, void* G,
-                 const int* tiles, int ntiles, bool mirror) {
-    if (prec == 1)
-        k_gram<float><<<ntiles, 256, 0, st>>>((const float*)A, n, ld, P, (float*)G, tiles, mirror);
-    else  // (split pairs from the centring; ld a multiple of 128: panel loads stay in their row)
-        k_gram_split<<<ntiles, 256, 0, st>>>((const uint32_t*)A, n, ld, P, (float*)G, tiles, mirror);
+void launch_gram(hipStream_t st, const float* A, long n, long ld, int P, float* G, const int* tiles,
+                 int ntiles, bool mirror) {
+    k_gram<float><<<ntiles, 256, 0, st>>>(A, n, ld, P, G, tiles, mirror);
+}
+// Up to one tile of 128 per compute unit, four blocks of 64 x 64 share it: they wait for
+// the same loads with a quarter of the products each.  4,096 samples: 860 columns (28
+// tiles) 43 us, 106 with whole tiles; 2,143 (153) 99, 115; 3,320 (351) 205, 179.
+constexpr int GRAM_SMALL = 256;
+void launch_gram_frags(hipStream_t st, const void* F, long n, long ld, int P, float* G,
+                       const int* tiles, int ntiles, int edge, bool mirror) {
+    const int nkb = (int)((n + 31) / 32), nct = (int)(ld / 16);
+    const u32x4* f = (const u32x4*)F;
+    if (edge == 256) {
+        const size_t lds = 2 * 32 * 2048;
+        (void)hipFuncSetAttribute((const void*)k_gram_frags<2, 4, 8, 4, 1, 1>,
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        k_gram_frags<2, 4, 8, 4, 1, 1><<<ntiles, 512, lds, st>>>(f, nkb, nct, ld, P, G, tiles, mirror);
+    } else if (ntiles > GRAM_SMALL) {
+        k_gram_frags<2, 2, 4, 4, 2, 1><<<ntiles, 256, 2 * 16 * 2048, st>>>(f, nkb, nct, ld, P, G,
+                                                                          tiles, mirror);
+    } else {
+        k_gram_frags<2, 2, 2, 2, 2, 2><<<4 * ntiles, 256, 2 * 8 * 2048, st>>>(f, nkb, nct, ld, P, G,
+                                                                             tiles, mirror);
+    }
 }
 void launch_dense_matvec(hipStream_t st, int prec, const void* G, int P, long ld, const double* v,
                          double* out, double* dpart, const CgScalars* sc, int tri, void* scratch) {

@@ -250,17 +250,23 @@ void launch_cg_small(hipStream_t st, const Dims& d, const QgtBatch& q, const voi
 // entry is stored as the BF16 pair (hi << 16) | lo that the BF16 Gram reads
 void launch_jacobian_centred(hipStream_t st, const Dims& d, int prec, const int8_t* s,
                              const void* tact, long n, long nmean, void* O, int P, long ld,
-                             const double* cs, bool split);
+                             const double* cs);
+// the same for all n samples as operand fragments of the BF16 Gram
+void launch_jacobian_frags(hipStream_t st, const Dims& d, const int8_t* s, const float* tact, long n,
+                           void* F, int P, long ld, const double* cs);
 void launch_jacobian(hipStream_t st, const Dims& d, int prec, const int8_t* s, const void* tact,
                      long n, void* O, int P, long ld);
 // centre and scale the columns of the FP64 O [n][ld] (first P); scratch holds
 // column-sum partials, at least P doubles
 void launch_center_cols(hipStream_t st, double* O, long n, long ld, int P, double* cs,
                         double* scratch, size_t scratch_bytes);
-int gram_tiles(int P);
-void fill_gram_tiles(int P, int* host_tiles);
-void launch_gram(hipStream_t st, int prec, const void* A, long n, long ld, int P, void* G,
-                 const int* tiles, int ntiles, bool mirror);
+int gram_edge(int P, bool mirror);  // BF16 form's tile edge
+int gram_tiles(int P, int edge = 128);
+void fill_gram_tiles(int P, int edge, int* host_tiles);
+void launch_gram(hipStream_t st, const float* A, long n, long ld, int P, float* G, const int* tiles,
+                 int ntiles, bool mirror);
+void launch_gram_frags(hipStream_t st, const void* F, long n, long ld, int P, float* G,
+                       const int* tiles, int ntiles, int edge, bool mirror);
 // FP64 Gram over row slices (deterministic slice sum); slices from gram_slices,
 // part: gram_part_bytes(ntiles, slices) of scratch (slices == 1: the plain kernel)
 int gram_slices(int ntiles, long n);
