@@ -203,53 +203,76 @@ __global__ __launch_bounds__(256) void k_jac_rows(Dims d, const int8_t* __restri
 }
 
 // G[p][q] = sum_k A[k][p] A[k][q] for the upper block triangle, mirrored where the
-// products read the lower one too.
-// Block = 4 waves = a 128 x 128 tile of G; each wave a 64 x 64 quarter as
-// 4 x 4 MFMA tiles of 16 x 16 sharing its operand fragments.
-template <typename R>
-__global__ __launch_bounds__(256) void k_gram(const R* __restrict__ A, long n, long ld, int P,
-                                              R* __restrict__ G, const int* __restrict__ tiles,
-                                              bool mirror) {
-    const int tp = tiles[2 * blockIdx.x], tq = tiles[2 * blockIdx.x + 1];
+// products read the lower one too.  Block = 4 waves = a tile of G of 32 T rows and
+// columns, SUB x SUB of them per listed 128 x 128 tile; each wave a quarter as T x T
+// MFMA tiles of 16 x 16.  The operands of the next U steps of 4 samples are loaded,
+// lanes over columns, while these U are multiplied; rows of A are whole tiles of
+// columns long.  FP32, 4,096 samples: P = 860 (28 tiles, in quarters) 135 us, 653 with
+// the loads of each step waited for; P = 3,320 (351 whole tiles) 680, 917; from some
+// thousand tiles on the waves hide the loads either way (U = 1: 8,384 columns 3.3 ms).
+template <typename R, int T, int U, int SUB>
+__global__ __launch_bounds__(256, 2) void k_gram(const R* __restrict__ A, long n, long ld, int P,
+                                                 R* __restrict__ G, const int* __restrict__ tiles,
+                                                 bool mirror) {
+    const int lt = blockIdx.x / (SUB * SUB), sub = blockIdx.x % (SUB * SUB);
+    const int lp = tiles[2 * lt], lq = tiles[2 * lt + 1];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int lr = lane & 15, lk = lane >> 4;
-    const int p0 = tp * 128 + (wave >> 1) * 64;
-    const int q0 = tq * 128 + (wave & 1) * 64;
+    const int p0 = 32 * T * (lp * SUB + sub / SUB) + (wave >> 1) * 16 * T;
+    const int q0 = 32 * T * (lq * SUB + sub % SUB) + (wave & 1) * 16 * T;
     typedef typename std::conditional<sizeof(R) == 8, v4d, v4f>::type acc_t;
-    acc_t acc[4][4];
+    acc_t acc[T][T];
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < T; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = acc_t{0, 0, 0, 0};
-    for (long k0 = 0; k0 < n; k0 += 4) {
-        const long k = k0 + lk;
-        R fa[4], fb[4];
+        for (int b = 0; b < T; ++b) acc[a][b] = acc_t{0, 0, 0, 0};
+    R na[U][T], nb[U][T];
+    auto load = [&](long k0) {
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            const long p = p0 + a * 16 + lr, q = q0 + a * 16 + lr;
-            fa[a] = (k < n && p < ld) ? A[k * ld + p] : (R)0;
-            fb[a] = (k < n && q < ld) ? A[k * ld + q] : (R)0;
-        }
+        for (int u = 0; u < U; ++u) {
+            const R* row = A + min(k0 + 4 * u + lk, n - 1) * ld + lr;
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                if constexpr (sizeof(R) == 8)
-                    acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[a], fb[b], acc[a][b], 0, 0, 0);
-                else
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[a], fb[b], acc[a][b], 0, 0, 0);
+            for (int a = 0; a < T; ++a) {
+                na[u][a] = row[p0 + 16 * a];
+                nb[u][a] = row[q0 + 16 * a];
             }
+        }
+    };
+    load(0);
+    for (long k0 = 0; k0 < n; k0 += 4 * U) {
+        R fa[U][T], fb[U][T];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int a = 0; a < T; ++a) {
+                const bool in = k0 + 4 * u + lk < n;
+                fa[u][a] = in ? na[u][a] : (R)0;
+                fb[u][a] = nb[u][a];
+            }
+        load(k0 + 4 * U);  // (past n: the last row)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int a = 0; a < T; ++a)
+#pragma unroll
+                for (int b = 0; b < T; ++b) {
+                    if constexpr (sizeof(R) == 8)
+                        acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[u][a], fb[u][b], acc[a][b], 0, 0, 0);
+                    else
+                        acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[u][a], fb[u][b], acc[a][b], 0, 0, 0);
+                }
     }
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < T; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
+        for (int b = 0; b < T; ++b)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const long p = p0 + a * 16 + acc_row<R>(lk, i), q = q0 + b * 16 + lr;
                 if (p < P && q < P) {
                     G[p * ld + q] = acc[a][b][i];
-                    if (mirror && tp != tq) G[q * ld + p] = acc[a][b][i];
+                    if (mirror && lp != lq) G[q * ld + p] = acc[a][b][i];
                 }
             }
 }
@@ -868,7 +891,7 @@ size_t gram_part_bytes(int ntiles, int slices) {
 void launch_gram_sliced(hipStream_t st, const double* A, long n, long ld, int P, double* G,
                         const int* tiles, int ntiles, int slices, double* part) {
     if (slices <= 1 || !part) {
-        k_gram<double><<<ntiles, 256, 0, st>>>(A, n, ld, P, G, tiles, true);
+        k_gram<double, 4, 1, 1><<<ntiles, 256, 0, st>>>(A, n, ld, P, G, tiles, true);
         return;
     }
     long rps = (n + slices - 1) / slices;
@@ -876,14 +899,18 @@ void launch_gram_sliced(hipStream_t st, const double* A, long n, long ld, int P,
     k_gram_slices<<<(unsigned)(ntiles * slices), 256, 0, st>>>(A, n, ld, ntiles, rps, tiles, part);
     k_gram_fin<<<(unsigned)(ntiles * 256), 256, 0, st>>>(part, ntiles, slices, tiles, P, ld, G);
 }
+// Up to one tile of 128 per compute unit, four blocks of 64 x 64 share it: they wait for
+// the same loads with a quarter of the products each.  4,096 samples, BF16 form: 860
+// columns (28 tiles) 43 us, 106 with whole tiles; 2,143 (153) 99, 115; 3,320 (351) 205,
+// 179; FP32: 135; 360; 694, 680.
+constexpr int GRAM_SMALL = 256;
 void launch_gram(hipStream_t st, const float* A, long n, long ld, int P, float* G, const int* tiles,
                  int ntiles, bool mirror) {
-    k_gram<float><<<ntiles, 256, 0, st>>>(A, n, ld, P, G, tiles, mirror);
+    if (ntiles > GRAM_SMALL)
+        k_gram<float, 4, 1, 1><<<ntiles, 256, 0, st>>>(A, n, ld, P, G, tiles, mirror);
+    else
+        k_gram<float, 2, 8, 2><<<4 * ntiles, 256, 0, st>>>(A, n, ld, P, G, tiles, mirror);
 }
-// Up to one tile of 128 per compute unit, four blocks of 64 x 64 share it: they wait for
-// the same loads with a quarter of the products each.  4,096 samples: 860 columns (28
-// tiles) 43 us, 106 with whole tiles; 2,143 (153) 99, 115; 3,320 (351) 205, 179.
-constexpr int GRAM_SMALL = 256;
 void launch_gram_frags(hipStream_t st, const void* F, long n, long ld, int P, float* G,
                        const int* tiles, int ntiles, int edge, bool mirror) {
     const int nkb = (int)((n + 31) / 32), nct = (int)(ld / 16);
