@@ -282,8 +282,9 @@ __global__ __launch_bounds__(256, 2) void k_gram(const R* __restrict__ A, long n
 // rows), the tile's partial written in tile order [128][128]; k_gram_fin sums
 // the slices in order (deterministic) and writes G with the lower triangle
 // mirrored (within a diagonal tile only entries on or above the diagonal are
-// taken, so G is exactly symmetric).
-__global__ __launch_bounds__(256) void k_gram_slices(const double* __restrict__ A, long n, long ld,
+// taken, so G is exactly symmetric).  The next step's operands are loaded while
+// this one's are multiplied.
+__global__ __launch_bounds__(256, 2) void k_gram_slices(const double* __restrict__ A, long n, long ld,
                                                      int ntiles, long rows_per_slice,
                                                      const int* __restrict__ tiles,
                                                      double* __restrict__ part) {
@@ -300,14 +301,25 @@ __global__ __launch_bounds__(256) void k_gram_slices(const double* __restrict__ 
     for (int a = 0; a < 4; ++a)
 #pragma unroll
         for (int b = 0; b < 4; ++b) acc[a][b] = v4d{0, 0, 0, 0};
+    double na[4], nb[4];
+    auto load = [&](long k0) {
+        const double* row = A + min(k0 + lk, r1 - 1) * ld + lr;
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+            na[a] = row[p0 + a * 16];
+            nb[a] = row[q0 + a * 16];
+        }
+    };
+    if (r0 < r1) load(r0);  // (a slice past the rows is zero)
     for (long k0 = r0; k0 < r1; k0 += 4) {
-        const long k = k0 + lk;
         double fa[4], fb[4];
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
-            fa[a] = k < r1 ? A[k * ld + p0 + a * 16 + lr] : 0.0;
-            fb[a] = k < r1 ? A[k * ld + q0 + a * 16 + lr] : 0.0;
+            fa[a] = k0 + lk < r1 ? na[a] : 0.0;
+            fb[a] = nb[a];
         }
+        load(k0 + 4);  // (past r1: the last row)
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int a = 0; a < 4; ++a)
 #pragma unroll
