@@ -255,7 +255,8 @@ def dense_qgt_measure(torch, precision="fp32", repeats=2):
       Gram matrix: N_s P (P + 1) flops (the symmetric product) on the FP32 matrix
         cores; in the BF16 form three BF16 products per FP32 product (hi hi + hi lo
         + lo hi), 3 N_s P (P + 1) flops on the BF16 matrix cores,
-      dense product: P^2 4 bytes read (the matrix once; HBM)."""
+      dense product: P (P + 1) / 2 4 bytes read (the symmetric matrix's upper
+        triangle once; HBM)."""
     from paper_2112_10526_amd.nqs import VMCState
     w = synth.WORKLOADS["heis1d_n64"]
     st = VMCState.from_workload(w, precision=precision, qgt="jacobian_dense")
@@ -265,7 +266,7 @@ def dense_qgt_measure(torch, precision="fp32", repeats=2):
             if precision == "bf16" else ("mfma", Ns * P * (P + 1.0), "TFLOP/s", PEAK["mfma_fp32"]))
     work = {"jacobian": ("hbm", Ns * P * 4.0, "GB/s", PEAK["hbm"]),
             "gram": gram,
-            "dense_matvec": ("hbm", P * P * 4.0, "GB/s", PEAK["hbm"])}
+            "dense_matvec": ("hbm", P * (P + 1) / 2 * 4.0, "GB/s", PEAK["hbm"])}
     best = {}
     for _ in range(repeats):
         st.load_samples(s)  # (a solve marks the batch and its gradient as used)

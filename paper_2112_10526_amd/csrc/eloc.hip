@@ -18,10 +18,10 @@
 // Bound by the vector ALU: a factor is three operations in this order (the sign times
 // the activation, the fused multiply-add, the product), so what a hidden unit costs
 // besides is spread over SB samples and ICH chunks, and the waves of a compute unit
-// come from item groups too.  16,384 samples, with theta: Heisenberg 16x16, 1,024
-// hidden units, FP32: 999 us (1,500 with one wave over all bonds of 8 samples and
-// activations read out of the lanes; its operations alone take 730); TFIM 10x10, 200
-// hidden units, FP64: 114 us (125), 16x16, 256 hidden units: 313 us (437).
+// come from item groups too.  16,384 samples, this kernel alone: Heisenberg 16x16,
+// 1,024 hidden units, FP32: 842 us (1,340 with one wave over all bonds of 8 samples and
+// activations read out of the lanes; its 2.6e10 operations alone take 470 at the
+// measured rate of FP32 multiply-adds); TFIM 10x10, 200 hidden units, FP64: 77 us (91).
 #include "kernels.h"
 
 namespace nqs {
@@ -229,7 +229,7 @@ static void launch_k(hipStream_t st, const Dims& d, const Tables& t, const HamDe
                      const int8_t* s, const void* tact, long n, double* out, int IW) {
     constexpr int JU = 16 / sizeof(R);
     // hidden rows of the table staged per chunk: at most 32 KiB, so that five blocks
-    // fit a compute unit (Heisenberg 16x16: 999 us, 1,186 with 64 KiB); at least JU,
+    // fit a compute unit (Heisenberg 16x16: 842 us, 1,029 with 64 KiB); at least JU,
     // which for the most sites, 4,096, are 64 KiB
     int JC = 64;
     while (JC > JU && (size_t)JC * d.Nw * sizeof(R) > 32768) JC /= 2;
@@ -241,8 +241,8 @@ static void launch_k(hipStream_t st, const Dims& d, const Tables& t, const HamDe
 
 // Samples and chunks per wave.  One chunk where the items fit it (7x7 TFIM, FP64: 44
 // us, 53 with room for two); eight samples only where the waves still fill every SIMD
-// eight deep (Heisenberg 16x16, FP32: 16,384 samples 999 us, 1,075 with four; 8,192
-// samples 605, 582 with four; 10x10, 2,000 samples 57, 40 with four).
+// eight deep (Heisenberg 16x16, FP32: 16,384 samples 842 us, 918 with four; 8,192
+// samples 526, 503 with four; 10x10, 2,000 samples with theta 57, 40 with four).
 template <typename R, int KIND>
 static void launch_items(hipStream_t st, const Dims& d, const Tables& t, const HamDev& H,
                          const int8_t* s, const void* tact, long n, double* out) {
