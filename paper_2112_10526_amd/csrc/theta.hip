@@ -80,12 +80,14 @@ __device__ __forceinline__ float act(float th, int col, int M) {
 // columns, its waves taking tiles w, w + nw, ..., and sums ln cosh over them: the
 // factors cosh x are multiplied over 16 columns before one logarithm.  G is
 // exact (no test inside the products: with one, the compiler moved every
-// accumulator between register files around each MFMA); MULTI: lattices too wide
-// for that walk the sites in chunks of G groups (the last one zero-padded), W
-// reloaded for each step of rows.
+// accumulator between register files around each MFMA), past 8 groups the next of 10,
+// 12, 14 and 17 with zero weights; MULTI: wider lattices walk the sites in chunks of G
+// groups for all rows of a block, W reloaded for each.
 // 16,384 x (100 sites, 200 hidden units) FP64, 0.76 GFLOP (12 us at the FP64 matrix
 // rate): theta 62 -> 34 us against staging W in LDS for every 64 x 64 tile with the
 // library tanh, ln psi 289 -> 41 us against a vector dot product per hidden unit.
+// 16,384 x (256 sites, 1,024 hidden units): theta FP64 492 -> 285, FP32 200 -> 150 us
+// (409 and 314 in chunks of 8 groups), ln psi 2,886 -> 352 and 1,027 -> 248.
 // What is left is vector issue: conversions, tanh and the drain of 512 blocks.
 constexpr int TH_ST = 8;  // staging words per thread and step
 
@@ -173,7 +175,7 @@ __global__ __launch_bounds__(EPI ? 512 : 256) void k_theta(
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int k = 16 * (c * G + g) + 4 * e + lk;
-                if constexpr (MULTI) {
+                if constexpr (MULTI || G > 8) {
                     const R v = w[(size_t)min(k, d.Na - 1) * d.Mw];
                     wf[4 * g + e] = k < d.Na ? v : (R)0;
                 } else {
@@ -425,15 +427,18 @@ static void theta_g(hipStream_t st, const Dims& d, const int8_t* s, long rows, c
     const int rounds = (tiles + 7) / 8;
     const int nw = EPI ? (tiles + rounds - 1) / rounds : 4;
     const int nby = EPI ? 1 : (tiles + nw - 1) / nw;
-    const int RB = MULTI ? 32 : theta_rows(rows, nby, 512);
+    const int fit = theta_rows(rows, nby, 512);
+    const int RB = !MULTI ? fit : (!EPI && fit >= 64) ? 64 : 32;
     const size_t lds = (size_t)RB * 16 * (G | 1) + (EPI ? 8 * (size_t)nw * RB : 0);
     const dim3 grid((unsigned)((rows + RB - 1) / RB), (unsigned)nby);
-    if (RB > 16)
-        k_theta<R, G, 2, EPI, MULTI><<<grid, 64 * nw, lds, st>>>(d, s, rows, RB, Wa, dst1,
-                                                                 dst2, dst2_stride, av);
-    else
-        k_theta<R, G, 1, EPI, MULTI><<<grid, 64 * nw, lds, st>>>(d, s, rows, RB, Wa, dst1,
-                                                                 dst2, dst2_stride, av);
+    auto go = [&](auto kernel) {
+        kernel<<<grid, 64 * nw, lds, st>>>(d, s, rows, RB, Wa, dst1, dst2, dst2_stride, av);
+    };
+    if constexpr (MULTI && !EPI) {  // (all of a block's rows at once)
+        if (RB == 64) return go(k_theta<R, G, 4, EPI, MULTI>);
+    }
+    if (MULTI || RB > 16) go(k_theta<R, G, 2, EPI, MULTI>);
+    else if constexpr (!MULTI) go(k_theta<R, G, 1, EPI, MULTI>);
 }
 template <typename R, int EPI>
 static void theta_r(hipStream_t st, const Dims& d, const int8_t* s, long rows, const void* Wa,
@@ -449,6 +454,10 @@ static void theta_r(hipStream_t st, const Dims& d, const int8_t* s, long rows, c
         case 6: return THETA_G(6, false);
         case 7: return THETA_G(7, false);
         case 8: return THETA_G(8, false);
+        case 9: case 10: return THETA_G(10, false);
+        case 11: case 12: return THETA_G(12, false);
+        case 13: case 14: return THETA_G(14, false);
+        case 15: case 16: case 17: return THETA_G(17, false);
         default: return THETA_G(8, true);
     }
 #undef THETA_G
