@@ -34,6 +34,26 @@ __device__ __forceinline__ double recip(double x) {
 }
 __device__ __forceinline__ float recip(float x) { return __builtin_amdgcn_rcpf(x); }
 
+// The reciprocals of f[0 .. Q-1] from their running products pre[q] = f[0] .. f[q]
+// (FP64: one reciprocal and two products each, where the instruction takes four times
+// as long as a product and needs two Newton steps: 4 sweeps of 4,096 chains, 10x10, 200
+// hidden units, 327 -> 278 us), or one by one (FP32)
+template <int Q>
+__device__ __forceinline__ void recips(const double (&f)[Q], const double (&pre)[Q], double (&r)[Q]) {
+    double inv = recip(pre[Q - 1]);
+#pragma unroll
+    for (int q = Q - 1; q > 0; --q) {
+        r[q] = inv * pre[q - 1];
+        inv *= f[q];
+    }
+    r[0] = inv;
+}
+template <int Q>
+__device__ __forceinline__ void recips(const float (&f)[Q], const float (&)[Q], float (&r)[Q]) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) r[q] = recip(f[q]);
+}
+
 // Sum / product over the chain's lanes, in every lane of the chain: rows of 16 lanes,
 // then pairs of rows, then (one chain per wave) the two halves.  With two chains per
 // wave (64 / CPW consecutive lanes each) one cross-lane reduction and one
@@ -189,12 +209,13 @@ __global__ __launch_bounds__(256) void k_sample(Dims d, const R* __restrict__ Tt
             __builtin_amdgcn_sched_barrier(0);  // (the reads stay ahead of the decision)
             bool accept;
             if (RULE == 0) {
-                R f[Q];
+                R f[Q], pre[Q];
                 R prod = (R)1;
 #pragma unroll
                 for (int qq = 0; qq < Q; ++qq) {
                     f[qq] = (R)1 - (R)sa * t[qq] * Tv[qq];
                     prod *= f[qq];
+                    pre[qq] = prod;
                 }
                 const R kf = sa < 0 ? ka_c.v[1] : ka_c.v[0];
                 if constexpr (sizeof(R) == 8) {
@@ -205,8 +226,10 @@ __global__ __launch_bounds__(256) void k_sample(Dims d, const R* __restrict__ Tt
                     accept = cur.u < 2.0f * lr;
                 }
                 if (accept) {
+                    R r[Q];
+                    recips(f, pre, r);
 #pragma unroll
-                    for (int qq = 0; qq < Q; ++qq) t[qq] = (t[qq] - (R)sa * Tv[qq]) * recip(f[qq]);
+                    for (int qq = 0; qq < Q; ++qq) t[qq] = (t[qq] - (R)sa * Tv[qq]) * r[qq];
                     s[cur.ia] = (int8_t)-sa;  // every lane of the chain stores the same value
                     if (nxt.ia == cur.ia) sa_n = -sa;
                 }
@@ -214,7 +237,7 @@ __global__ __launch_bounds__(256) void k_sample(Dims d, const R* __restrict__ Tt
                 // the ratio is formed for every chain of the wave (the cross-lane
                 // reduction runs outside divergent code); a bond with equal spins
                 // is the identity move, accepted with ratio 1
-                R g[Q], TT[Q], Td[Q];
+                R g[Q], pre[Q], TT[Q], Td[Q];
                 R prod = (R)1;
 #pragma unroll
                 for (int qq = 0; qq < Q; ++qq) {
@@ -223,6 +246,7 @@ __global__ __launch_bounds__(256) void k_sample(Dims d, const R* __restrict__ Tt
                     Td[qq] = (R)sa * (ta - tb);
                     g[qq] = TT[qq] - t[qq] * Td[qq];
                     prod *= g[qq];
+                    pre[qq] = prod;
                 }
                 const R ka = sa < 0 ? ka_c.v[1] : ka_c.v[0], kb = sb < 0 ? kb_c.v[1] : kb_c.v[0];
                 bool take;
@@ -236,8 +260,10 @@ __global__ __launch_bounds__(256) void k_sample(Dims d, const R* __restrict__ Tt
                 const bool ident = sa == sb;
                 accept = ident || take;
                 if (!ident && take) {
+                    R r[Q];
+                    recips(g, pre, r);
 #pragma unroll
-                    for (int qq = 0; qq < Q; ++qq) t[qq] = (t[qq] * TT[qq] - Td[qq]) * recip(g[qq]);
+                    for (int qq = 0; qq < Q; ++qq) t[qq] = (t[qq] * TT[qq] - Td[qq]) * r[qq];
                     s[cur.ia] = (int8_t)sb;
                     s[cur.ib] = (int8_t)sa;
                     sa_n = nxt.ia == cur.ia ? sb : nxt.ia == cur.ib ? sa : sa_n;
@@ -265,8 +291,8 @@ __global__ __launch_bounds__(256) void k_sample(Dims d, const R* __restrict__ Tt
 // Two chains per wave when the chains pair up and a lane's registers allow (FP32 up to
 // 8 x 2 hidden units per lane, FP64 up to 4 x 2).  FP64 takes one chain per wave below
 // 2,048 chains, where the shorter chain of operations counts and not their number
-// (10x10, 200 hidden units, 4 sweeps: 1,024 chains 171 us, 207 in pairs; 4,096 chains
-// 349, 328 in pairs); in FP32 the grouping fixes the rounding, so it stays.
+// (10x10, 200 hidden units, 4 sweeps: 1,024 chains 161 us, 187 in pairs; 4,096 chains
+// 325, 278 in pairs); in FP32 the grouping fixes the rounding, so it stays.
 int sampler_lanes(int QM, int prec, int C) {
     const bool pair = prec == 0 ? QM <= 4 && C >= 2048 : QM <= 8;
     return pair && C % 2 == 0 ? 32 : 64;
