@@ -19,9 +19,10 @@
 // the activation, the fused multiply-add, the product), so what a hidden unit costs
 // besides is spread over SB samples and ICH chunks, and the waves of a compute unit
 // come from item groups too.  16,384 samples, this kernel alone: Heisenberg 16x16,
-// 1,024 hidden units, FP32: 842 us (1,340 with one wave over all bonds of 8 samples and
+// 1,024 hidden units, FP32: 787 us (1,340 with one wave over all bonds of 8 samples and
 // activations read out of the lanes; its 2.6e10 operations alone take 470 at the
-// measured rate of FP32 multiply-adds); TFIM 10x10, 200 hidden units, FP64: 77 us (91).
+// measured rate of FP32 multiply-adds; at most 128 registers for four waves per
+// SIMD, 842 with 138 and three); TFIM 10x10, 200 hidden units, FP64: 77 us (91).
 #include "kernels.h"
 
 namespace nqs {
@@ -68,7 +69,7 @@ __device__ __forceinline__ void stage_rows(R* __restrict__ dst, const R* __restr
 }
 
 template <typename R, int KIND, int SB, int ICH>
-__global__ __launch_bounds__(256) void k_eloc(Dims d, const R* __restrict__ Tj,
+__global__ __launch_bounds__(256, sizeof(R) == 4 ? 4 : 1) void k_eloc(Dims d, const R* __restrict__ Tj,
                                               const R* __restrict__ Ks, HamDev H,
                                               const int8_t* __restrict__ s,
                                               const R* __restrict__ tact, long n,
@@ -229,7 +230,8 @@ static void launch_k(hipStream_t st, const Dims& d, const Tables& t, const HamDe
                      const int8_t* s, const void* tact, long n, double* out, int IW) {
     constexpr int JU = 16 / sizeof(R);
     // hidden rows of the table staged per chunk: at most 32 KiB, so that five blocks
-    // fit a compute unit (Heisenberg 16x16: 842 us, 1,029 with 64 KiB); at least JU,
+    // fit a compute unit (Heisenberg 16x16 with three waves per SIMD: 842 us, 1,029
+    // with 64 KiB); at least JU,
     // which for the most sites, 4,096, are 64 KiB
     int JC = 64;
     while (JC > JU && (size_t)JC * d.Nw * sizeof(R) > 32768) JC /= 2;
@@ -241,7 +243,7 @@ static void launch_k(hipStream_t st, const Dims& d, const Tables& t, const HamDe
 
 // Samples and chunks per wave.  One chunk where the items fit it (7x7 TFIM, FP64: 44
 // us, 53 with room for two); eight samples only where the waves still fill every SIMD
-// eight deep (Heisenberg 16x16, FP32: 16,384 samples 842 us, 918 with four; 8,192
+// eight deep (Heisenberg 16x16, FP32: 16,384 samples 787 us, 918 with four; 8,192
 // samples 526, 503 with four; 10x10, 2,000 samples with theta 57, 40 with four).
 template <typename R, int KIND>
 static void launch_items(hipStream_t st, const Dims& d, const Tables& t, const HamDev& H,
