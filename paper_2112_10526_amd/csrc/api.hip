@@ -367,19 +367,22 @@ void derive(nqs_ctx* c) {
         c->Bx = c->Ns > 1024 ? c->Ns : 1024;
         c->ksplit = (int)((c->Bx + 255) / 256);
         c->Pld = round_up(c->Pd, 128);
-        c->ntiles = gram_tiles(c->Pd);
+        c->Ple = round_up(2 * (long)c->P, 128);
+        // (every model sets all of them: the context may have held another model before)
+        c->tri = 0;
+        c->gedge = 128;
+        c->gS = c->hS = 1;
+        c->Plc = 0;
         if (c->cplx) {  // Re G and Im G are P x P
             c->Plc = round_up((long)c->P, 128);
-            c->ntiles = gram_tiles((int)c->P);
+            c->ntiles = gram_tiles((int)c->P, c->gedge);
             c->hS = h_gram_slices(c->ntiles, c->Ns, c->ncu);
-        }
-        c->gS = (!c->cplx && (c->symm || c->prec == 0)) ? gram_slices(c->ntiles, c->Ns) : 1;
-        c->Ple = round_up(2 * (long)c->P, 128);
-        if (!c->cplx) {
+        } else {
             const size_t des = c->symm ? 8 : esize(c->prec);
             c->tri = dense_tri(c->Pd, des, des * (size_t)c->Ns * c->Pld);
-            c->gedge = !c->symm && c->prec == 2 ? gram_edge(c->Pd, c->tri == 0) : 128;
+            if (!c->symm && c->prec == 2) c->gedge = gram_edge(c->Pd, c->tri == 0);
             c->ntiles = gram_tiles(c->Pd, c->gedge);
+            if (c->symm || c->prec == 0) c->gS = gram_slices(c->ntiles, c->Ns);
         }
         long nd = (long)d.Ma * d.Na / 256 + 2;
         const long nd2 = c->Bx / 64 + 2, nd3 = (long)c->Pd / 4 + 2;
