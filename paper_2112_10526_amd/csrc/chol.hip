@@ -25,53 +25,43 @@ namespace nqs {
 constexpr int CH_NB = 32;
 constexpr int CH_XD = 33;   // LDS row of a 32-column matrix
 
-// Elimination of the 32 x 32 block next to the identity, one wave, all in registers:
-// lane c < 32 holds column c of the (symmetric) block, lane 32 + c column c of the
-// identity, register i row i.  Step j takes A_ij / d_j times row j out of every row
-// i > j; column j's entries reach all lanes as scalars (readlane), so a step's chain
-// is a pivot, its reciprocal (hardware estimate, two Newton steps) and one product.
-// Scaling row j by 1 / sqrt(d_j) then gives L^T on the left and L^-1 on the right.
+// Cholesky elimination of the 32 x 32 block next to the identity, one wave, all in
+// registers: lane c < 32 holds column c of the (symmetric) block, lane 32 + c column c
+// of the identity, register i row i.  Step j scales row j by 1 / sqrt(d_j) (hardware
+// estimate, two Newton steps, the second with the product's low part: half a unit) and
+// takes l_i times it out of every row i > j, l_i being the scaled row's entry in lane i
+// (readlane).  That leaves L^T on the left and L^-1 on the right.  A_ic and A_ci lose
+// the same product l_i l_c, so the block stays symmetric to the bit: with A_ij times
+// (A_jc / d_j) its halves part by roundings that the multipliers of a nearly singular
+// block blow up (48 parameters, 30 samples, shift 1e-10: mean residual of the solve 134
+// x 2^-53 |A| |x|, 7 here).
 // Returns false if a pivot is not positive.
 __device__ __forceinline__ bool chol_block32(double (&a)[CH_NB]) {
-    const int c = threadIdx.x & 31;
     bool ok = true;
-    double dd = 1.0;  // lane c: pivot c
 #pragma unroll
     for (int j = 0; j < CH_NB; ++j) {
         double d = readlane(a[j], j);
         const bool pos = d > 0.0 && isfinite(d);
         ok = ok && pos;
         d = pos ? d : 1.0;
-        double r = __builtin_amdgcn_rcp(d);
-        r = fma(fma(-d, r, 1.0), r, r);
-        r = fma(fma(-d, r, 1.0), r, r);
-        const double t = -a[j] * r;
-        if (c == j) dd = d;
+        double h = __builtin_amdgcn_rsq(d), t = d * h;
+        h = fma(0.5 * h, fma(-t, h, 1.0), h);
+        t = d * h;
+        const double e = fma(-fma(d, h, -t), h, fma(-t, h, 1.0));  // 1 - d h^2
+        a[j] *= fma(0.5 * h, e, h);
         // (scalars in groups: one at a time, each product waits for its own readlane)
 #pragma unroll
         for (int i0 = j + 1; i0 < CH_NB; i0 += 8) {
-            double v[8];
+            double l[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u)
-                if (i0 + u < CH_NB) v[u] = readlane(a[i0 + u], j);
+                if (i0 + u < CH_NB) l[u] = readlane(a[j], i0 + u);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int u = 0; u < 8; ++u)
-                if (i0 + u < CH_NB) a[i0 + u] = fma(v[u], t, a[i0 + u]);
+                if (i0 + u < CH_NB) a[i0 + u] = fma(-l[u], a[j], a[i0 + u]);
         }
     }
-    // 1 / sqrt of every lane's pivot: hardware estimate, two coupled Newton steps
-    double h = __builtin_amdgcn_rsq(dd), g = dd * h;
-    h *= 0.5;
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const double e = fma(-h, g, 0.5);
-        g = fma(g, e, g);
-        h = fma(h, e, h);
-    }
-    const double rs = 2.0 * h;
-#pragma unroll
-    for (int j = 0; j < CH_NB; ++j) a[j] *= readlane(rs, j);
     return ok;
 }
 
@@ -171,10 +161,8 @@ __global__ __launch_bounds__(256) void k_chol_step(double* __restrict__ A, int n
     double y = 0.0;  // y_k = L_kk^-1 f_k, by the last wave's lanes
     const int yl = tid - 192;
     if (yl >= 0 && yl < CH_NB) {
-        double a[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int m = 0; m < CH_NB; ++m) a[m & 3] = fma(Y[yl][m], yk[m], a[m & 3]);  // (Y lower)
-        y = (a[0] + a[1]) + (a[2] + a[3]);
+        for (int m = 0; m < CH_NB; ++m) y = fma(Y[yl][m], yk[m], y);  // (Y lower)
     }
     __syncthreads();
     if (b == 0) {
@@ -254,15 +242,17 @@ __global__ __launch_bounds__(256) void k_chol_mirror(double* __restrict__ A, int
     }
 }
 
-// x_k = Yinv_k^T s_k by the first 32 lanes (s in LDS), into xk
+// x_k = Yinv_k^T s_k by the first 32 lanes (s in LDS), into xk.  The products with an
+// inverse run in order, here and for y_k: in four partial sums a nearly singular block
+// left a residual 1.3 times as large.
 __device__ __forceinline__ void chol_back_block(const double (*Yk)[CH_NB + 1], const double* s,
                                                 double* xk) {
     const int c = threadIdx.x;
     if (c >= CH_NB) return;
-    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    double a = 0.0;
 #pragma unroll
-    for (int m = 0; m < CH_NB; ++m) a[m & 3] = fma(Yk[m][c], s[m], a[m & 3]);  // (Yinv lower)
-    xk[c] = (a[0] + a[1]) + (a[2] + a[3]);
+    for (int m = 0; m < CH_NB; ++m) a = fma(Yk[m][c], s[m], a);  // (Yinv lower)
+    xk[c] = a;
 }
 
 // L^T x = y in one workgroup, Q columns per thread (n <= 1024 Q), the columns'
