@@ -34,19 +34,37 @@ __device__ __forceinline__ double recip(double x) {
 }
 __device__ __forceinline__ float recip(float x) { return __builtin_amdgcn_rcpf(x); }
 
-// The reciprocals of f[0 .. Q-1] from their running products pre[q] = f[0] .. f[q]
-// (FP64: one reciprocal and two products each, where the instruction takes four times
-// as long as a product and needs two Newton steps: 4 sweeps of 4,096 chains, 10x10, 200
-// hidden units, 327 -> 278 us), or one by one (FP32)
+// The reciprocals of f[0 .. Q-1], in FP64 from their running products, of which
+// pre[q] = f[0] .. f[q] are at hand: one reciprocal for eight factors, two or three
+// products and one Newton step each, where the instruction takes four times as long as
+// a product and needs two Newton steps (4 sweeps of 4,096 chains, 10x10, 200 hidden
+// units, 315 -> 289 us).  The running products alone would leave up to 8 units of 2^-53;
+// the step gives the value found one by one (the same bits in 3 million factors).
+// Eight, because a factor is a multiple of 2^-106 (1 less a product of two 53-bit
+// numbers) and not 0 in an accepted move: their product can be inverted, which that of
+// 32 need not be.  FP32: one by one.
+constexpr int RC_G = 8;
 template <int Q>
 __device__ __forceinline__ void recips(const double (&f)[Q], const double (&pre)[Q], double (&r)[Q]) {
-    double inv = recip(pre[Q - 1]);
-#pragma unroll
-    for (int q = Q - 1; q > 0; --q) {
-        r[q] = inv * pre[q - 1];
-        inv *= f[q];
+    if constexpr (Q == 1) {
+        r[0] = recip(f[0]);
+        return;
     }
-    r[0] = inv;
+#pragma unroll
+    for (int q0 = 0; q0 < Q; q0 += RC_G) {
+        constexpr int G = Q < RC_G ? Q : RC_G;
+        double p[G];
+#pragma unroll
+        for (int q = 0; q < G; ++q)
+            p[q] = Q <= RC_G ? pre[q] : (q > 0 ? p[q > 0 ? q - 1 : 0] * f[q0 + q] : f[q0]);
+        double inv = recip(p[G - 1]);
+#pragma unroll
+        for (int q = G - 1; q >= 0; --q) {
+            const double y = q > 0 ? inv * p[q > 0 ? q - 1 : 0] : inv;
+            r[q0 + q] = fma(fma(-f[q0 + q], y, 1.0), y, y);
+            inv *= f[q0 + q];
+        }
+    }
 }
 template <int Q>
 __device__ __forceinline__ void recips(const float (&f)[Q], const float (&)[Q], float (&r)[Q]) {
