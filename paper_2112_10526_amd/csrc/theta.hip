@@ -16,17 +16,17 @@
 
 namespace nqs {
 
-// e^{-y} for y in [0, 44] as its FP64 value `e` and as `m` = e^{-y} - 1, each with
-// its own relative accuracy: a two-term (Cody-Waite) reduction by ln 2 and the
-// Taylor polynomial of e^r - 1 (|r| <= ln 2 / 2, degree 13: the remainder is below
-// 2^-56 of the result).
-struct ExpNeg {
-    double e, m;
+// e^{-y} = 2^k e^r for y in [0, 44]: a two-term (Cody-Waite) reduction by ln 2, with what
+// rounding takes off r as rl, and c of e^r - 1 = r + r^2 / 2 + r^3 c by its Taylor
+// polynomial (|r| <= ln 2 / 2, degree 13: the remainder is below 2^-56 of the result).
+struct ExpRed {
+    double r, rl, c;
+    int k;
 };
-__device__ __forceinline__ ExpNeg exp_neg(double y) {
+__device__ __forceinline__ ExpRed exp_red(double y) {
     const double k = rint(-y * 1.4426950408889634074);
-    double r = fma(-k, 0.6931471805601177, -y);      // ln 2 to 40 bits (k times it is exact)
-    r = fma(-k, -1.7239444525614835e-13, r);  // the rest of ln 2
+    const double r0 = fma(-k, 0.6931471805601177, -y);      // ln 2 to 40 bits (exact)
+    const double r = fma(-k, -1.7239444525614835e-13, r0);  // the rest of ln 2
     double p = 1.0 / 6227020800.0;
     p = fma(p, r, 1.0 / 479001600.0);
     p = fma(p, r, 1.0 / 39916800.0);
@@ -38,9 +38,16 @@ __device__ __forceinline__ ExpNeg exp_neg(double y) {
     p = fma(p, r, 1.0 / 120.0);
     p = fma(p, r, 1.0 / 24.0);
     p = fma(p, r, 1.0 / 6.0);
-    p = fma(p, r, 0.5);
-    p = fma(p * r, r, r);  // e^r - 1
-    const double s = ldexp(1.0, (int)k);
+    return ExpRed{r, fma(-k, -1.7239444525614835e-13, r0 - r), p, (int)k};
+}
+// e^{-y} as its FP64 value `e` and as `m` = e^{-y} - 1, each with its own relative accuracy
+struct ExpNeg {
+    double e, m;
+};
+__device__ __forceinline__ ExpNeg exp_neg(double y) {
+    const ExpRed x = exp_red(y);
+    const double p = fma(fma(x.c, x.r, 0.5) * x.r, x.r, x.r);  // e^r - 1
+    const double s = ldexp(1.0, x.k);
     return ExpNeg{fma(s, p, s), fma(s, p, s - 1.0)};
 }
 __device__ __forceinline__ double recip64(double x) {
@@ -48,14 +55,27 @@ __device__ __forceinline__ double recip64(double x) {
     y = fma(fma(-x, y, 1.0), y, y);
     return fma(fma(-x, y, 1.0), y, y);
 }
-// tanh|x| = -m / (2 + m), m = e^{-2|x|} - 1 (1 past |x| = 22)
+// tanh|x| = -m / (2 + m), m = e^{-2|x|} - 1 (1 past |x| = 22).  m and 2 + m are carried
+// as sums of two numbers, so that the quotient's is the only full rounding: at most 0.7
+// units in the last place, 0.29 rms (0.84 and 0.32 for the library's; m and 2 + m rounded
+// to one number each: 2.5 and 0.93).
 __device__ __forceinline__ double tanh64(double x) {
     const double a = fabs(x);
-    const double m = exp_neg(2.0 * (a > 22.0 ? 22.0 : a)).m, d = 2.0 + m;  // d in [1, 2]
-    const double y = recip64(d);
-    double q = -m * y;
-    q = fma(fma(-d, q, -m), y, q);
-    return copysign(q, x);
+    const ExpRed g = exp_red(2.0 * (a > 22.0 ? 22.0 : a));
+    const double h = 0.5 * g.r, q2 = h * g.r;  // e^r - 1 = hi + lo
+    double hi = g.r + q2, lo = q2 - (hi - g.r);
+    lo += fma(2.0 * q2 * g.r, g.c, fma(h, g.r, -q2) + g.rl);
+    const double t = hi + lo;
+    lo -= t - hi;
+    hi = t;
+    const double s = ldexp(1.0, g.k), u = s * hi, v = s - 1.0;
+    const double m = v + u;  // (|v| >= |u|, or v = 0)
+    const double ml = fma(s, lo, (u - (m - v)) + (s - (v + 1.0)));
+    const double d = 2.0 + m, dl = (m - (d - 2.0)) + ml;
+    double y = __builtin_amdgcn_rcp(d);
+    y = fma(fma(-d, y, 1.0), y, y);
+    const double q = -m * y;
+    return copysign(fma(fma(-d, q, -m) - fma(dl, q, ml), y, q), x);
 }
 // cosh x - 1 = m^2 / (2 e^{-|x|}), m = e^{-|x|} - 1, for |x| <= 22 (larger: its value at 22)
 __device__ __forceinline__ double coshm1(double a) {
