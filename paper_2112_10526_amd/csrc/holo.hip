@@ -35,14 +35,12 @@ __device__ __forceinline__ double2 cdiv(double2 a, double2 b) {
     return make_double2((a.x * b.x + a.y * b.y) / d, (a.y * b.x - a.x * b.y) / d);
 }
 __device__ __forceinline__ double cabs2(double2 a) { return a.x * a.x + a.y * a.y; }
-// tanh(x + iy) = (sinh 2x + i sin 2y) / (cosh 2x + cos 2y), the hyperbolic pair from
-// one e^{2|x|} - 1
+// tanh(x + iy) = (sinh 2x + i sin 2y) / (cosh 2x + cos 2y)
 __device__ __forceinline__ double2 ctanh(double2 z) {
-    const double q = expm1(2.0 * fabs(z.x)), ie = 1.0 / (1.0 + q);
     double sy, cy;
     sincos(2.0 * z.y, &sy, &cy);
-    const double d = 1.0 / (0.5 * ((1.0 + q) + ie) + cy);
-    return make_double2(copysign(0.5 * (q + q * ie) * d, z.x), sy * d);
+    const double d = cosh(2.0 * z.x) + cy;
+    return make_double2(sinh(2.0 * z.x) / d, sy / d);
 }
 // cosh(x + iy) = cosh x cos y + i sinh x sin y
 __device__ __forceinline__ double2 ccosh(double2 z) {
