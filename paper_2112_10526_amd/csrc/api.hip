@@ -1258,16 +1258,12 @@ int s_issue_solve(nqs_ctx* c, double diag_shift, double tol, int maxiter) {
     return run_cg(c, NQS_QGT_JACOBIAN_DENSE, diag_shift, mi);
 }
 
-// b = a, and the host word flagged if any value is not finite
-__global__ void k_copy_finite(const double* __restrict__ a, double* __restrict__ b, long n,
-                              volatile int32_t* flag) {
+// the host word flagged if any value is not finite
+__global__ void k_check_finite(const double* __restrict__ a, long n, volatile int32_t* flag) {
     bool bad = false;
     for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < n;
-         e += (long)gridDim.x * blockDim.x) {
-        const double v = a[e];
-        b[e] = v;
-        bad = bad || !isfinite(v);
-    }
+         e += (long)gridDim.x * blockDim.x)
+        bad = bad || !isfinite(a[e]);
     if (bad) *flag = 1;
 }
 
@@ -1569,25 +1565,27 @@ int nqs_set_params(nqs_ctx* c, const double* p, int on_device) {
     int st = set_device(c);
     if (st) return st;
     const size_t np = param_doubles(c);
-    // staging: the values are checked before any parameter changes (device values as
-    // they are copied into a scratch vector, one pass and one wait; host values here)
-    double* in = c->cplx ? (double*)c->b.hmean : c->b.tmpv;
-    std::vector<double> h;
+    // the values are checked before any parameter changes: device values in a scratch
+    // vector (a runtime copy takes them from wherever the pointer leads, another device
+    // too), with one wait; host values here
+    const double* in = p;
     if (on_device) {
+        double* stage = c->cplx ? (double*)c->b.hmean : c->b.tmpv;
+        HIPCHK(c, hipMemcpyAsync(stage, p, 8 * np, hipMemcpyDefault, c->stream));
         c->h_flag[2] = 0;
         const unsigned nb = (unsigned)std::min<size_t>((np + 255) / 256, 1024);
-        k_copy_finite<<<nb, 256, 0, c->stream>>>(p, in, (long)np, &c->h_flag[2]);
+        k_check_finite<<<nb, 256, 0, c->stream>>>(stage, (long)np, &c->h_flag[2]);
         HIPCHK(c, hipStreamSynchronize(c->stream));
         if (c->h_flag[2]) return fail(c, NQS_ENUMERIC, "non-finite parameter");
+        in = stage;
     } else {
-        h.assign(p, p + np);
         for (size_t k = 0; k < np; ++k)
-            if (!std::isfinite(h[k])) return fail(c, NQS_ENUMERIC, "non-finite parameter");
-        HIPCHK(c, hipMemcpyAsync(in, h.data(), 8 * np, hipMemcpyHostToDevice, c->stream));
+            if (!std::isfinite(p[k])) return fail(c, NQS_ENUMERIC, "non-finite parameter");
     }
+    const hipMemcpyKind kind = on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
     const bool held = c->have_samples;  // the held batch's activations follow
     if (c->cplx) {
-        HIPCHK(c, hipMemcpyAsync(c->b.hp, in, 8 * np, hipMemcpyDeviceToDevice, c->stream));
+        HIPCHK(c, hipMemcpyAsync(c->b.hp, in, 8 * np, kind, c->stream));
         h_params_changed(c);
         if (held) {
             launch_h_theta(c->stream, c->N, c->M, c->b.hp, c->b.htab, c->b.samples, c->Ns, c->b.htsm,
@@ -1596,9 +1594,11 @@ int nqs_set_params(nqs_ctx* c, const double* p, int on_device) {
         }
     } else {
         if (c->symm) {  // the symmetric parameters, expanded to the plain RBM's
-            HIPCHK(c, hipMemcpyAsync(c->b.psym, in, 8 * np, hipMemcpyDeviceToDevice, c->stream));
+            HIPCHK(c, hipMemcpyAsync(c->b.psym, in, 8 * np, kind, c->stream));
             launch_symm_expand(c->stream, c->N, c->G, c->alpha, c->vb, c->hb, c->b.perms,
                                c->b.psym, c->b.tmpv);
+        } else if (!on_device) {
+            HIPCHK(c, hipMemcpyAsync(c->b.tmpv, in, 8 * np, kind, c->stream));
         }
         launch_unpack(c->stream, c->d, c->b.tmpv, c->b.Pm, (int)c->P);
         launch_tables(c->stream, c->d, c->prec, c->b.Pm, c->b.tab);
@@ -1608,7 +1608,7 @@ int nqs_set_params(nqs_ctx* c, const double* p, int on_device) {
             launch_theta(c->stream, c->d, c->prec, c->b.tab, c->b.samples, (int)c->Ns, c->b.tsm,
                          nullptr, 0);
     }
-    if (!on_device) HIPCHK(c, hipStreamSynchronize(c->stream));  // (the host copy has been read)
+    if (!on_device) HIPCHK(c, hipStreamSynchronize(c->stream));  // (p has been read)
     c->params_set = true;
     return last_launch(c);
 }

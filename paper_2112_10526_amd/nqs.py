@@ -182,24 +182,19 @@ class VMCState:
 
     # ------------------------------------------------------------------
     def set_params(self, p):
-        if self.complex:  # complex128 values, passed as (real, imaginary) pairs
-            if torch.is_tensor(p):
-                p = torch.view_as_real(self._dev(p, torch.complex128)).contiguous()
-                self._check(self.lib.nqs_set_params(self.ctx, _ptr(p), 1))
-                return
-            p = np.ascontiguousarray(np.asarray(p, dtype=np.complex128))
-            if p.size != self.n_params:
-                raise ValueError(f"expected {self.n_params} parameters")
-            self._check(self.lib.nqs_set_params(self.ctx, p.ctypes.data_as(ctypes.c_void_p), 0))
-            return
-        p = np.ascontiguousarray(np.asarray(p, dtype=np.float64)) if not torch.is_tensor(p) else p
         if torch.is_tensor(p):
-            p = self._dev(p, torch.float64)
-            self._check(self.lib.nqs_set_params(self.ctx, _ptr(p), 1))
-        else:
-            if p.size != self.n_params:
+            # complex128 values are passed as (real, imaginary) pairs
+            p = self._dev(p, torch.complex128 if self.complex else torch.float64)
+            if p.numel() < self.n_params:
                 raise ValueError(f"expected {self.n_params} parameters")
-            self._check(self.lib.nqs_set_params(self.ctx, p.ctypes.data_as(ctypes.c_void_p), 0))
+            if self.complex:
+                p = torch.view_as_real(p).contiguous()
+            self._check(self.lib.nqs_set_params(self.ctx, _ptr(p), 1))
+            return
+        p = np.ascontiguousarray(np.asarray(p, np.complex128 if self.complex else np.float64))
+        if p.size != self.n_params:
+            raise ValueError(f"expected {self.n_params} parameters")
+        self._check(self.lib.nqs_set_params(self.ctx, p.ctypes.data_as(ctypes.c_void_p), 0))
 
     def get_params(self) -> np.ndarray:
         out = np.zeros(self.n_params, dtype=np.complex128 if self.complex else np.float64)
