@@ -1353,7 +1353,10 @@ const char* nqs_last_error(const nqs_ctx* c) { return c ? c->err.c_str() : "null
 
 int nqs_set_stream(nqs_ctx* c, void* hip_stream) {
     if (!c) return NQS_EINVAL;
-    if (c->stream) HIPCHK(c, hipStreamSynchronize(c->stream));
+    const int st = set_device(c);
+    if (st) return st;
+    // (work queued on the null stream is not ordered with a non-blocking stream either)
+    HIPCHK(c, hipStreamSynchronize(c->stream));
     c->stream = (hipStream_t)hip_stream;
     return NQS_OK;
 }
