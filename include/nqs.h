@@ -251,7 +251,8 @@ int nqs_set_sampler(nqs_ctx* ctx, nqs_rule rule, int n_chains, int samples_per_c
 int nqs_set_qgt(nqs_ctx* ctx, nqs_qgt kind);
 
 /* Bytes of device workspace the current configuration needs (0 if the
- * configuration is incomplete).  This is the context's HBM footprint. */
+ * configuration is incomplete).  This is the context's HBM footprint.  A complex
+ * model's also binds with less: its Gram matrix is then formed in fewer row slices. */
 size_t nqs_workspace_bytes(const nqs_ctx* ctx);
 
 /* Bind caller-owned device memory (>= nqs_workspace_bytes, 256-byte aligned)

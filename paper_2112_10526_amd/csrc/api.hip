@@ -1526,7 +1526,12 @@ int nqs_bind_workspace(nqs_ctx* c, void* dev_ptr, size_t bytes) {
         const int st = h_check(c);
         if (st) return st;
     }
-    const size_t need = layout(c, nullptr);
+    if (c->cplx) c->hS = h_gram_slices(c->ntiles, c->Ns, c->ncu);
+    size_t need = layout(c, nullptr);
+    while (bytes < need && c->cplx && c->hS > 1) {  // (fewer slices of the Gram do as well)
+        --c->hS;
+        need = layout(c, nullptr);
+    }
     if (!dev_ptr || bytes < need)
         return fail(c, NQS_ENOMEM, "workspace needs " + std::to_string(need) + " bytes");
     if ((uintptr_t)dev_ptr % ALIGN) return fail(c, NQS_EINVAL, "workspace must be 256-byte aligned");

@@ -893,11 +893,17 @@ void launch_h_force(hipStream_t st, const double* U, long n, long ld, int P, con
 // units per row (one block fills a unit), a slice's partials counted as 5e-5 of a
 // round per tile (their write and read against the products of a whole tile);
 // slices of at least 128 rows of U.  Ten tiles, 8,192 rows: 25 slices, 250 blocks
-// in one round, 108-128 us; 16 slices, 160 blocks, 157 us.
+// in one round, 108-128 us; 16 slices, 160 blocks, 157 us.  The partials (256 KiB a tile
+// and slice) stay within 64 MiB, or those of some 2,048 blocks with slices of at least
+// 256 rows: past that a slice more saves a few percent of a round and costs as much
+// memory as half of G (64 sites, 128 units: three slices 1.74 GB, one 0.58 GB, 4 %).
 int h_gram_slices(int ntiles, long n, int ncu) {
+    int cap = 1;
+    while (cap < 16 && (long)ntiles * cap < 2048 && n / cap >= 256) cap *= 2;
+    if (cap < 256 / ntiles) cap = 256 / ntiles;
     int best = 1;
     double least = 1e30;
-    for (int S = 1; S <= 64 && (S == 1 || 2 * n / S >= 128); ++S) {
+    for (int S = 1; S <= 64 && S <= cap && (S == 1 || 2 * n / S >= 128); ++S) {
         const long rounds = ((long)ntiles * S + ncu - 1) / ncu;
         const double cost = (double)rounds / S + 5e-5 * ntiles * S;
         if (cost < least) {
