@@ -22,7 +22,7 @@ namespace {
 constexpr size_t ALIGN = 256;
 
 struct Buffers {
-    double *Pm, *grad, *x, *r, *p, *p2, *Ap, *tmpv, *gacc;
+    double *Pm, *grad, *x, *r, *p, *p2, *tmpv, *gacc;
     int32_t* bonds;
     int8_t* sub;
     Tables tab;
@@ -207,7 +207,6 @@ size_t layout(nqs_ctx* c, char* base) {
     b.r = (double*)take(8 * PV);
     b.p = (double*)take(8 * PV);
     b.p2 = (double*)take(8 * PV);
-    b.Ap = (double*)take(8 * PV);
     b.tmpv = (double*)take(8 * PVX);
     b.gacc = (double*)take(8 * PV);
     b.bonds = (int32_t*)take(8 * c->bonds.size() / 2 + 8);

@@ -38,7 +38,7 @@ struct Dims {
     int Kb;       // round_up(Na, 32): K extent of the BF16 theta operand
     int Kq;       // round_up(Na, 128): site extent of the CG operands (whole k-groups)
     int QM;       // ceil(M / 64): hidden units per lane in the sampler
-    int lpc, Q;  // the sampler\'s lanes per chain and hidden units per lane
+    int lpc, Q;  // the sampler's lanes per chain and hidden units per lane
     int vb, hb;   // visible / hidden bias present
 };
 

@@ -529,18 +529,6 @@ __global__ __launch_bounds__(64 * WP * WQ, 2) void k_gram_frags(const u32x4* __r
             }
 }
 
-template <int NT>
-__device__ __forceinline__ double bsum(double v, double* sh) {
-    v = wave_sum(v);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    double r = 0.0;
-#pragma unroll
-    for (int w = 0; w < NT / 64; ++w) r += sh[w];
-    __syncthreads();
-    return r;
-}
-
 // out = G v + shift v (FP64 accumulation) and the block partials of v . out.
 // Each wave handles DMV_RW rows at once, so every 4-element slice of v it loads
 // serves DMV_RW rows of G (4 consecutive entries per lane per step).  No

@@ -804,13 +804,7 @@ __global__ void k_h_embed(const double* __restrict__ A, const double* __restrict
     E[i * lde + j] = v;
 }
 
-// interleaved complex vector <-> embedding [re..., im...]
-__global__ void k_h_split(int P, const double2* __restrict__ z, double* __restrict__ emb) {
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= P) return;
-    emb[p] = z[p].x;
-    emb[P + p] = z[p].y;
-}
+// embedding [re..., im...] -> interleaved complex vector
 __global__ void k_h_join(int P, const double* __restrict__ emb, double2* __restrict__ z) {
     const int p = blockIdx.x * 256 + threadIdx.x;
     if (p >= P) return;
@@ -936,9 +930,6 @@ void launch_h_axpy(hipStream_t st, int P, const double2* in, double cr, double c
 void launch_h_embed(hipStream_t st, const double* G, int P, long ld, double* E, long lde) {
     k_h_embed<<<dim3(nbk(2L * P, 256), (unsigned)(2 * P)), 256, 0, st>>>(G, G + (size_t)P * ld, P,
                                                                          ld, E, lde);
-}
-void launch_h_split(hipStream_t st, int P, const double2* z, double* emb) {
-    k_h_split<<<nbk(P, 256), 256, 0, st>>>(P, z, emb);
 }
 void launch_h_join(hipStream_t st, int P, const double* emb, double2* z) {
     k_h_join<<<nbk(P, 256), 256, 0, st>>>(P, emb, z);

@@ -52,7 +52,6 @@ struct CgScalars {
 // tables.hip
 void launch_unpack(hipStream_t st, const Dims& d, const double* p, double* Pm, int P);
 void launch_pack(hipStream_t st, const Dims& d, const double* Pm, double* p, int P);
-void launch_mask(hipStream_t st, const Dims& d, double* V);
 void launch_tables(hipStream_t st, const Dims& d, int prec, const double* Pm, const Tables& t);
 void launch_init_chains(hipStream_t st, int N, int C, uint64_t seed, int sz0, int8_t* s);
 void launch_zero(hipStream_t st, void* p, size_t bytes);
@@ -153,7 +152,6 @@ size_t qgt_th_bytes(const Dims& d, int prec, long Nsp);
 int qgt_nbw(long n, int prec);
 // activation rows to allocate for n samples (whole contraction-1 blocks)
 long qgt_act_rows(long n);
-int qgt_nbu(const Dims& d);
 int qgt_nbr(const Dims& d);   // 64-entry blocks of a CG vector (the largest partial count)
 int qgt_nbv(const Dims& d, int prec);  // CG update blocks = head partials per array
 size_t qgt_spin_bytes(const Dims& d, int prec, long Nsp);  // bytes of Sp (and of St)
@@ -246,8 +244,7 @@ void launch_cg_small(hipStream_t st, const Dims& d, const QgtBatch& q, const voi
 
 // dense.hip
 // n rows of dJ = (O - cs / nmean) / sqrt(nmean) (cs: column sums over the whole
-// batch of nmean samples); split (FP32 entries only): each
-// entry is stored as the BF16 pair (hi << 16) | lo that the BF16 Gram reads
+// batch of nmean samples)
 void launch_jacobian_centred(hipStream_t st, const Dims& d, int prec, const int8_t* s,
                              const void* tact, long n, long nmean, void* O, int P, long ld,
                              const double* cs);
@@ -337,7 +334,6 @@ void launch_h_matvec(hipStream_t st, const double* G, int P, long ld, const doub
 // out = in + c x (+ c2 x2), x and x2 embedded [re | im], c complex
 void launch_h_axpy(hipStream_t st, int P, const double2* in, double cr, double ci, const double* x,
                    double c2r, double c2i, const double* x2, double2* out);
-void launch_h_split(hipStream_t st, int P, const double2* z, double* emb);
 void launch_h_join(hipStream_t st, int P, const double* emb, double2* z);
 
 // chol.hip: (A + shift I) x = f by an in-place blocked Cholesky of the FP64

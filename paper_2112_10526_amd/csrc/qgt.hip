@@ -1536,7 +1536,6 @@ int qgt_nbw(long n, int prec) {
     return nb_of(n, prec == 0 ? 16 * W5_RT : W7_ROWS);
 }
 long qgt_act_rows(long n) { return (n + W_ROWS_MAX - 1) / W_ROWS_MAX * W_ROWS_MAX; }
-int qgt_nbu(const Dims& d) { return nb_of((long)d.Ma * d.Na, 256); }
 int qgt_nbr(const Dims& d) { return nb_of((long)d.Ma * d.Na, 64); }
 int qgt_nbv(const Dims& d, int prec) { return nb_of((long)d.Ma * d.Na, prec == 0 ? 64 : 128); }
 size_t qgt_pop_bytes(const Dims& d, int prec) {

@@ -35,16 +35,6 @@ __global__ void k_pack(Dims d, const double* __restrict__ Pm, double* __restrict
     p[idx] = Pm[(size_t)j * d.Na + i];
 }
 
-// Zero every augmented entry that is not a parameter of this model.
-__global__ void k_mask(Dims d, double* __restrict__ V) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= d.Ma * d.Na) return;
-    const int j = e / d.Na, i = e - j * d.Na;
-    const bool keep = (j < d.M && i < d.N) || (d.hb && j < d.M && i == d.N) ||
-                      (d.vb && j == d.M && i < d.N);
-    if (!keep) V[e] = 0.0;
-}
-
 // T = tanh(2 W) in two layouts, and the theta-GEMM operand W~^T (rows i <= N,
 // row N holding b), in the compute precision.
 template <typename R>
@@ -147,9 +137,6 @@ void launch_unpack(hipStream_t st, const Dims& d, const double* p, double* Pm, i
 }
 void launch_pack(hipStream_t st, const Dims& d, const double* Pm, double* p, int P) {
     k_pack<<<blocks(P, 256), 256, 0, st>>>(d, Pm, p, P);
-}
-void launch_mask(hipStream_t st, const Dims& d, double* V) {
-    k_mask<<<blocks((long)d.Ma * d.Na, 256), 256, 0, st>>>(d, V);
 }
 void launch_tables(hipStream_t st, const Dims& d, int prec, const double* Pm, const Tables& t) {
     const long n = (long)d.Na * d.Mw;
