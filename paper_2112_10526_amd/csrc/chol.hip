@@ -10,11 +10,11 @@
 // row of each.  L^T x = y walks the diagonal blocks from the last: x_k from the
 // stored inverse, then its part out of the columns before it, whose entries of L
 // are loaded ahead (they do not depend on x): one workgroup for systems of up to
-// 2,048, one launch per block above.
+// 1,024, one launch per block above.
 // The steps are a chain of dependent latencies (32 pivots at about 0.15 us each,
 // one panel after the other), so launches and passes were what could go.  n = 880:
-// 28 steps of 13.9 us (5 us of them the elimination, 3 us the loads behind the
-// previous launch) and 73 us backward, 0.48 ms; a panel and an update launch per
+// 28 steps of 13.5 us (some 5 us of them the elimination, 3 us the loads behind the
+// previous launch) and 72 us backward, 0.45 ms; a panel and an update launch per
 // step (28 + 11 us) with a left-looking backward solve took 1.31 ms.  n = 8,448 (the
 // 64-site complex model): 43 -> 33 ms.
 // A pivot that is not positive (A + shift I not positive definite) sets *bad.
@@ -255,11 +255,10 @@ __device__ __forceinline__ void chol_back_block(const double (*Yk)[CH_NB + 1], c
     xk[c] = a;
 }
 
-// L^T x = y in one workgroup, Q columns per thread (n <= 1024 Q), the columns'
-// running right-hand side in registers: per diagonal block its 32 values meet in
-// LDS, x_k, then every earlier column loses its part.  The block's rows of L are
-// loaded ahead of that chain and stay in flight across its barriers.
-template <int Q>
+// L^T x = y in one workgroup, a column per thread (n <= 1024), the columns' running
+// right-hand side in registers: per diagonal block its 32 values meet in LDS, x_k,
+// then every earlier column loses its part.  The block's rows of L are loaded ahead of
+// that chain and stay in flight across its barriers.
 __global__ __launch_bounds__(1024) void k_chol_back(const double* __restrict__ L, int n, long ld,
                                                     const double* __restrict__ Yinv,
                                                     const double* __restrict__ y,
@@ -268,42 +267,31 @@ __global__ __launch_bounds__(1024) void k_chol_back(const double* __restrict__ L
     __shared__ double sk[CH_NB], xk[CH_NB];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nblk = (n + CH_NB - 1) / CH_NB;
-    double s[Q];
-#pragma unroll
-    for (int q = 0; q < Q; ++q) s[q] = tid + 1024 * q < n ? y[tid + 1024 * q] : 0.0;
+    double s = tid < n ? y[tid] : 0.0;
     double yn = Yinv[(size_t)(nblk - 1) * CH_NB * CH_NB + tid];
     for (int kb = nblk - 1; kb >= 0; --kb) {
         const int k0 = kb * CH_NB;
         Yk[kb & 1][tid >> 5][tid & 31] = yn;  // (waits for it before the loads below)
-        double l[Q][CH_NB];
+        double l[CH_NB];
         const double* Lk = L + (long)k0 * ld;
         const int last = n - 1 - k0;  // (rows past n repeat the last one; their x is 0)
+        const unsigned i = (unsigned)min(tid, n - 1);
+        if (64 * wave < k0) {  // (the wave has earlier columns)
 #pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const unsigned i = (unsigned)min(tid + 1024 * q, n - 1);
-            if (64 * wave + 1024 * q < k0) {  // (the wave has earlier columns)
-#pragma unroll
-                for (int m = 0; m < CH_NB; ++m) l[q][m] = (Lk + (long)min(m, last) * ld)[i];
-            }
+            for (int m = 0; m < CH_NB; ++m) l[m] = (Lk + (long)min(m, last) * ld)[i];
         }
         yn = Yinv[(size_t)max(kb - 1, 0) * CH_NB * CH_NB + tid];
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const int i = tid + 1024 * q - k0;
-            if (i >= 0 && i < CH_NB) sk[i] = s[q];  // (zero past n)
-        }
+        if (tid >= k0 && tid < k0 + CH_NB) sk[tid - k0] = s;  // (zero past n)
         lds_barrier();
         chol_back_block(Yk[kb & 1], sk, xk);
         if (tid < CH_NB && k0 + tid < n) x[k0 + tid] = xk[tid];
         lds_barrier();
+        if (tid < k0) {
+            double a[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int q = 0; q < Q; ++q)
-            if (tid + 1024 * q < k0) {
-                double a[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                for (int m = 0; m < CH_NB; ++m) a[m & 3] = fma(l[q][m], xk[m], a[m & 3]);
-                s[q] -= (a[0] + a[1]) + (a[2] + a[3]);
-            }
+            for (int m = 0; m < CH_NB; ++m) a[m & 3] = fma(l[m], xk[m], a[m & 3]);
+            s -= (a[0] + a[1]) + (a[2] + a[3]);
+        }
     }
 }
 
@@ -376,10 +364,11 @@ void launch_chol_solve(hipStream_t st, double* A, int n, long ld, double shift, 
     const int nblk = (n + CH_NB - 1) / CH_NB;
     if (nblk > 1)
         k_chol_mirror<<<(unsigned)((long)nblk * (nblk - 1) / 2), 256, 0, st>>>(A, n, ld);
+    // (n = 880: 72 us in one workgroup, 28 launches of 4.4 otherwise; past 1,024 the rows of
+    // L no longer fit the workgroup's registers: whole SR solves at n = 1,056 841 us with
+    // two columns a thread, 782 in launches; 1,456: 1,276, 1,118; 1,982: 2,133, 1,794)
     if (n <= 1024) {
-        k_chol_back<1><<<1, 1024, 0, st>>>(A, n, ld, Yinv, y, x);
-    } else if (n <= 2048) {
-        k_chol_back<2><<<1, 1024, 0, st>>>(A, n, ld, Yinv, y, x);
+        k_chol_back<<<1, 1024, 0, st>>>(A, n, ld, Yinv, y, x);
     } else {
         for (int k0 = (nblk - 1) * CH_NB; k0 >= 0; k0 -= CH_NB)
             k_chol_back_step<<<k0 > 0 ? (k0 + 255) / 256 : 1, 256, 0, st>>>(A, n, ld, k0, Yinv, y,
