@@ -448,6 +448,10 @@ enum {
     NQS_PROF_PREPARE = 12,  /* per-step layout of the batch for the contractions */
     NQS_PROF_CLASSES = 13
 };
+/* The on-the-fly CG of a small FP64 system (round_up(n_hidden + 1, 16) x
+ * round_up(n_sites + 1, 16) at most 512 and, times the samples, at most 2^18) is one
+ * launch for the whole solve: it is timed as one NQS_PROF_QGT_W launch, and
+ * NQS_PROF_REDUCE and the CG's share of NQS_PROF_OUTER stay zero. */
 
 /* Time every launch of the kernel classes selected by `class_mask` (bit k =
  * class k) with HIP events on the context's stream; 0 switches timing off.

@@ -9,13 +9,15 @@
 //   w = J r + beta w_old;  z = (w - mean w) / n;  G p = J^T z;
 //   alpha = r.r / (sum z (w - mean w) + shift p.p);  x, r, and r.r, r.p, p.p.
 // Bound by the FP64 matrix cores of that one unit (n Ma Na / 32 cycles an iteration)
-// and the chain of reductions between them: 7 us an iteration at 10 sites, 10 hidden
+// and the chain of reductions between them: 5.9 us an iteration at 10 sites, 10 hidden
 // units and 1,024 samples, where the three kernels take 15 us and their gaps.
 #include "kernels.h"
 
 namespace nqs {
 
-constexpr int CS_NW = 8;        // waves (256 registers each: the activations fit)
+// waves, of 256 registers each: the activations fit (with two hidden tiles 20 registers
+// pass through scratch)
+constexpr int CS_NW = 8;
 constexpr long CS_LIMIT = 1L << 18;
 
 // Sum over the four 16-lane rows of a wave with the result scattered: lane 16 q + r

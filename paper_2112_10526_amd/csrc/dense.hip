@@ -834,7 +834,7 @@ void launch_center_cols(hipStream_t st, double* O, long n, long ld, int P, doubl
 // Edge of the BF16 Gram's tiles: 256 where nothing reads the mirrored half (a tile on
 // the diagonal holds two of G's 128 x 128 tiles of one triangle) and they are enough
 // for half the compute units (4,096 samples: P = 4,224, 153 tiles of 256, 271 us, 326
-// with 128; 3,320, 91 tiles, 254, 197 with 128).
+// with 128; 3,320, 91 tiles, 254, 180 with 128).
 int gram_edge(int P, bool mirror) {
     const int nt = (P + 255) / 256;
     return !mirror && nt * (nt + 1) / 2 >= 128 ? 256 : 128;

@@ -164,7 +164,7 @@ __global__ __launch_bounds__(256) void k_h_log_psi(int N, int M, const double2* 
 // product, product over the wave, division of an accepted move), so the next one's
 // table row and site factors are loaded while the current one is decided; with both
 // tables in LDS a call took 1-3 % less (38 x 38), not worth a second kernel.
-// 20 x 20, 256 chains, 16 segments of 20 proposals: 105 us (17 launches of 13.8 us
+// 20 x 20, 256 chains, 16 segments of 20 proposals: 116 us (17 launches of 13.8 us
 // and as many theta launches of 4.4 us when each segment was its own).
 // ---------------------------------------------------------------------------
 constexpr int H_QM = 8;  // hidden units per lane, at most (M <= 512)

@@ -309,8 +309,8 @@ __global__ __launch_bounds__(256) void k_sample(Dims d, const R* __restrict__ Tt
 // Two chains per wave when the chains pair up and a lane's registers allow (FP32 up to
 // 8 x 2 hidden units per lane, FP64 up to 4 x 2).  FP64 takes one chain per wave below
 // 2,048 chains, where the shorter chain of operations counts and not their number
-// (10x10, 200 hidden units, 4 sweeps: 1,024 chains 161 us, 187 in pairs; 4,096 chains
-// 325, 278 in pairs); in FP32 the grouping fixes the rounding, so it stays.
+// (10x10, 200 hidden units, 4 sweeps with theta: 1,024 chains 157 us, 193 in pairs;
+// 2,048 209, 207; 4,096 341, 302); in FP32 the grouping fixes the rounding, so it stays.
 int sampler_lanes(int QM, int prec, int C) {
     const bool pair = prec == 0 ? QM <= 4 && C >= 2048 : QM <= 8;
     return pair && C % 2 == 0 ? 32 : 64;

@@ -104,11 +104,12 @@ __device__ __forceinline__ float act(float th, int col, int M) {
 // 12, 14 and 17 with zero weights; MULTI: wider lattices walk the sites in chunks of G
 // groups for all rows of a block, W reloaded for each.
 // 16,384 x (100 sites, 200 hidden units) FP64, 0.76 GFLOP (12 us at the FP64 matrix
-// rate): theta 62 -> 34 us against staging W in LDS for every 64 x 64 tile with the
-// library tanh, ln psi 289 -> 41 us against a vector dot product per hidden unit.
-// 16,384 x (256 sites, 1,024 hidden units): theta FP64 492 -> 285, FP32 200 -> 150 us
+// rate): theta 62 -> 37 us against staging W in LDS for every 64 x 64 tile with the
+// library tanh, ln psi 289 -> 40 us against a vector dot product per hidden unit.
+// 16,384 x (256 sites, 1,024 hidden units): theta FP64 492 -> 296, FP32 200 -> 150 us
 // (409 and 314 in chunks of 8 groups), ln psi 2,886 -> 352 and 1,027 -> 248.
-// What is left is vector issue: conversions, tanh and the drain of 512 blocks.
+// What is left is vector issue: conversions, tanh and the drain of 512 blocks.  The
+// FP64 ln psi forms of 14 and 17 groups keep 28 to 90 of their registers in scratch.
 constexpr int TH_ST = 8;  // staging words per thread and step
 
 // (1 + f) multiplied over the 16 lanes of a DPP row, less 1
@@ -431,7 +432,7 @@ __global__ __launch_bounds__(256) void k_theta_bf16(Dims d, const int8_t* __rest
     }
 }
 
-// Rows per block: the fewest of 16, 32, 64, 128 that leave `target` blocks or more
+// Rows per block: the most of 16, 32, 64, 128 that leave `target` blocks or more
 // (16 rows where even those are fewer).
 static int theta_rows(long rows, long nby, long target) {
     int RB = 128;
