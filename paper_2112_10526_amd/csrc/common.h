@@ -87,22 +87,26 @@ __device__ __forceinline__ double dpp(double v) {
     const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true);
     return __hiloint2double(hi, lo);
 }
-// DPP controls: quad_perm [1,0,3,2] = 0xB1, [2,3,0,1] = 0x4E, row_ror:4 = 0x124,
-// row_ror:8 = 0x128.  After the four steps every lane holds its row's result.
+// DPP controls: quad_perm [1,0,3,2] = 0xB1, [2,3,0,1] = 0x4E, row_mirror = 0x140,
+// row_half_mirror = 0x141.  Each step adds what the other side adds, the two operands
+// exchanged, so after the four steps every lane holds its row's result and all hold the
+// same bits: quads q, ((q0 + q3) + (q1 + q2)).  (Rotations by 4 and 8 give the even
+// quads (q0 + q3) + (q1 + q2) and the odd ones (q0 + q1) + (q2 + q3), which may round
+// differently: a decision taken in every lane has to be the same in all of them.)
 template <typename T>
 __device__ __forceinline__ T row16_sum(T v) {
     v += dpp<0xB1>(v);
     v += dpp<0x4E>(v);
-    v += dpp<0x124>(v);
-    v += dpp<0x128>(v);
+    v += dpp<0x140>(v);
+    v += dpp<0x141>(v);
     return v;
 }
 template <typename T>
 __device__ __forceinline__ T row16_prod(T v) {
     v *= dpp<0xB1>(v);
     v *= dpp<0x4E>(v);
-    v *= dpp<0x124>(v);
-    v *= dpp<0x128>(v);
+    v *= dpp<0x140>(v);
+    v *= dpp<0x141>(v);
     return v;
 }
 __device__ __forceinline__ float readlane(float v, int l) {
