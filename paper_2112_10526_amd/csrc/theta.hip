@@ -205,9 +205,28 @@ __global__ __launch_bounds__(EPI ? 512 : 256) void k_theta(
             }
     };
     const int tile0 = (EPI ? 0 : (int)blockIdx.y * nw) + wave;
+    // ln psi of one row tile of up to 15 sites, the smallest calls: the visible part's
+    // operands are loaded along with W's, 16 lanes per row (64 rows of 10 sites, 10 units:
+    // kernel 4.7 -> 4.26 us; from two groups of sites on it does not pay)
+    constexpr bool VIS = EPI == 1 && RT == 1 && G == 1 && !MULTI;
+    double vis[4] = {0.0, 0.0, 0.0, 0.0};  // of rows 4 (wave + nw k) + lk
     if constexpr (!MULTI) {
+        int8_t sv[4];
+        double a = 0.0;
+        if constexpr (VIS) {
+            const int i = min(lr, d.N - 1);
+            if (av) a = av[i];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                sv[k] = s[(r0 + min(4 * (wave + nw * k) + lk, nr - 1)) * d.N + i];
+        }
         load_w(tile0, 0);
         stage(0);
+        if constexpr (VIS) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) vis[k] = lr < d.N ? a * (double)sv[k] : 0.0;
+            __builtin_amdgcn_sched_barrier(0);
+        }
         __syncthreads();
     }
     const int trounds = EPI ? (tiles + nw - 1) / nw : 1;
@@ -304,15 +323,25 @@ __global__ __launch_bounds__(EPI ? 512 : 256) void k_theta(
     }
     if constexpr (EPI == 1) {  // the waves' sums in order, and the visible part
         __syncthreads();
-        // (16 lanes per row; every lane stays in the loop for the row sums)
-        for (int rb = 4 * wave; rb < nr; rb += 4 * nw) {
+        // (16 lanes per row, nw <= 8; every lane stays in the loop for the row sums)
+        auto row_out = [&](int rb, double v) {
             const int row = min(rb + lk, nr - 1);
-            double v = 0.0;
-            if (av)
-                for (int i = lr; i < d.N; i += 16) v += av[i] * (double)s[(r0 + row) * d.N + i];
-            for (int w = lr; w < nw; w += 16) v += red[w * RB + row];
+            if (lr < nw) v += red[lr * RB + row];
             v = row16_sum(v);
             if (lr == 0 && rb + lk < nr) dst1[r0 + row] = (R)v;
+        };
+        if constexpr (VIS) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (4 * (wave + nw * k) < nr) row_out(4 * (wave + nw * k), vis[k]);
+        } else {
+            for (int rb = 4 * wave; rb < nr; rb += 4 * nw) {
+                const int row = min(rb + lk, nr - 1);
+                double v = 0.0;
+                if (av)
+                    for (int i = lr; i < d.N; i += 16) v += av[i] * (double)s[(r0 + row) * d.N + i];
+                row_out(rb, v);
+            }
         }
     }
 }
