@@ -207,7 +207,7 @@ __global__ __launch_bounds__(EPI ? 512 : 256) void k_theta(
     const int tile0 = (EPI ? 0 : (int)blockIdx.y * nw) + wave;
     // ln psi of one row tile of up to 15 sites, the smallest calls: the visible part's
     // operands are loaded along with W's, 16 lanes per row (64 rows of 10 sites, 10 units:
-    // kernel 4.7 -> 4.26 us; from two groups of sites on it does not pay)
+    // kernel 4.6 -> 4.13 us; from two groups of sites on it does not pay)
     constexpr bool VIS = EPI == 1 && RT == 1 && G == 1 && !MULTI;
     double vis[4] = {0.0, 0.0, 0.0, 0.0};  // of rows 4 (wave + nw k) + lk
     if constexpr (!MULTI) {
